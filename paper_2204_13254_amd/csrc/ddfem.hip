@@ -1589,16 +1589,26 @@ static void mv(Ctx& C, const Items& it, bool trans, const void* in, void* out, c
 // the scalar forms.
 static int vec_width(int nr) { return nr % 4 == 0 ? 4 : (nr % 2 == 0 ? 2 : 1); }
 
-// per-RHS block partials of x . y over n rows [n][nrhs] (kDotBlocks blocks)
+// Workgroups of a reduction over n rows [n][nrhs] with w right-hand sides to a
+// lane: one row to a lane while that takes fewer than kDotBlocks (a small
+// problem's reduction is bound by the chain over the block partials, not by
+// its rows; all kernels that share a partial buffer use the same count).
+static int dot_blocks(int64_t n, int nrhs, int w) {
+  const int lpr = 256 / (nrhs / w);
+  return (int)std::max<int64_t>(1, std::min<int64_t>(kDotBlocks, (n + lpr - 1) / lpr));
+}
+static int dot_blocks(const Ctx& C, int64_t n) { return dot_blocks(n, C.nrhs, vec_width(C.nrhs)); }
+
+// per-RHS block partials of x . y over n rows [n][nrhs] (dot_blocks blocks)
 static void dot_partial(Ctx& C, hipStream_t st, int64_t n, const double* x, const double* y, double* partial,
                         const int* skip) {
-  const int nr = C.nrhs, V = vec_width(nr);
+  const int nr = C.nrhs, V = vec_width(nr), nb = dot_blocks(C, n);
   if (V == 4)
-    hipLaunchKernelGGL((k_dot_partial_v<4>), dim3(kDotBlocks), dim3(256), 0, st, n, x, y, nr, partial, skip);
+    hipLaunchKernelGGL((k_dot_partial_v<4>), dim3(nb), dim3(256), 0, st, n, x, y, nr, partial, skip);
   else if (V == 2)
-    hipLaunchKernelGGL((k_dot_partial_v<2>), dim3(kDotBlocks), dim3(256), 0, st, n, x, y, nr, partial, skip);
+    hipLaunchKernelGGL((k_dot_partial_v<2>), dim3(nb), dim3(256), 0, st, n, x, y, nr, partial, skip);
   else
-    hipLaunchKernelGGL(k_dot_partial, dim3(kDotBlocks), dim3(256), 0, st, n, x, y, nr, partial, skip);
+    hipLaunchKernelGGL(k_dot_partial, dim3(nb), dim3(256), 0, st, n, x, y, nr, partial, skip);
 }
 
 // v[rows[k]] = sign * p[lam[k]] (B_s^T p on the listed interface rows); with
@@ -1654,16 +1664,16 @@ static void corner_scatter(Ctx& C, hipStream_t st, const T* z, T* x, T scale, co
 // Fp = sum_s B_s (u + u2) with the partials of p . Fp (p may be null)
 template <class T>
 static void scatter_dot(Ctx& C, const T* u, const T* u2, double* Fp, const double* p, const int* skip) {
-  const int nr = C.nrhs, V = vec_width(nr);
+  const int nr = C.nrhs, V = vec_width(nr), nb = dot_blocks(C, C.nlam);
   hipStream_t st = C.st;
   if (V == 4)
-    hipLaunchKernelGGL((k_scatter_dot_v<T, 4>), dim3(kDotBlocks), dim3(256), 0, st, C.nlam, C.d_lrow0, C.d_lrow1, u,
+    hipLaunchKernelGGL((k_scatter_dot_v<T, 4>), dim3(nb), dim3(256), 0, st, C.nlam, C.d_lrow0, C.d_lrow1, u,
                        u2, Fp, p, nr, C.d_partial, skip);
   else if (V == 2)
-    hipLaunchKernelGGL((k_scatter_dot_v<T, 2>), dim3(kDotBlocks), dim3(256), 0, st, C.nlam, C.d_lrow0, C.d_lrow1, u,
+    hipLaunchKernelGGL((k_scatter_dot_v<T, 2>), dim3(nb), dim3(256), 0, st, C.nlam, C.d_lrow0, C.d_lrow1, u,
                        u2, Fp, p, nr, C.d_partial, skip);
   else
-    hipLaunchKernelGGL(k_scatter_dot<T>, dim3(kDotBlocks), dim3(256), 0, st, C.nlam, C.d_lrow0, C.d_lrow1, u, u2,
+    hipLaunchKernelGGL(k_scatter_dot<T>, dim3(nb), dim3(256), 0, st, C.nlam, C.d_lrow0, C.d_lrow1, u, u2,
                        Fp, p, nr, C.d_partial, skip);
 }
 
@@ -1865,16 +1875,17 @@ template <bool FIRST>
 static void gm_project(Ctx& C, int nv, double* w, const int* stop) {
   const int nr = C.nrhs;
   const int64_t n = C.n_grow, ldv = n * nr;
+  const int nb = dot_blocks(n, nr, 1);
   hipStream_t st = C.st;
   const double* V = C.d_gmV;
   const double* ss = C.d_gm_st->ss;
   double* part = FIRST ? C.d_gm_partial : nullptr;
 #define DD_GM_PROJECT(K)                                                                                      \
-  hipLaunchKernelGGL((k_gm_project<K, FIRST>), dim3(kDotBlocks), dim3(256), 0, st, n, nv, V, ldv,             \
+  hipLaunchKernelGGL((k_gm_project<K, FIRST>), dim3(nb), dim3(256), 0, st, n, nv, V, ldv,             \
                      (const double*)C.d_gm_h, w, nr, part, ss, stop)
   if (nv <= 8 && nr % 2 == 0)
     // two right-hand sides per lane (a wider form holds too many registers)
-    hipLaunchKernelGGL((k_gm_project_v<8, FIRST, 2>), dim3(kDotBlocks), dim3(256), 0, st, n, nv, V, ldv,
+    hipLaunchKernelGGL((k_gm_project_v<8, FIRST, 2>), dim3(nb), dim3(256), 0, st, n, nv, V, ldv,
                        (const double*)C.d_gm_h, w, nr, part, ss, stop);
   else if (nv <= 8)
     DD_GM_PROJECT(8);
@@ -1901,6 +1912,7 @@ static void gmres_iteration(Ctx& C, int j) {
   const int nr = C.nrhs, m = kGmresRestart;
   hipStream_t st = C.st;
   const int64_t n = C.n_grow, nl = n * nr, ldv = nl;
+  const int nb = dot_blocks(n, nr, 1);
   double* V = C.d_gmV;
   double* w = V + (int64_t)(j + 1) * ldv;
   GmState* gs = C.d_gm_st;
@@ -1908,19 +1920,19 @@ static void gmres_iteration(Ctx& C, int j) {
   apply_G<T>(C, V + (int64_t)j * ldv, w, stop);
   // h1 = [V_0 .. V_j, w]^T w (the last entry, |w|^2, is not used)
   if (vec_width(nr) == 4)
-    hipLaunchKernelGGL((k_mdot_v<4>), dim3(kDotBlocks, (j + 2 + kMdotChunk - 1) / kMdotChunk), dim3(256), 0, st, n,
+    hipLaunchKernelGGL((k_mdot_v<4>), dim3(nb, (j + 2 + kMdotChunk - 1) / kMdotChunk), dim3(256), 0, st, n,
                        j + 2, (const double*)V, ldv, (const double*)w, nr, C.d_gm_partial, stop);
   else if (vec_width(nr) == 2)
-    hipLaunchKernelGGL((k_mdot_v<2>), dim3(kDotBlocks, (j + 2 + kMdotChunk - 1) / kMdotChunk), dim3(256), 0, st, n,
+    hipLaunchKernelGGL((k_mdot_v<2>), dim3(nb, (j + 2 + kMdotChunk - 1) / kMdotChunk), dim3(256), 0, st, n,
                        j + 2, (const double*)V, ldv, (const double*)w, nr, C.d_gm_partial, stop);
   else
-    hipLaunchKernelGGL(k_mdot, dim3(kDotBlocks, (j + 2 + kMdotChunk - 1) / kMdotChunk), dim3(256), 0, st, n, j + 2,
+    hipLaunchKernelGGL(k_mdot, dim3(nb, (j + 2 + kMdotChunk - 1) / kMdotChunk), dim3(256), 0, st, n, j + 2,
                        (const double*)V, ldv, (const double*)w, nr, C.d_gm_partial, stop);
-  hipLaunchKernelGGL(k_mdot_reduce, dim3(j + 2), dim3(256), 0, st, j + 2, nr, kDotBlocks,
+  hipLaunchKernelGGL(k_mdot_reduce, dim3(j + 2), dim3(kScalarThreads), 0, st, j + 2, nr, nb,
                      (const double*)C.d_gm_partial, C.d_gm_h, C.d_gm_tot, 1, stop);
   // w' = w - V h1 with h2 = V^T w' and |w'|^2
   gm_project<true>(C, j + 1, w, stop);
-  hipLaunchKernelGGL(k_mdot_reduce, dim3(j + 2), dim3(256), 0, st, j + 2, nr, kDotBlocks,
+  hipLaunchKernelGGL(k_mdot_reduce, dim3(j + 2), dim3(kScalarThreads), 0, st, j + 2, nr, nb,
                      (const double*)C.d_gm_partial, C.d_gm_h, C.d_gm_tot, 0, stop);
   hipLaunchKernelGGL(k_gm_givens, dim3(1), dim3(kScalarThreads), 0, st, j, nr, (const double*)C.d_gm_h,
                      (const double*)C.d_gm_tot, gs, C.d_gm_H, C.d_gm_cs, C.d_gm_sn, C.d_gm_g, m, C.opt.cg_tol,
@@ -1950,7 +1962,7 @@ static int dp2_gmres(Ctx& C, int* iters, double* relres) {
   robin_apply<T>(C, n, nullptr, (const T*)C.X[4], (const T*)nullptr, C.d_gm_rhs, nullptr);
   hipLaunchKernelGGL(k_zero<double>, dim3(nblk(nl)), dim3(256), 0, st, nl, C.d_lam2, (const int*)nullptr);
   dot_partial(C, st, n, (const double*)C.d_gm_rhs, (const double*)C.d_gm_rhs, C.d_gm_wpart, nullptr);
-  hipLaunchKernelGGL(k_gm_init, dim3(1), dim3(kScalarThreads), 0, st, nr, (const double*)C.d_gm_wpart, gs);
+  hipLaunchKernelGGL(k_gm_init, dim3(1), dim3(kScalarThreads), 0, st, nr, dot_blocks(C, n), (const double*)C.d_gm_wpart, gs);
   auto read_state = [&]() {
     HIPCHK(hipMemcpyAsync(C.h_gm_st, gs, sizeof(GmState), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
@@ -1972,7 +1984,7 @@ static int dp2_gmres(Ctx& C, int* iters, double* relres) {
       hipLaunchKernelGGL(k_rsub, dim3(nblk(nl)), dim3(256), 0, st, nl, (const double*)C.d_gm_rhs, V);
     }
     dot_partial(C, st, n, (const double*)V, (const double*)V, C.d_gm_wpart, nullptr);
-    hipLaunchKernelGGL(k_gm_cycle, dim3(1), dim3(kScalarThreads), 0, st, nr, (const double*)C.d_gm_wpart, gs,
+    hipLaunchKernelGGL(k_gm_cycle, dim3(1), dim3(kScalarThreads), 0, st, nr, dot_blocks(C, n), (const double*)C.d_gm_wpart, gs,
                        C.d_gm_g, m, cap);
     hipLaunchKernelGGL(k_vnormalize, dim3(nblk(nl)), dim3(256), 0, st, n, (const double*)V, (const double*)gs->ss,
                        V, nr, (const int*)nullptr);
@@ -2022,13 +2034,14 @@ static int dp2_gmres(Ctx& C, int* iters, double* relres) {
 }
 
 static void dot_to_host(Ctx& C, const double* x, const double* y, int64_t n, double* out) {
+  const int nb = dot_blocks(C, n);
   dot_partial(C, C.st, n, x, y, C.d_partial, nullptr);
-  HIPCHK(hipMemcpyAsync(C.h_partial, C.d_partial, sizeof(double) * kDotBlocks * kMaxRhs, hipMemcpyDeviceToHost,
+  HIPCHK(hipMemcpyAsync(C.h_partial, C.d_partial, sizeof(double) * nb * kMaxRhs, hipMemcpyDeviceToHost,
                         C.st));
   HIPCHK(hipStreamSynchronize(C.st));
   for (int r = 0; r < C.nrhs; ++r) {
     double s = 0.0;
-    for (int b = 0; b < kDotBlocks; ++b) s += C.h_partial[b * kMaxRhs + r];
+    for (int b = 0; b < nb; ++b) s += C.h_partial[b * kMaxRhs + r];
     out[r] = s;
   }
 }
@@ -2040,15 +2053,15 @@ static void dot_to_host(Ctx& C, const double* x, const double* y, int64_t n, dou
 // in flight per lane, their nonzeros in batches of 8 (batches of 12 spilled:
 // 19.65 against 19.40 ms/step; one row of 12: 19.75; four rows of 6: 20.02)
 static void lam_precond(Ctx& C, const int* skip) {
-  const int nr = C.nrhs;
+  const int nr = C.nrhs, nb = dot_blocks(C, C.nlam);
   if (vec_width(nr) == 4)
-    hipLaunchKernelGGL((k_lam_precond_v<1, 4, 4>), dim3(kDotBlocks), dim3(256), 0, C.st, C.nlam, C.d_lrp, C.d_lci,
+    hipLaunchKernelGGL((k_lam_precond_v<1, 4, 4>), dim3(nb), dim3(256), 0, C.st, C.nlam, C.d_lrp, C.d_lci,
                        C.d_lvals, (const double*)C.d_res, C.d_z, nr, C.d_partial, C.d_partial2, skip);
   else if (vec_width(nr) == 2)
-    hipLaunchKernelGGL((k_lam_precond_v<2, 4, 2>), dim3(kDotBlocks), dim3(256), 0, C.st, C.nlam, C.d_lrp, C.d_lci,
+    hipLaunchKernelGGL((k_lam_precond_v<2, 4, 2>), dim3(nb), dim3(256), 0, C.st, C.nlam, C.d_lrp, C.d_lci,
                        C.d_lvals, (const double*)C.d_res, C.d_z, nr, C.d_partial, C.d_partial2, skip);
   else
-    hipLaunchKernelGGL((k_lam_precond<2, 8>), dim3(kDotBlocks), dim3(256), 0, C.st, C.nlam, C.d_lrp, C.d_lci,
+    hipLaunchKernelGGL((k_lam_precond<2, 8>), dim3(nb), dim3(256), 0, C.st, C.nlam, C.d_lrp, C.d_lci,
                        C.d_lvals, (const double*)C.d_res, C.d_z, nr, C.d_partial, C.d_partial2, skip);
 }
 
@@ -2102,10 +2115,11 @@ static int dd_solve_once(Ctx& C, const double* b, double* x, Ctx::Warm* warm, in
     lambda_gather<T>(C, C.n_grow, C.d_code2, (const double*)C.d_lam2, (T*)X[5], nullptr, (const T*)X[2]);
   } else if (C.nlam > 0) {
     const int64_t nl = C.nlam * nr;
+    const int nb = dot_blocks(C, C.nlam);
     scatter_dot<T>(C, (const T*)X[4], (const T*)nullptr, C.d_d, (const double*)nullptr, gate);
     // ---- CG on F lambda = d (stage 0 of k_cg_scalar resets the whole state) ----
     dot_partial(C, st, C.nlam, C.d_d, C.d_d, C.d_partial, gate);
-    hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, st, 0, nr, (const double*)C.d_partial,
+    hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, st, 0, nr, nb, (const double*)C.d_partial,
                        (const double*)nullptr, C.d_cg, C.opt.cg_tol, gate);
     hipLaunchKernelGGL(k_copy, dim3(nblk(nl)), dim3(256), 0, st, nl, (const double*)C.d_d, C.d_res, gate);
     if (warm && warm->have > 0) {
@@ -2117,7 +2131,7 @@ static int dd_solve_once(Ctx& C, const double* b, double* x, Ctx::Warm* warm, in
       apply_F<T>(C, C.d_lam, C.d_Fp, nullptr);
       hipLaunchKernelGGL(k_sub, dim3(nblk(nl)), dim3(256), 0, st, nl, C.d_d, C.d_Fp, C.d_res);
       dot_partial(C, st, C.nlam, C.d_res, C.d_res, C.d_partial, nullptr);
-      hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, st, 3, nr, (const double*)C.d_partial,
+      hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, st, 3, nr, nb, (const double*)C.d_partial,
                          (const double*)nullptr, C.d_cg, C.opt.cg_tol, (const int*)nullptr);
     } else {
       hipLaunchKernelGGL(k_zero<double>, dim3(nblk(nl)), dim3(256), 0, st, nl, C.d_lam, gate);
@@ -2126,7 +2140,7 @@ static int dd_solve_once(Ctx& C, const double* b, double* x, Ctx::Warm* warm, in
     const bool pre = C.opt.precond == 1 && C.lam_nnz > 0;
     if (pre) {
       lam_precond(C, gate);
-      hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, st, 4, nr, (const double*)C.d_partial,
+      hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, st, 4, nr, nb, (const double*)C.d_partial,
                          (const double*)nullptr, C.d_cg, C.opt.cg_tol, gate);
     }
     hipLaunchKernelGGL(k_copy, dim3(nblk(nl)), dim3(256), 0, st, nl, (const double*)(pre ? C.d_z : C.d_res), C.d_p,
@@ -2147,7 +2161,7 @@ static int dd_solve_once(Ctx& C, const double* b, double* x, Ctx::Warm* warm, in
       double* pc = (k & 1) ? C.d_p2 : C.d_p;
       double* pn = (k & 1) ? C.d_p : C.d_p2;
       apply_F<T>(C, pc, C.d_Fp, done, true, true);
-      hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, st, 1, nr, (const double*)C.d_partial,
+      hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, st, 1, nr, nb, (const double*)C.d_partial,
                          (const double*)nullptr, C.d_cg, C.opt.cg_tol, (const int*)nullptr);
       if (pre) {
         if (vec_width(nr) == 4)
@@ -2160,12 +2174,13 @@ static int dd_solve_once(Ctx& C, const double* b, double* x, Ctx::Warm* warm, in
           hipLaunchKernelGGL(k_cg_xr, dim3(nblk(nl)), dim3(256), 0, st, C.nlam, nr, (const CgState*)C.d_cg,
                              (const double*)pc, (const double*)C.d_Fp, C.d_lam, C.d_res);
         lam_precond(C, done);
-        hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, st, 2, nr, (const double*)C.d_partial,
+        hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, st, 2, nr, nb, (const double*)C.d_partial,
                            (const double*)C.d_partial2, C.d_cg, C.opt.cg_tol, (const int*)nullptr);
       } else {
-        hipLaunchKernelGGL(k_cg_xr_dot, dim3(kDotBlocks), dim3(256), 0, st, C.nlam, nr, (const CgState*)C.d_cg,
+        const int nbs = dot_blocks(C.nlam, nr, 1);  // (one right-hand side to a lane)
+        hipLaunchKernelGGL(k_cg_xr_dot, dim3(nbs), dim3(256), 0, st, C.nlam, nr, (const CgState*)C.d_cg,
                            (const double*)pc, (const double*)C.d_Fp, C.d_lam, C.d_res, C.d_partial);
-        hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, st, 2, nr, (const double*)C.d_partial,
+        hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, st, 2, nr, nbs, (const double*)C.d_partial,
                            (const double*)C.d_partial, C.d_cg, C.opt.cg_tol, (const int*)nullptr);
       }
       // p' and v = B_s^T p' in multiplier order (a gather over the interface
@@ -2354,7 +2369,7 @@ static void capture_step(Ctx& C, Ctx::StepGraph& sg, const double* b, double* x,
   try {
     int* gate = reinterpret_cast<int*>(reinterpret_cast<char*>(C.d_rs) + offsetof(RefineState, gate));
     dot_partial(C, st, C.P.nint, b, b, C.d_rpart, nullptr);
-    hipLaunchKernelGGL(k_refine_init, dim3(1), dim3(kScalarThreads), 0, st, nr, (const double*)C.d_rpart, C.d_rs);
+    hipLaunchKernelGGL(k_refine_init, dim3(1), dim3(kScalarThreads), 0, st, nr, dot_blocks(C, C.P.nint), (const double*)C.d_rpart, C.d_rs);
     dd_solve_once<T>(C, b, x, nullptr, it_dummy, rr_dummy, gate, iters, 0);
     for (int k = 1; k <= sweeps + 1; ++k) {
       // only the last residual writes T x and S x (460 MB less at 64^3 with
@@ -2367,7 +2382,7 @@ static void capture_step(Ctx& C, Ctx::StepGraph& sg, const double* b, double* x,
       csr_launch(C, st, 1, x, nullptr, nullptr, nullptr, b, ca, cb, C.g_r, last ? tx : nullptr,
                  last && tx ? nullptr : gate + (k - 1), last ? sx : nullptr);
       dot_partial(C, st, C.P.nint, (const double*)C.g_r, (const double*)C.g_r, C.d_rpart, gate + (k - 1));
-      hipLaunchKernelGGL(k_refine_check, dim3(1), dim3(kScalarThreads), 0, st, k, nr, (const double*)C.d_rpart,
+      hipLaunchKernelGGL(k_refine_check, dim3(1), dim3(kScalarThreads), 0, st, k, nr, dot_blocks(C, C.P.nint), (const double*)C.d_rpart,
                          C.opt.refine_tol, C.d_rs, C.d_cg);
       if (k > sweeps) break;
       dd_solve_once<T>(C, C.g_r, C.g_t4, nullptr, it_dummy, rr_dummy, gate + k, iters, k);

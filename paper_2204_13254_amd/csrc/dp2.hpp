@@ -137,13 +137,8 @@ __global__ void __launch_bounds__(256) k_mdot(int64_t n, int nv, const double* _
   for (int k = 0; k < kMdotChunk; ++k) {
     if (k >= kn) break;
     red[tid] = s[k];
-    __syncthreads();
-    if (tid < nrhs) {
-      double t = 0.0;
-      for (int l = 0; l < lpr; ++l) t += red[l * nrhs + tid];
-      partial[((int64_t)(k0 + k) * gridDim.x + blockIdx.x) * kMaxRhs + tid] = t;
-    }
-    __syncthreads();
+    const double t = lane_sum<256>(red, lpr, nrhs);
+    if (tid < nrhs) partial[((int64_t)(k0 + k) * gridDim.x + blockIdx.x) * kMaxRhs + tid] = t;
   }
 }
 
@@ -184,43 +179,25 @@ __global__ void __launch_bounds__(256) k_mdot_v(int64_t n, int nv, const double*
     if (k >= kn) break;
 #pragma unroll
     for (int u = 0; u < V; ++u) red[tid * V + u] = s[k][u];
-    __syncthreads();
-    if (tid < nrhs) {
-      const int qq = tid / V, u = tid % V;
-      double t = 0.0;
-      for (int l = 0; l < lpr; ++l) t += red[(l * G + qq) * V + u];
-      partial[((int64_t)(k0 + k) * gridDim.x + blockIdx.x) * kMaxRhs + tid] = t;
-    }
-    __syncthreads();
+    const double t = lane_sum<256>(red, lpr, nrhs);
+    if (tid < nrhs) partial[((int64_t)(k0 + k) * gridDim.x + blockIdx.x) * kMaxRhs + tid] = t;
   }
 }
 
 // h[k][r] = sum_b partial (fixed order); with tot, tot[k][r] = h[k][r]
-// (assign) or tot[k][r] += h[k][r].  One workgroup per k: a power-of-two
-// number of lanes per right-hand side take strided block shares, then a
-// fixed-shape tree in LDS.
-__global__ void __launch_bounds__(256) k_mdot_reduce(int nv, int nrhs, int nblocks, const double* __restrict__ partial,
-                                                     double* __restrict__ h, double* __restrict__ tot, int assign,
-                                                     const int* __restrict__ skip) {
+// (assign) or tot[k][r] += h[k][r].  One workgroup of kScalarThreads per k
+// (256 threads left 64 dependent loads to a lane: 14 us against 5 us).
+__global__ void __launch_bounds__(kScalarThreads) k_mdot_reduce(int nv, int nrhs, int nblocks,
+                                                                const double* __restrict__ partial,
+                                                                double* __restrict__ h, double* __restrict__ tot,
+                                                                int assign, const int* __restrict__ skip) {
   if (skip && *skip) return;
-  __shared__ double red[256];
-  const int k = blockIdx.x;
-  const int tid = threadIdx.x;
-  int lpr = 1;  // lanes per right-hand side: a power of two, so the tree halves evenly
-  while (2 * lpr * nrhs <= 256) lpr *= 2;
-  const int r = tid % nrhs, lane = tid / nrhs;
-  double s = 0.0;
-  if (lane < lpr)
-    for (int b = lane; b < nblocks; b += lpr) s += partial[((int64_t)k * nblocks + b) * kMaxRhs + r];
-  red[tid] = s;
-  __syncthreads();
-  for (int half = lpr / 2; half > 0; half /= 2) {
-    if (lane < half) red[tid] += red[tid + half * nrhs];
-    __syncthreads();
-  }
+  __shared__ double part[kScalarThreads];
+  const int k = blockIdx.x, tid = threadIdx.x;
+  const double t = partial_total(partial + (int64_t)k * nblocks * kMaxRhs, nblocks, nrhs, part);
   if (tid < nrhs) {
-    h[k * kMaxRhs + tid] = red[tid];
-    if (tot) tot[k * kMaxRhs + tid] = assign ? red[tid] : tot[k * kMaxRhs + tid] + red[tid];
+    h[k * kMaxRhs + tid] = t;
+    if (tot) tot[k * kMaxRhs + tid] = assign ? t : tot[k * kMaxRhs + tid] + t;
   }
 }
 
@@ -241,7 +218,7 @@ __global__ void __launch_bounds__(256) k_mupdate(int64_t n, int nv, const double
 // The two projections of classical Gram-Schmidt applied twice on the new
 // vector w = V_{j+1} against the basis V_0 .. V_j (nv = j + 1 vectors, nv <=
 // KMAX), each one pass over the basis.  Grid-stride over rows (layout
-// [n][nrhs]), kDotBlocks workgroups; the coefficients h [k][kMaxRhs] are
+// [n][nrhs]), dot_blocks workgroups; the coefficients h [k][kMaxRhs] are
 // staged in LDS.
 //  first:  w' = w - sum_k h1_k V_k, with the block partials of V_k . w' (k <
 //          nv) and of |w'|^2 (index nv), for the second projection
@@ -296,13 +273,8 @@ __global__ void __launch_bounds__(256) k_gm_project(int64_t n, int nv, const dou
   for (int k = 0; k <= KMAX; ++k) {
     if (k > nv) break;
     red[tid] = k < nv ? dots[k < KMAX ? k : 0] : nn;
-    __syncthreads();
-    if (tid < nrhs) {
-      double t = 0.0;
-      for (int l2 = 0; l2 < lpr; ++l2) t += red[l2 * nrhs + tid];
-      partial[((int64_t)k * gridDim.x + blockIdx.x) * kMaxRhs + tid] = t;
-    }
-    __syncthreads();
+    const double t = lane_sum<256>(red, lpr, nrhs);
+    if (tid < nrhs) partial[((int64_t)k * gridDim.x + blockIdx.x) * kMaxRhs + tid] = t;
   }
 }
 
@@ -377,14 +349,8 @@ __global__ void __launch_bounds__(256) k_gm_project_v(int64_t n, int nv, const d
     if (k > nv) break;
 #pragma unroll
     for (int u = 0; u < V; ++u) red[tid * V + u] = k < nv ? dots[k < KMAX ? k : 0][u] : nn[u];
-    __syncthreads();
-    if (tid < nrhs) {
-      const int qq = tid / V, u = tid % V;
-      double t = 0.0;
-      for (int l2 = 0; l2 < lpr; ++l2) t += red[(l2 * G + qq) * V + u];
-      partial[((int64_t)k * gridDim.x + blockIdx.x) * kMaxRhs + tid] = t;
-    }
-    __syncthreads();
+    const double t = lane_sum<256>(red, lpr, nrhs);
+    if (tid < nrhs) partial[((int64_t)k * gridDim.x + blockIdx.x) * kMaxRhs + tid] = t;
   }
 }
 
@@ -424,30 +390,13 @@ struct GmState {
   int jmax;                // columns of the cycle's update (the largest cols)
 };
 
-// fixed-order total of kDotBlocks block partials ([kDotBlocks][kMaxRhs]) of
-// right-hand side threadIdx.x (valid for threadIdx.x < nrhs) by a workgroup
-// of kScalarThreads threads
-__device__ __forceinline__ double gm_total(const double* __restrict__ pa, int nrhs, double* part) {
-  const int t = threadIdx.x, lpr = blockDim.x / nrhs, rr = t % nrhs, ln = t / nrhs;
-  double a = 0.0;
-  if (ln < lpr)
-    for (int b = ln; b < kDotBlocks; b += lpr) a += pa[b * kMaxRhs + rr];
-  part[t] = a;
-  __syncthreads();
-  double v = 0.0;
-  if (t < nrhs)
-    for (int l = 0; l < lpr; ++l) v += part[l * nrhs + t];
-  __syncthreads();
-  return v;
-}
-
 // start of the solve: partial = block partials of |rhs|^2
-__global__ void __launch_bounds__(kScalarThreads) k_gm_init(int nrhs, const double* __restrict__ partial,
+__global__ void __launch_bounds__(kScalarThreads) k_gm_init(int nrhs, int nb, const double* __restrict__ partial,
                                                             GmState* __restrict__ st) {
   __shared__ double part[kScalarThreads];
   __shared__ int any_open;
   if (threadIdx.x == 0) any_open = 0;
-  const double s = gm_total(partial, nrhs, part);
+  const double s = partial_total(partial, nb, nrhs, part);
   const int r = threadIdx.x;
   if (r < nrhs) {
     const double b = sqrt(s > 0.0 ? s : 0.0);
@@ -467,13 +416,13 @@ __global__ void __launch_bounds__(kScalarThreads) k_gm_init(int nrhs, const doub
 }
 
 // start of a restart cycle: partial = block partials of |r0|^2; g = |r0| e_1
-__global__ void __launch_bounds__(kScalarThreads) k_gm_cycle(int nrhs, const double* __restrict__ partial,
+__global__ void __launch_bounds__(kScalarThreads) k_gm_cycle(int nrhs, int nb, const double* __restrict__ partial,
                                                              GmState* __restrict__ st, double* __restrict__ g, int m,
                                                              int cap) {
   __shared__ double part[kScalarThreads];
   __shared__ int any_open;
   if (threadIdx.x == 0) any_open = 0;
-  const double s = gm_total(partial, nrhs, part);
+  const double s = partial_total(partial, nb, nrhs, part);
   const int r = threadIdx.x;
   if (r < nrhs) {
     st->ss[r] = s;

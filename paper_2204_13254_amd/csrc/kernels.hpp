@@ -656,24 +656,42 @@ __device__ __forceinline__ void vstore(T* __restrict__ p, const T (&o)[V]) {
   }
 }
 
+// Sum over l < lpr of red[l nrhs + r] for right-hand side r = threadIdx.x
+// (valid for threadIdx.x < nrhs): halving steps by the whole workgroup of NT
+// threads down to 8 rows, then those in order.  Fixed shape, so the result
+// does not depend on timing.  Bound by the length of its dependent chain: one
+// thread adding all lpr rows (1024 of them at one RHS) took 18 us in
+// k_cg_scalar, against 4.9 us with the halving.  Every thread calls it; red
+// is consumed; ends with a barrier.
+template <int NT>
+__device__ __forceinline__ double lane_sum(double* red, int lpr, int nrhs) {
+  int n = lpr;
+  while (n > 8) {
+    const int h = (n + 1) / 2;
+    __syncthreads();
+    for (int e = threadIdx.x; e < (n - h) * nrhs; e += NT) red[e] += red[e + h * nrhs];
+    n = h;
+  }
+  __syncthreads();
+  double t = 0.0;
+  if ((int)threadIdx.x < nrhs)
+    for (int l = 0; l < n; ++l) t += red[l * nrhs + threadIdx.x];
+  __syncthreads();
+  return t;
+}
+
 // block partials of per-RHS sums held V to a lane: lane (l, q), l < lpr,
-// q < G = nrhs / V, holds right-hand sides q V .. q V + V - 1; summed over l
-// in lane order.  Ends with a barrier (callable twice in a row).
+// q < G = nrhs / V, holds right-hand sides q V .. q V + V - 1 (so red holds
+// lane l's row of nrhs values).  Ends with a barrier (callable twice in a row).
 template <int V>
 __device__ __forceinline__ void block_rhs_sum_v(const double (&s)[V], int nrhs, int lpr,
                                                 double* __restrict__ partial) {
   __shared__ double red[256 * V];
-  const int tid = threadIdx.x, G = nrhs / V;
+  const int tid = threadIdx.x;
 #pragma unroll
   for (int v = 0; v < V; ++v) red[tid * V + v] = s[v];
-  __syncthreads();
-  if (tid < nrhs) {
-    const int q = tid / V, v = tid % V;
-    double t = 0.0;
-    for (int l = 0; l < lpr; ++l) t += red[(l * G + q) * V + v];
-    partial[blockIdx.x * kMaxRhs + tid] = t;
-  }
-  __syncthreads();
+  const double t = lane_sum<256>(red, lpr, nrhs);
+  if (tid < nrhs) partial[blockIdx.x * kMaxRhs + tid] = t;
 }
 
 struct MvOut {
@@ -2201,7 +2219,7 @@ __global__ void __launch_bounds__(256) k_newmark_load(int64_t n, const double* _
 // K8: conjugate gradients on the interface system, per right-hand side.
 // Dot products: fixed-order two-stage reductions (deterministic).
 // --------------------------------------------------------------------------
-constexpr int kDotBlocks = 1024;
+constexpr int kDotBlocks = 1024;  // most workgroups of a reduction (and of the partial buffers)
 
 __global__ void __launch_bounds__(256) k_dot_partial(int64_t n, const double* __restrict__ x,
                                                      const double* __restrict__ y, int nrhs,
@@ -2220,12 +2238,8 @@ __global__ void __launch_bounds__(256) k_dot_partial(int64_t n, const double* __
       s += x[row * nrhs + r] * y[row * nrhs + r];
   }
   red[tid] = s;
-  __syncthreads();
-  if (tid < nrhs) {
-    double t = 0.0;
-    for (int l = 0; l < lanes_per_rhs; ++l) t += red[l * nrhs + tid];
-    partial[blockIdx.x * kMaxRhs + tid] = t;
-  }
+  const double t = lane_sum<256>(red, lanes_per_rhs, nrhs);
+  if (tid < nrhs) partial[blockIdx.x * kMaxRhs + tid] = t;
 }
 
 // Vector form of k_dot_partial: V right-hand sides per lane (nrhs a
@@ -2258,12 +2272,8 @@ __device__ __forceinline__ void block_rhs_sum(double s, int nrhs, int lanes_per_
   __shared__ double red[256];
   const int tid = threadIdx.x;
   red[tid] = s;
-  __syncthreads();
-  if (tid < nrhs) {
-    double t = 0.0;
-    for (int l = 0; l < lanes_per_rhs; ++l) t += red[l * nrhs + tid];
-    partial[blockIdx.x * kMaxRhs + tid] = t;
-  }
+  const double t = lane_sum<256>(red, lanes_per_rhs, nrhs);
+  if (tid < nrhs) partial[blockIdx.x * kMaxRhs + tid] = t;
 }
 
 // F p = sum_s B_s u_s (each multiplier pulls its two copies, + lo, - hi),
@@ -2395,10 +2405,27 @@ struct CgState {
 // stage: 0 = init (rr = rr0 = rz = sum A), 1 = alpha = rz / (sum A = p.Fp),
 //        2 = beta (sum A = new r.z, sum B = new r.r), 3 = warm start (rr = rz =
 //        sum A, convergence flags only), 4 = preconditioned start (rz = sum A)
-// One workgroup of kScalarThreads threads (the first level of the sum is
-// kDotBlocks / lanes deep; with 1024 threads a short chain of L2 loads).
+// One workgroup of kScalarThreads threads; nb = workgroups of the kernel that
+// wrote the partials (the first level of the sum is nb / lanes deep).
 constexpr int kScalarThreads = 1024;
-__global__ void __launch_bounds__(kScalarThreads) k_cg_scalar(int stage, int nrhs, const double* __restrict__ partial,
+
+// fixed-order two-level sum of the nb block partials ([nb][kMaxRhs]) of
+// right-hand side threadIdx.x (valid for threadIdx.x < nrhs): thread t sums
+// blocks t / nrhs, t / nrhs + L, ... of rhs t % nrhs, then the L lanes are
+// added by halving.  Workgroup of kScalarThreads threads.
+__device__ __forceinline__ double partial_total(const double* __restrict__ pa, int nb, int nrhs, double* part) {
+  const int t = threadIdx.x, lpr = min(kScalarThreads / nrhs, nb), rr = t % nrhs, ln = t / nrhs;
+  double a = 0.0;
+  if (ln < lpr) {
+#pragma unroll 4
+    for (int b = ln; b < nb; b += lpr) a += pa[b * kMaxRhs + rr];
+  }
+  part[t] = a;
+  return lane_sum<kScalarThreads>(part, lpr, nrhs);
+}
+
+__global__ void __launch_bounds__(kScalarThreads) k_cg_scalar(int stage, int nrhs, int nb,
+                                                              const double* __restrict__ partial,
                                                               const double* __restrict__ partial_b,
                                                               CgState* __restrict__ st, double tol,
                                                               const int* __restrict__ gate) {
@@ -2408,24 +2435,8 @@ __global__ void __launch_bounds__(kScalarThreads) k_cg_scalar(int stage, int nrh
   __shared__ int any_active;
   if (r == 0) any_active = 0;
   __syncthreads();
-  // fixed-order two-level sum of the block partials: thread t sums blocks
-  // t/nrhs, t/nrhs + L, ... of rhs t%nrhs, then lanes are added in order
   __shared__ double part[kScalarThreads];
-  auto total = [&](const double* pa) -> double {
-    const int t = threadIdx.x, lpr = blockDim.x / nrhs, rr = t % nrhs, ln = t / nrhs;
-    double a = 0.0;
-    if (ln < lpr) {
-#pragma unroll 4
-      for (int b = ln; b < kDotBlocks; b += lpr) a += pa[b * kMaxRhs + rr];
-    }
-    part[t] = a;
-    __syncthreads();
-    double v = 0.0;
-    if (t < nrhs)
-      for (int l = 0; l < lpr; ++l) v += part[l * nrhs + t];
-    __syncthreads();
-    return v;
-  };
+  auto total = [&](const double* pa) -> double { return partial_total(pa, nb, nrhs, part); };
   const double s = total(partial);
   const double sb = stage == 2 ? total(partial_b) : 0.0;
   if (stage == 0 && r == 0) st->breakdown = 0;  // stage 0 resets the whole state
@@ -3098,36 +3109,21 @@ struct RefineState {
   int done[kMaxGraphSweeps + 1], breakdown[kMaxGraphSweeps + 1];
 };
 
-// fixed-order sum of the kDotBlocks partials of rhs r ([kDotBlocks][kMaxRhs])
-__device__ double partial_total(const double* __restrict__ pa, int nrhs, double* part) {
-  const int t = threadIdx.x, lpr = blockDim.x / nrhs, rr = t % nrhs, ln = t / nrhs;
-  double a = 0.0;
-  if (ln < lpr)
-    for (int b = ln; b < kDotBlocks; b += lpr) a += pa[b * kMaxRhs + rr];
-  part[t] = a;
-  __syncthreads();
-  double v = 0.0;
-  if (t < nrhs)
-    for (int l = 0; l < lpr; ++l) v += part[l * nrhs + t];
-  __syncthreads();
-  return v;
-}
-
 // clear the state; bn from the partials of b . b; gate[0] = 0
-__global__ void __launch_bounds__(kScalarThreads) k_refine_init(int nrhs, const double* __restrict__ partial,
+__global__ void __launch_bounds__(kScalarThreads) k_refine_init(int nrhs, int nb, const double* __restrict__ partial,
                                                                 RefineState* __restrict__ rs) {
   __shared__ double part[kScalarThreads];
   int* w = reinterpret_cast<int*>(rs);
   for (size_t k = threadIdx.x; k < sizeof(RefineState) / sizeof(int); k += blockDim.x) w[k] = 0;
   __syncthreads();
-  const double s = partial_total(partial, nrhs, part);
+  const double s = partial_total(partial, nb, nrhs, part);
   if ((int)threadIdx.x < nrhs) rs->bn[threadIdx.x] = s;
 }
 
 // after solve k-1 (k >= 1): gres[k-1] = |r| / |b| from the partials of r . r,
 // gate[k] = 1 when every RHS meets tol (the CG state is then marked done, so
 // the gated solve's CG kernels return at once); a closed gate stays closed
-__global__ void __launch_bounds__(kScalarThreads) k_refine_check(int k, int nrhs, const double* __restrict__ partial,
+__global__ void __launch_bounds__(kScalarThreads) k_refine_check(int k, int nrhs, int nb, const double* __restrict__ partial,
                                                                  double tol, RefineState* __restrict__ rs,
                                                                  CgState* __restrict__ cg) {
   __shared__ double part[kScalarThreads];
@@ -3138,7 +3134,7 @@ __global__ void __launch_bounds__(kScalarThreads) k_refine_check(int k, int nrhs
   }
   if (threadIdx.x == 0) all_ok = 1;
   __syncthreads();
-  const double s = partial_total(partial, nrhs, part);
+  const double s = partial_total(partial, nb, nrhs, part);
   const int r = threadIdx.x;
   if (r < nrhs) {
     const double bn = rs->bn[r];

@@ -1,0 +1,54 @@
+"""Shapes where the launch rules of the solve change: problems smaller than a
+full reduction grid, right-hand-side counts on either side of each product
+form, against the monolithic oracle."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle.newmark import NewmarkOracle
+from workloads.mesh import cube_mesh
+from workloads.partition import box_partition
+from workloads.sources import dense_random_source
+
+pytestmark = pytest.mark.gpu
+
+
+def _steps(n, parts, nrhs, precision, N=2, **opt):
+    """Relative error of N Newmark steps from rest, largest over steps and RHS."""
+    from paper_2204_13254_amd.solver import DDSolver
+    c, t, _ = cube_mesh(n)
+    p = box_partition(n, parts)
+    eps = np.random.default_rng(n).uniform(1, 4, len(t))
+    dt = 0.4 / n
+    o = NewmarkOracle(c, t, eps=eps, dt=dt)
+    J = dense_random_source(o.d.n_e, ~o.d.pec, N, dt, dt, dt, seed=1, nrhs=nrhs)
+    Eo = o.run(J)
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        s = DDSolver(c, t, p, eps, dt=dt, nrhs=nrhs, precision=precision, stream=st,
+                     cg_tol=1e-13 if precision == "fp64" else 1e-6, **opt)
+        Jd = torch.tensor(J, device="cuda")
+        z = torch.zeros((nrhs, s.n_edges), dtype=torch.float64, device="cuda")
+        E = [z, z.clone()]
+        for k in range(N):
+            E.append(s.step(Jd[k], Jd[k - 1] if k else z, E[-1], E[-2]))
+        out = torch.stack(E[2:]).cpu().numpy()
+    return max(np.linalg.norm(out[k] - Eo[k + 1], axis=1).max() / np.linalg.norm(Eo[k + 1], axis=1).min()
+               for k in range(N))
+
+
+# the bars of the parity tests: 1e-10 in FP64, 1e-8 with FP32 factors
+BAR = {"fp64": 1e-10, "fp32_refine": 1e-8}
+
+
+@pytest.mark.parametrize("nrhs", [1, 2, 3, 7, 13, 31])
+@pytest.mark.parametrize("precision", ["fp64", "fp32_refine"])
+def test_reductions_of_a_few_workgroups(nrhs, precision):
+    assert _steps(5, (2, 2, 1), nrhs, precision) <= BAR[precision]
+
+
+@pytest.mark.parametrize("opt", [dict(precond=0), dict(method="dp2")])
+@pytest.mark.parametrize("nrhs", [1, 5])
+def test_reductions_of_the_other_solvers(opt, nrhs):
+    assert _steps(5, (1, 2, 2), nrhs, "fp64", **opt) <= BAR["fp64"]
