@@ -1546,10 +1546,6 @@ static void mv_dispatch(Ctx& C, hipStream_t s, const Items& it, bool trans, cons
     mv_launch<T, 1, 0, CLS, 0>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip);
   else if (nr == 2)
     mv_launch<T, 2, 0, CLS, 0>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip);
-  else if (nr <= 4)
-    mv_launch<T, 4, 0, CLS, 0>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip);
-  else if (nr <= 8)
-    mv_launch<T, 8, 0, CLS, 0>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip);
   else if (nr == 16)
     mv_launch<T, 0, 1, CLS, 16>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip);
   else if (nr < 16)

@@ -595,9 +595,12 @@ __global__ void k_pull_coarse(int64_t n, const int64_t* __restrict__ ptr, const 
 // reduction inside this kernel needs device-scope release/acquire fences,
 // which write back / invalidate the per-XCD L2 and cost far more than the
 // extra launch.)
-// Modes: nrhs <= NV uses vector FMAs (lanes of a column group reduced with
-// cross-lane shuffles); nrhs in 9..32 uses MFMA 16x16x4 in 16-wide RHS
-// blocks (NB16 of them).
+// Modes: one or two right-hand sides use vector FMAs (lanes of a column group
+// reduced with cross-lane shuffles); 3..32 use MFMA 16x16x4 in 16-wide RHS
+// blocks (NB16 of them), zero-padded: the pass is bound by its tile loads, so
+// the padding costs nothing.  Where the line lies (24^3, 64 boxes, solve, FP32
+// factors): 2.08 / 2.18 ms at 1 / 2 RHS with vector FMAs, 2.3 ms at 3..8 with
+// MFMA, where vector FMAs took 3.8 ms (3 RHS) to 6.8 ms (8).
 // --------------------------------------------------------------------------
 struct MvItem {
   int32_t s, o, lo, hi;  // subdomain, output block, tile range [lo, hi)
@@ -774,9 +777,9 @@ __global__ void __launch_bounds__(256) k_tile_mv(int64_t n_items, const MvItem* 
     }
     // factor values of the current / next tile, and (prefetched together with
     // them) the input values the lane needs: MFMA path bv[nb][ks] = x[8g+ks][nb*16+i],
-    // vector path (NV <= 2) x[8g+ks][r]; wider vector paths load x inline
-    constexpr bool PX = MF || NV <= 2;
-    constexpr int NX = PX ? 8 * (MF ? NB16 : NV) : 1;
+    // vector path x[8g+ks][r]
+    static_assert(NV <= 2, "the vector path keeps its input values in registers");
+    constexpr int NX = 8 * (MF ? NB16 : NV);
     T cur[16], nxt[16], xc[NX], xn[NX];
     auto tile_ptr = [&](int m) -> const T* {
       const int ti = trans ? m : w.o, tj = trans ? w.o : m;
@@ -788,17 +791,21 @@ __global__ void __launch_bounds__(256) k_tile_mv(int64_t n_items, const MvItem* 
     auto load_x = [&](int m, T* xv) {
       const T* xb = xbase + (int64_t)m * kNB * nrhs;
       if constexpr (MF) {
+        // the row of step ks as a wave-uniform base plus one lane offset for
+        // all of them (eight lane addresses per block cost more than the
+        // products at 3..15 RHS)
 #pragma unroll
         for (int nb = 0; nb < NB16; ++nb) {
           const int col = nb * 16 + i;
-          const int cc = col < nrhs ? col : nrhs - 1;
+          const unsigned off = 8u * g * nrhs + (unsigned)(col < nrhs ? col : nrhs - 1);
 #pragma unroll
           for (int ks = 0; ks < 8; ++ks) {
-            const T v = xb[(8 * g + ks) * nrhs + cc];
+            const T* xk = xb + ks * nrhs;
+            const T v = xk[off];
             xv[nb * 8 + ks] = col < nrhs ? v : (T)0;
           }
         }
-      } else if constexpr (PX) {
+      } else {
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks)
 #pragma unroll
@@ -854,42 +861,23 @@ __global__ void __launch_bounds__(256) k_tile_mv(int64_t n_items, const MvItem* 
     }
     // vector path: one tile in flight
     for (int k = w.lo; k < (MF ? w.lo : w.hi); ++k) {
-      const int m = ent(k) & kListMask;
       if (k + 1 < w.hi) {
         const int32_t e1 = ent(k + 1);
         load_tile(e1, nxt);
         load_x(e1 & kListMask, xn);
       }
-      if constexpr (PX) {
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks)
+      for (int ks = 0; ks < 8; ++ks)
 #pragma unroll
-          for (int r = 0; r < NV; ++r) {
-            vacc[r] += cur[ks] * xc[ks * NV + r];
-            vacc[NV + r] += cur[8 + ks] * xc[ks * NV + r];
-          }
-      } else {
-        const T* xb = xbase + (int64_t)m * kNB * nrhs;
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-          const T* xr = xb + (8 * g + ks) * nrhs;
-#pragma unroll
-          for (int r = 0; r < NV; ++r) {
-            if (r < nrhs) {
-              const T xv = xr[r];
-              vacc[r] += cur[ks] * xv;
-              vacc[NV + r] += cur[8 + ks] * xv;
-            }
-          }
+        for (int r = 0; r < NV; ++r) {
+          vacc[r] += cur[ks] * xc[ks * NV + r];
+          vacc[NV + r] += cur[8 + ks] * xc[ks * NV + r];
         }
-      }
       if (k + 1 < w.hi) {
 #pragma unroll
         for (int u = 0; u < 16; ++u) cur[u] = nxt[u];
-        if constexpr (PX) {
 #pragma unroll
-          for (int u = 0; u < NX; ++u) xc[u] = xn[u];
-        }
+        for (int u = 0; u < NX; ++u) xc[u] = xn[u];
       }
     }
     // ---- epilogue ------------------------------------------------------------
@@ -995,10 +983,11 @@ __global__ void __launch_bounds__(256) k_tile_mv2(int64_t n_items, const MvItem*
 #pragma unroll
       for (int nb = 0; nb < NB16; ++nb) {
         const int col = nb * 16 + i;
-        const int cc = col < nrhs ? col : nrhs - 1;
+        const unsigned off = 8u * g * nrhs + (unsigned)(col < nrhs ? col : nrhs - 1);
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) {
-          const T v = xb[(8 * g + ks) * nrhs + cc];
+          const T* xk = xb + ks * nrhs;
+          const T v = xk[off];
           xv[nb * 8 + ks] = col < nrhs ? v : (T)0;
         }
       }
@@ -1303,10 +1292,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LD == 
 #pragma unroll
       for (int nb = 0; nb < NB16; ++nb) {
         const int col = nb * 16 + i;
-        const int cc = col < nrhs ? col : nrhs - 1;
+        const unsigned off = 8u * g * nrhs + (unsigned)(col < nrhs ? col : nrhs - 1);
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) {
-          const T v = xb[(8 * g + ks) * nrhs + cc];
+          const T* xk = xb + ks * nrhs;
+          const T v = xk[off];
           xv[nb * 8 + ks] = col < nrhs ? v : (T)0;
         }
       }
