@@ -97,6 +97,7 @@ struct Items {
   void* partial = nullptr;   // own partial slots (lists that run beside others), or null
   bool pair = false;         // row-pair items (k_tile_mv2)
   bool oct = false;          // row-octet workgroup items (k_tile_mv8)
+  bool rows4 = false;        // one workgroup of kRowWaves waves per item (k_tile_mvw)
 };
 
 // Work-list shapes (longest tile range of one wave per product class, and
@@ -256,6 +257,7 @@ struct Ctx {
   int64_t *d_lrow0 = nullptr, *d_lrow1 = nullptr;
   int64_t *d_cgptr = nullptr, *d_cgrows = nullptr;  // coarse gather
   int64_t n_csc = 0;
+  int32_t* d_crow = nullptr;  // [rows_total] coarse row of a subdomain corner row (-1: none)
   int64_t *d_cscrows = nullptr, *d_csccrow = nullptr;  // corner scatter
   int64_t* d_dsrc = nullptr;
   int32_t *d_interior = nullptr, *d_dof = nullptr, *d_tdof = nullptr;
@@ -414,7 +416,36 @@ static std::vector<It> place_xcd(int nsub, const std::vector<It>& v, const It& p
   return placed;
 }
 
-static Items make_items(Ctx& C, const std::vector<MvItem>& blocks, int chunk, bool grouped = false, int bucket = 1) {
+// Whether a list takes the row-group form (k_tile_mvw).  A wave streams its
+// row's tiles one after the other, so a list of few rows takes as long as the
+// longest row's chain of loads: four waves share a row while all rows together
+// stay within 8192 waves (32 on each of the 256 CUs), an average row gives
+// every wave two tiles, and no row is longer than four default coarse chunks
+// (beyond that the split lists are faster: the coarse passes of a graded 48^3
+// case with rows of 200 tiles and more took 122 us grouped against 73 us
+// split plus a 20 us reduce).
+static bool row_groups(const std::vector<MvItem>& blocks) {
+  int64_t tiles = 0, longest = 0;
+  for (const MvItem& b : blocks) {
+    tiles += b.hi - b.lo;
+    longest = std::max<int64_t>(longest, b.hi - b.lo);
+  }
+  const int64_t rows = (int64_t)blocks.size();
+  return rows > 0 && rows * kRowWaves <= 8192 && tiles >= 2 * kRowWaves * rows && longest <= 16 * kRowWaves;
+}
+
+static Items make_items(Ctx& C, const std::vector<MvItem>& blocks, int chunk, bool grouped = false, int bucket = 1,
+                        bool one_wave = false) {
+  if (!one_wave && row_groups(blocks)) {
+    std::vector<MvItem> placed = place_xcd(
+        C.nsub, blocks, MvItem{-1, 0, 0, 0, -1, 0}, [](const MvItem& a) { return a.s; },
+        [](const MvItem& a) { return (int64_t)(a.hi - a.lo); }, grouped ? bucket : 1, 1);
+    Items it;
+    it.n = (int64_t)placed.size();
+    it.d = upload(placed, C.owned, C.st);
+    it.rows4 = true;
+    return it;
+  }
   bool split = false;
   for (const MvItem& b : blocks)
     if (b.hi - b.lo > chunk) split = true;
@@ -823,6 +854,10 @@ static void build_device(Ctx& C, const double* coords) {
     C.n_csc = (int64_t)cscrows.size();
     C.d_cscrows = upload(cscrows, C.owned, st);
     C.d_csccrow = upload(csccrow, C.owned, st);
+    std::vector<int32_t> crow(C.rows_total, -1);
+    if (C.rows_total > INT32_MAX) throw DDError{DD_ERR_OOM, "too many local rows"};
+    for (size_t k = 0; k < cscrows.size(); ++k) crow[cscrows[k]] = (int32_t)csccrow[k];
+    C.d_crow = upload(crow, C.owned, st);
     // multipliers
     C.nlam = P.nlambda();
     std::vector<int64_t> r0(C.nlam), r1(C.nlam);
@@ -962,7 +997,7 @@ static void build_device(Ctx& C, const double* coords) {
     C.corner_N = make_items(C, cN, C.tuning.chunk);
     // (summing the symmetric partials inside this pass instead of a reduce on
     // the side stream measured slower: it lengthens the main-stream chain)
-    C.corner_T = make_items(C, cT, C.tuning.chunk);
+    C.corner_T = make_items(C, cT, C.tuning.chunk, false, 1, true);
     C.co_N = make_items(C, oN, C.tuning.chunk);
     C.co_T = make_items(C, oT, C.tuning.chunk);
     C.blk_corner_N.swap(cN);
@@ -1266,7 +1301,7 @@ static void build_full_items(Ctx& C) {
       pb.push_back({a.s, a.o, b0, (int32_t)pl.size(), -1, 0, b.o, -1});
       ++k;
     }
-    it = make_items(C, pb, C.tuning.full_chunk, true, C.tuning.full_bucket);
+    it = make_items(C, pb, C.tuning.full_chunk, true, C.tuning.full_bucket, true);
     it.mlist = upload(pl, C.owned, C.st);
     it.pair = true;
   };
@@ -1502,7 +1537,7 @@ static int item_class(const Ctx& C, const Items& it) {
 
 template <class T, int NV, int NB16, int CLS, int LD>
 static void mv_launch(Ctx& C, hipStream_t s, const Items& it, bool trans, const void* in, void* out, const void* add,
-                      T alpha, const void* add_c, T alpha_c, const int* skip) {
+                      T alpha, const void* add_c, T alpha_c, const int* skip, const int32_t* crow) {
   const bool split = it.n_out > 0;
   const T* tiles = (const T*)(trans ? C.d_tilesT : C.d_tiles);
   T* partial = (T*)(it.partial ? it.partial : C.d_partial_mv);
@@ -1518,19 +1553,35 @@ static void mv_launch(Ctx& C, hipStream_t s, const Items& it, bool trans, const 
       hipLaunchKernelGGL((k_tile_mv8<T, NB16, CLS, LD>), dim3((unsigned)g8), dim3(256), 0, s, it.n, it.d, C.d_subs,
                          tiles, (const T*)in, (T*)out, (const T*)add, alpha, (const T*)add_c, alpha_c, C.nrhs,
                          (int)trans, (const int32_t*)it.mlist, skip, (const T*)C.d_zero_tile);
-    } else if (it.pair) {
+      return;
+    }
+    if (it.pair) {
       hipLaunchKernelGGL((k_tile_mv2<T, NB16, CLS, LD>), dim3((unsigned)grid), dim3(256), 0, s, it.n, it.d, C.d_subs,
                          tiles, (const T*)in, (T*)out, (const T*)add, alpha, (const T*)add_c, alpha_c, C.nrhs,
                          (int)trans, partial, (const int32_t*)it.mlist, skip, (const T*)C.d_zero_tile);
-    } else {
-      hipLaunchKernelGGL((k_tile_mv<T, NV, NB16, CLS, LD>), dim3((unsigned)grid), dim3(256), 0, s, it.n, it.d,
-                         C.d_subs, tiles, (const T*)in, (T*)out, (const T*)add, alpha, (const T*)add_c, alpha_c,
-                         C.nrhs, (int)trans, partial, (const int32_t*)it.mlist, skip, (const T*)C.d_zero_tile);
     }
-  } else {
-    hipLaunchKernelGGL((k_tile_mv<T, NV, NB16, CLS, LD>), dim3((unsigned)grid), dim3(256), 0, s, it.n, it.d,
-                       C.d_subs, tiles, (const T*)in, (T*)out, (const T*)add, alpha, (const T*)add_c, alpha_c,
-                       C.nrhs, (int)trans, partial, (const int32_t*)it.mlist, skip, (const T*)C.d_zero_tile);
+  }
+  if (it.rows4) {
+    hipLaunchKernelGGL((k_tile_mvw<T, NV, NB16, CLS, LD>), dim3((unsigned)it.n), dim3(64 * kRowWaves), 0, s, it.d,
+                       C.d_subs, tiles, (const T*)in, (T*)out, (const T*)add, alpha, (const T*)add_c, alpha_c, C.nrhs,
+                       (int)trans, (const int32_t*)it.mlist, skip, (const T*)C.d_zero_tile);
+    return;
+  }
+  if (!it.pair) {
+    bool gathered = false;
+    if constexpr (CLS == DD_PROF_CORNER) {
+      if (crow) {
+        gathered = true;
+        hipLaunchKernelGGL((k_tile_mv<T, NV, NB16, CLS, LD, true>), dim3((unsigned)grid), dim3(256), 0, s, it.n, it.d,
+                           C.d_subs, tiles, (const T*)in, (T*)out, (const T*)add, alpha, (const T*)add_c, alpha_c,
+                           C.nrhs, (int)trans, partial, (const int32_t*)it.mlist, skip, (const T*)C.d_zero_tile, crow);
+      }
+    }
+    if (!gathered)
+      hipLaunchKernelGGL((k_tile_mv<T, NV, NB16, CLS, LD, false>), dim3((unsigned)grid), dim3(256), 0, s, it.n, it.d,
+                         C.d_subs, tiles, (const T*)in, (T*)out, (const T*)add, alpha, (const T*)add_c, alpha_c,
+                         C.nrhs, (int)trans, partial, (const int32_t*)it.mlist, skip, (const T*)C.d_zero_tile,
+                         (const int32_t*)nullptr);
   }
   if (split)
     hipLaunchKernelGGL(k_mv_reduce<T>, dim3((unsigned)it.n_out), dim3(256), 0, s, it.n_out, it.outs, C.d_subs,
@@ -1539,42 +1590,43 @@ static void mv_launch(Ctx& C, hipStream_t s, const Items& it, bool trans, const 
 
 template <class T, int CLS>
 static void mv_dispatch(Ctx& C, hipStream_t s, const Items& it, bool trans, const void* in, void* out,
-                        const void* add, T alpha, const void* add_c, T alpha_c, const int* skip) {
+                        const void* add, T alpha, const void* add_c, T alpha_c, const int* skip,
+                        const int32_t* crow) {
   const int nr = C.nrhs;
   // full RHS blocks (16, 32) take the instances with a compile-time stride
   if (nr == 1)
-    mv_launch<T, 1, 0, CLS, 0>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip);
+    mv_launch<T, 1, 0, CLS, 0>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip, crow);
   else if (nr == 2)
-    mv_launch<T, 2, 0, CLS, 0>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip);
+    mv_launch<T, 2, 0, CLS, 0>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip, crow);
   else if (nr == 16)
-    mv_launch<T, 0, 1, CLS, 16>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip);
+    mv_launch<T, 0, 1, CLS, 16>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip, crow);
   else if (nr < 16)
-    mv_launch<T, 0, 1, CLS, 0>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip);
+    mv_launch<T, 0, 1, CLS, 0>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip, crow);
   else if (nr == 32)
-    mv_launch<T, 0, 2, CLS, 32>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip);
+    mv_launch<T, 0, 2, CLS, 32>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip, crow);
   else
-    mv_launch<T, 0, 2, CLS, 0>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip);
+    mv_launch<T, 0, 2, CLS, 0>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip, crow);
 }
 
 // out = add + alpha * (product) on r-row output blocks, add_c + alpha_c *
-// (product) on corner-row output blocks (forward passes only); side: launch
-// on the side stream (not used while per-class timing is on)
+// (product) on corner-row output blocks (forward passes only); crow (corner
+// rows' transposed pass): input rows are read through it
 template <class T>
 static void mv(Ctx& C, const Items& it, bool trans, const void* in, void* out, const void* add, T alpha,
-               const int* skip = nullptr, const void* add_c = nullptr, T alpha_c = (T)1, bool side = false) {
+               const int* skip = nullptr, const void* add_c = nullptr, T alpha_c = (T)1, const int32_t* crow = nullptr) {
   if (it.n == 0) return;
   hipEvent_t e0, e1;
   bool timed = prof_begin(C, item_class(C, it), &e0, &e1);
-  hipStream_t s = side ? C.st2 : C.st;
+  hipStream_t s = C.st;
   const int cls = item_class(C, it);
   if (cls == DD_PROF_FULL)
-    mv_dispatch<T, DD_PROF_FULL>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip);
+    mv_dispatch<T, DD_PROF_FULL>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip, crow);
   else if (cls == DD_PROF_CROSS)
-    mv_dispatch<T, DD_PROF_CROSS>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip);
+    mv_dispatch<T, DD_PROF_CROSS>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip, crow);
   else if (cls == DD_PROF_CORNER)
-    mv_dispatch<T, DD_PROF_CORNER>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip);
+    mv_dispatch<T, DD_PROF_CORNER>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip, crow);
   else
-    mv_dispatch<T, DD_PROF_COARSE>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip);
+    mv_dispatch<T, DD_PROF_COARSE>(C, s, it, trans, in, out, add, alpha, add_c, alpha_c, skip, crow);
   if (timed) HIPCHK(hipEventRecord(e1, C.st));
 }
 
@@ -1783,11 +1835,11 @@ static void apply_local(Ctx& C, const int* skip) {
   if (C.Kc > 0) {
     coarse_gather<T>(C, st, (const T*)X[6], (T*)X[6], nullptr, skip);
     coarse_solve<T>(C, X[6], X[7], X[5], skip);
-    corner_scatter<T>(C, st, (const T*)X[5], (T*)X[6], (T)1, skip);
   }
-  // Psi_G^T z goes to its own buffer (rows of subdomains without corners
-  // stay zero from setup), so it does not wait for M v; consumers add X9
-  if (C.Kc > 0) mv<T>(C, C.corner_T, true, X[6], X[9], nullptr, (T)1, skip);
+  // Psi_G^T z (z read from the coarse rows through B_c) goes to its own buffer
+  // (rows of subdomains without corners stay zero from setup), so it does not
+  // wait for M v; consumers add X9
+  if (C.Kc > 0) mv<T>(C, C.corner_T, true, X[5], X[9], nullptr, (T)1, skip, nullptr, (T)1, C.d_crow);
   if (overlap) join_side(C);
 }
 
@@ -1814,9 +1866,8 @@ static void interface_local(Ctx& C, void* u, const void* gp, void* out, void* xc
     // corner rows of X6: g' - Psi_G u (above); their coarse sum; x_c = K_cc^-1 (.)
     coarse_gather<T>(C, C.st, (const T*)X[6], (T*)X[6], nullptr, skip);
     coarse_solve<T>(C, X[6], X[7], xc, skip);
-    // -x_c on the corner rows of X6; X9 = -Psi_G^T x_c
-    corner_scatter<T>(C, C.st, (const T*)xc, (T*)X[6], (T)-1, skip);
-    mv<T>(C, C.corner_T, true, X[6], X[9], nullptr, (T)1, skip);
+    // X9 = -Psi_G^T x_c, x_c read from the coarse rows through B_c
+    mv<T>(C, C.corner_T, true, xc, X[9], nullptr, (T)-1, skip, nullptr, (T)1, C.d_crow);
   }
   if (overlap) join_side(C);
   if (C.sym.n > 0) symv_reduce<T>(C, out, C.Kc > 0 ? X[9] : nullptr, skip, C.st);
@@ -2777,22 +2828,22 @@ static int adjoint_impl(Ctx& C, const double* ebar_next, double* ebar_n, double*
 // next solve).
 template <class T>
 static void rebuild_lists(Ctx& C, int which) {
-  auto remake = [&](Items& it, const std::vector<MvItem>& blk, int chunk, bool grouped, int bucket) {
+  auto remake = [&](Items& it, const std::vector<MvItem>& blk, int chunk, bool one_wave = false) {
     int32_t* ml = it.mlist;
     it.mlist = nullptr;
     release_items(C, it);
-    it = make_items(C, blk, chunk, grouped, bucket);
+    it = make_items(C, blk, chunk, false, 1, one_wave);
     it.mlist = ml;
   };
   HIPCHK(hipStreamSynchronize(C.st));
   drop_graphs(C);
   if (which & 1) {
-    remake(C.corner_N, C.blk_corner_N, C.tuning.chunk, false, 1);
-    remake(C.corner_T, C.blk_corner_T, C.tuning.chunk, false, 1);
+    remake(C.corner_N, C.blk_corner_N, C.tuning.chunk);
+    remake(C.corner_T, C.blk_corner_T, C.tuning.chunk, true);
   }
   if ((which & 2) && C.coarse_lists) {
-    remake(C.co_N, C.blk_co_N, C.tuning.coarse_chunk, false, 1);
-    remake(C.co_T, C.blk_co_T, C.tuning.coarse_chunk, false, 1);
+    remake(C.co_N, C.blk_co_N, C.tuning.coarse_chunk);
+    remake(C.co_T, C.blk_co_T, C.tuning.coarse_chunk);
   }
   if ((which & 4) && C.full_N.d) build_full_items<T>(C);
   if ((which & 8) && C.sym.pw != sym_width(C)) make_sym_list(C, sym_width(C), sizeof(T));
@@ -2927,7 +2978,7 @@ static void autotune_impl(Ctx& C, dd_tuning* out) {
   // (the corner-coupling passes; the result fields keep their names)
   auto trailing = [&] {
     mv<T>(C, C.corner_N, false, X[5], X[6], nullptr, one);
-    mv<T>(C, C.corner_T, true, X[6], X[8], nullptr, one);
+    mv<T>(C, C.corner_T, true, X[5], X[8], nullptr, one, nullptr, nullptr, one, C.d_crow);
   };
   const bool prof = C.prof;
   C.prof = false;

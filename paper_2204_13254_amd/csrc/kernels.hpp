@@ -734,17 +734,153 @@ __device__ __forceinline__ void load_chunk8(const T* __restrict__ blk, int l, T*
   }
 }
 
-// NV > 0: vector path for nrhs <= NV; NV == 0: MFMA path with NB16 RHS blocks.
-// CLS only names the product class in kernel traces (0 interface blocks of
-// the inverse factors, 1 full r-blocks, 3 coarse, 4 corner rows).
-template <class T, int NV, int NB16, int CLS, int LD>
+// Sum over the tiles k = lo, lo + step, ... < hi of one output block's range by
+// one wave.  NV > 0: vector path for nrhs <= NV, vacc[mb NV + r]; NV == 0:
+// MFMA path with NB16 RHS blocks, macc[mb NB16 + nb].  GZ: input row x of the
+// subdomain is row crow[x] of `in` (-1: zero): the corner rows read through
+// B_c straight from the coarse solution, without a copy per subdomain.
+// NS: separate MFMA sums, one to a ring slot, added at the end (three where the
+// form also serves 3..8 RHS: one chain over a row's tiles had up to twice the
+// rounding error of the four lane groups of a vector product).
+template <class T, int NV, int NB16, int NS, bool GZ>
+__device__ __forceinline__ void mv_range(const SubDev& q, const T* __restrict__ tiles, const T* __restrict__ in,
+                                         int nrhs, int trans, int o, int lo, int hi, int step,
+                                         const int32_t* __restrict__ mlist, const T* __restrict__ zero,
+                                         const int32_t* __restrict__ crow,
+                                         typename Mfma<T>::acc_t (&macc)[NV ? 1 : 2 * NB16],
+                                         T (&vacc)[NV ? 2 * NV : 1]) {
+  const int l = threadIdx.x & 63;
+  const int g = l >> 4, i = l & 15;
+  const T* xbase = GZ ? in : in + q.row_off * nrhs;
+  constexpr bool MF = NV == 0;
+  typename Mfma<T>::acc_t ms[NS][MF ? 2 * NB16 : 1];
+  if constexpr (MF) {
+#pragma unroll
+    for (int u = 0; u < NS; ++u)
+#pragma unroll
+      for (int a = 0; a < 2 * NB16; ++a) ms[u][a] = typename Mfma<T>::acc_t{0, 0, 0, 0};
+  } else {
+#pragma unroll
+    for (int a = 0; a < 2 * NV; ++a) vacc[a] = 0;
+  }
+  // factor values of a tile, and (loaded together with them) the input values
+  // the lane needs: MFMA path xv[nb*8 + ks] = x[8g+ks][nb*16+i], vector path
+  // xv[ks*NV + r] = x[8g+ks][r]
+  static_assert(NV <= 2, "the vector path keeps its input values in registers");
+  constexpr int NX = 8 * (MF ? NB16 : NV);
+  // Loads are unconditional (clamped to an in-bounds column, then zeroed
+  // by a select): a masked load compiles to a branch whose other arm waits
+  // for every load in flight.
+  auto load_x = [&](int m, T* xv) {
+    int32_t cr[8];
+    if constexpr (GZ) {
+      const int4* cp = reinterpret_cast<const int4*>(crow + q.row_off + (int64_t)m * kNB + 8 * g);
+      const int4 c0 = cp[0], c1 = cp[1];
+      cr[0] = c0.x; cr[1] = c0.y; cr[2] = c0.z; cr[3] = c0.w;
+      cr[4] = c1.x; cr[5] = c1.y; cr[6] = c1.z; cr[7] = c1.w;
+    }
+    const T* xb = xbase + (int64_t)m * kNB * nrhs;
+#pragma unroll
+    for (int nb = 0; nb < (MF ? NB16 : NV); ++nb) {
+      // column of the lane: its own in the MFMA path, r = nb for all lanes in
+      // the vector path
+      const int col = MF ? nb * 16 + i : nb;
+      const unsigned cc = (unsigned)(col < nrhs ? col : nrhs - 1);
+      // the row of step ks as a wave-uniform base plus one lane offset for all
+      // of them (eight lane addresses per block cost more than the products
+      // at 3..15 RHS)
+      const unsigned off = 8u * g * nrhs + cc;
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) {
+        T v;
+        if constexpr (GZ) {
+          v = xbase[(int64_t)(cr[ks] >= 0 ? cr[ks] : 0) * nrhs + cc];
+          v = cr[ks] >= 0 ? v : (T)0;
+        } else {
+          const T* xk = xb + ks * nrhs;
+          v = xk[off];
+        }
+        xv[MF ? nb * 8 + ks : ks * NV + nb] = col < nrhs ? v : (T)0;
+      }
+    }
+  };
+  // a lane reads the zero tile for the quarters flagged all-zero (lane
+  // group g holds columns 8g..8g+7: column half g / 2)
+  auto ld = [&](int k, T* c, T* xv) {
+    const int32_t e = mlist ? mlist[k] : k;
+    const int m = e & kListMask, zq = (e >> 25) & 15, ch = g >> 1;
+    const T* tp = tiles + tile_index(q, trans ? m : o, trans ? o : m) * kTile;
+    load_chunk8(((zq >> ch) & 1) ? zero : tp, l, c);
+    load_chunk8((((zq >> (2 + ch)) & 1) ? zero : tp) + 512, l, c + 8);
+    load_x(m, xv);
+  };
+  // two tiles (and their input blocks) in flight: a ring of three buffers
+  // over the range, the loop unrolled by three so that each buffer stays in
+  // fixed registers (no copies between iterations)
+  T rb[3][16], rx[3][NX];
+  auto mm = [&](int u) {
+    if constexpr (MF) {
+#pragma unroll
+      for (int nb = 0; nb < NB16; ++nb)
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+          ms[u % NS][nb] = Mfma<T>::op(rb[u][ks], rx[u][nb * 8 + ks], ms[u % NS][nb]);
+          ms[u % NS][NB16 + nb] = Mfma<T>::op(rb[u][8 + ks], rx[u][nb * 8 + ks], ms[u % NS][NB16 + nb]);
+        }
+    } else {
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks)
+#pragma unroll
+        for (int r = 0; r < NV; ++r) {
+          vacc[r] += rb[u][ks] * rx[u][ks * NV + r];
+          vacc[NV + r] += rb[u][8 + ks] * rx[u][ks * NV + r];
+        }
+    }
+  };
+  if (lo < hi) ld(lo, rb[0], rx[0]);
+  if (lo + step < hi) ld(lo + step, rb[1], rx[1]);
+  for (int k = lo; k < hi; k += 3 * step) {
+    if (k + 2 * step < hi) ld(k + 2 * step, rb[2], rx[2]);
+    mm(0);
+    if (k + 3 * step < hi) ld(k + 3 * step, rb[0], rx[0]);
+    if (k + step < hi) mm(1);
+    if (k + 4 * step < hi) ld(k + 4 * step, rb[1], rx[1]);
+    if (k + 2 * step < hi) mm(2);
+  }
+  if constexpr (MF) {
+#pragma unroll
+    for (int a = 0; a < 2 * NB16; ++a) {
+      macc[a] = ms[0][a];
+#pragma unroll
+      for (int u = 1; u < NS; ++u) macc[a] += ms[u][a];
+    }
+  } else {
+    // the four lane groups hold the column quarters of a row
+#pragma unroll
+    for (int a = 0; a < 2 * NV; ++a) {
+      T v = vacc[a];
+      v += __shfl_xor(v, 16);
+      v += __shfl_xor(v, 32);
+      vacc[a] = v;
+    }
+  }
+}
+
+template <int NB16, int LD>
+constexpr int mv_sums() {
+  return NB16 == 1 && LD == 0 ? 3 : 1;
+}
+
+// CLS only names the product class in kernel traces (1 interior blocks, 3
+// coarse, 4 corner rows, 5 couplings).
+template <class T, int NV, int NB16, int CLS, int LD, bool GZ>
 __global__ void __launch_bounds__(256) k_tile_mv(int64_t n_items, const MvItem* __restrict__ items,
                                                  const SubDev* __restrict__ subs, const T* __restrict__ tiles,
                                                  const T* __restrict__ in, T* __restrict__ out,
                                                  const T* __restrict__ add, T alpha, const T* __restrict__ add_c,
                                                  T alpha_c, int nrhs_rt, int trans, T* __restrict__ partial,
                                                  const int32_t* __restrict__ mlist, const int* __restrict__ skip,
-                                                 const T* __restrict__ zero) {
+                                                 const T* __restrict__ zero, const int32_t* __restrict__ crow) {
   if (skip && *skip) return;
   // LD > 0: the RHS count is LD (= 16 NB16), a compile-time row stride
   const int nrhs = LD > 0 ? LD : nrhs_rt;
@@ -762,135 +898,21 @@ __global__ void __launch_bounds__(256) k_tile_mv(int64_t n_items, const MvItem* 
     const SubDev q = subs[w.s];
     const int l = threadIdx.x & 63;
     const int g = l >> 4, i = l & 15;
-    const T* xbase = in + q.row_off * nrhs;
     constexpr bool MF = NV == 0;
-    constexpr int NA = MF ? 2 * NB16 : 2 * NV;
-    // accumulators: vector path acc[mb*NV + r]; MFMA path acc[mb*NB16 + nb]
     typename Mfma<T>::acc_t macc[MF ? 2 * NB16 : 1];
-    T vacc[MF ? 1 : NA];
-    if constexpr (MF) {
-#pragma unroll
-      for (int a = 0; a < 2 * NB16; ++a) macc[a] = typename Mfma<T>::acc_t{0, 0, 0, 0};
-    } else {
-#pragma unroll
-      for (int a = 0; a < NA; ++a) vacc[a] = 0;
-    }
-    // factor values of the current / next tile, and (prefetched together with
-    // them) the input values the lane needs: MFMA path bv[nb][ks] = x[8g+ks][nb*16+i],
-    // vector path x[8g+ks][r]
-    static_assert(NV <= 2, "the vector path keeps its input values in registers");
-    constexpr int NX = 8 * (MF ? NB16 : NV);
-    T cur[16], nxt[16], xc[NX], xn[NX];
-    auto tile_ptr = [&](int m) -> const T* {
-      const int ti = trans ? m : w.o, tj = trans ? w.o : m;
-      return tiles + tile_index(q, ti, tj) * kTile;
-    };
-    // Loads are unconditional (clamped to an in-bounds column, then zeroed
-    // by a select): a masked load compiles to a branch whose other arm waits
-    // for every load in flight, prefetches included.
-    auto load_x = [&](int m, T* xv) {
-      const T* xb = xbase + (int64_t)m * kNB * nrhs;
-      if constexpr (MF) {
-        // the row of step ks as a wave-uniform base plus one lane offset for
-        // all of them (eight lane addresses per block cost more than the
-        // products at 3..15 RHS)
-#pragma unroll
-        for (int nb = 0; nb < NB16; ++nb) {
-          const int col = nb * 16 + i;
-          const unsigned off = 8u * g * nrhs + (unsigned)(col < nrhs ? col : nrhs - 1);
-#pragma unroll
-          for (int ks = 0; ks < 8; ++ks) {
-            const T* xk = xb + ks * nrhs;
-            const T v = xk[off];
-            xv[nb * 8 + ks] = col < nrhs ? v : (T)0;
-          }
-        }
-      } else {
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks)
-#pragma unroll
-          for (int r = 0; r < NV; ++r) {
-            const T v = xb[(8 * g + ks) * nrhs + (r < nrhs ? r : nrhs - 1)];
-            xv[ks * NV + r] = r < nrhs ? v : (T)0;
-          }
-      }
-    };
-    auto ent = [&](int k) -> int32_t { return mlist ? mlist[k] : k; };
-    // a lane reads the zero tile for the quarters flagged all-zero (lane
-    // group g holds columns 8g..8g+7: column half g / 2)
-    auto load_tile = [&](int32_t e, T* c) {
-      const T* tp = tile_ptr(e & kListMask);
-      const int zq = (e >> 25) & 15, ch = g >> 1;
-      load_chunk8(((zq >> ch) & 1) ? zero : tp, l, c);
-      load_chunk8((((zq >> (2 + ch)) & 1) ? zero : tp) + 512, l, c + 8);
-    };
-    if constexpr (MF) {
-      // two tiles (and their input blocks) in flight: a ring of three
-      // buffers over the item's tiles, the loop unrolled by three so that
-      // each buffer stays in fixed registers (no copies between iterations)
-      T rb[3][16], rx[3][NX];
-      auto ld = [&](int k, int u) {
-        const int32_t e = ent(k);
-        load_tile(e, rb[u]);
-        load_x(e & kListMask, rx[u]);
-      };
-      auto mm = [&](int u) {
-#pragma unroll
-        for (int nb = 0; nb < NB16; ++nb)
-#pragma unroll
-          for (int ks = 0; ks < 8; ++ks) {
-            macc[nb] = Mfma<T>::op(rb[u][ks], rx[u][nb * 8 + ks], macc[nb]);
-            macc[NB16 + nb] = Mfma<T>::op(rb[u][8 + ks], rx[u][nb * 8 + ks], macc[NB16 + nb]);
-          }
-      };
-      if (w.lo < w.hi) ld(w.lo, 0);
-      if (w.lo + 1 < w.hi) ld(w.lo + 1, 1);
-      for (int k = w.lo; k < w.hi; k += 3) {
-        if (k + 2 < w.hi) ld(k + 2, 2);
-        mm(0);
-        if (k + 3 < w.hi) ld(k + 3, 0);
-        if (k + 1 < w.hi) mm(1);
-        if (k + 4 < w.hi) ld(k + 4, 1);
-        if (k + 2 < w.hi) mm(2);
-      }
-    }
-    if (!MF && w.lo < w.hi) {
-      const int32_t e0 = ent(w.lo);
-      load_tile(e0, cur);
-      load_x(e0 & kListMask, xc);
-    }
-    // vector path: one tile in flight
-    for (int k = w.lo; k < (MF ? w.lo : w.hi); ++k) {
-      if (k + 1 < w.hi) {
-        const int32_t e1 = ent(k + 1);
-        load_tile(e1, nxt);
-        load_x(e1 & kListMask, xn);
-      }
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks)
-#pragma unroll
-        for (int r = 0; r < NV; ++r) {
-          vacc[r] += cur[ks] * xc[ks * NV + r];
-          vacc[NV + r] += cur[8 + ks] * xc[ks * NV + r];
-        }
-      if (k + 1 < w.hi) {
-#pragma unroll
-        for (int u = 0; u < 16; ++u) cur[u] = nxt[u];
-#pragma unroll
-        for (int u = 0; u < NX; ++u) xc[u] = xn[u];
-      }
-    }
+    T vacc[MF ? 1 : 2 * NV];
+    mv_range<T, NV, NB16, mv_sums<NB16, LD>(), GZ>(q, tiles, in, nrhs, trans, w.o, w.lo, w.hi, 1, mlist, zero, crow, macc, vacc);
     // ---- epilogue ------------------------------------------------------------
     T* dst;
     const T* adp = nullptr;
     T scale;
     if (w.slot < 0) {
       // corner output rows (o >= kr) take their own alpha / add
-      const bool crow = w.o >= q.kI + q.kG;
-      const T* ad = crow ? add_c : add;
+      const bool crow_out = w.o >= q.kI + q.kG;
+      const T* ad = crow_out ? add_c : add;
       dst = out + (q.row_off + (int64_t)w.o * kNB) * nrhs;
       if (ad) adp = ad + (q.row_off + (int64_t)w.o * kNB) * nrhs;
-      scale = crow ? alpha_c : alpha;
+      scale = crow_out ? alpha_c : alpha;
     } else {
       dst = partial + (int64_t)w.slot * kNB * nrhs;
       scale = (T)1;
@@ -913,13 +935,6 @@ __global__ void __launch_bounds__(256) k_tile_mv(int64_t n_items, const MvItem* 
           }
         }
     } else {
-#pragma unroll
-      for (int a = 0; a < NA; ++a) {
-        T v = vacc[a];
-        v += __shfl_xor(v, 16);
-        v += __shfl_xor(v, 32);
-        vacc[a] = v;
-      }
       // lane group g writes right-hand sides r with r % 4 == g
 #pragma unroll
       for (int mb = 0; mb < 2; ++mb)
@@ -934,6 +949,69 @@ __global__ void __launch_bounds__(256) k_tile_mv(int64_t n_items, const MvItem* 
         }
     }
   }  // groups
+}
+
+// Row-group form of k_tile_mv: the four waves of a workgroup share one output
+// block, wave w taking tiles lo + w, lo + w + 4, ..., and their sums meet in
+// LDS in wave order (deterministic; no partial slots and no reduce launch).
+// For lists of few rows, where one wave per row leaves most of the chip idle
+// and its serial chain of tile loads is the whole time (make_items has the
+// rule): at 24^3, 64 boxes, FP64, 1 RHS a coarse pass went from 13.7 us plus
+// a 4.6 us reduce to 6.7 us, a corner-row pass from 12.1 to 7.0 us.  (Eight
+// waves: no faster there, and beside the symmetric product of a large problem
+// a workgroup of eight waits for two free wave slots on every SIMD.)
+constexpr int kRowWaves = 4;
+template <class T, int NV, int NB16, int CLS, int LD>
+__global__ void __launch_bounds__(64 * kRowWaves) k_tile_mvw(const MvItem* __restrict__ items, const SubDev* __restrict__ subs,
+                                                  const T* __restrict__ tiles, const T* __restrict__ in,
+                                                  T* __restrict__ out, const T* __restrict__ add, T alpha,
+                                                  const T* __restrict__ add_c, T alpha_c, int nrhs_rt, int trans,
+                                                  const int32_t* __restrict__ mlist, const int* __restrict__ skip,
+                                                  const T* __restrict__ zero) {
+  if (skip && *skip) return;
+  const int nrhs = LD > 0 ? LD : nrhs_rt;
+  constexpr bool MF = NV == 0;
+  constexpr int NC = MF ? 16 * NB16 : NV;  // columns of a block in LDS
+  __shared__ T red[kRowWaves * 16 * NC];   // one row half at a time
+  const MvItem w = items[blockIdx.x];
+  if (w.s < 0) return;  // padding item (uniform over the workgroup)
+  const SubDev q = subs[w.s];
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l = threadIdx.x & 63, g = l >> 4, i = l & 15;
+  typename Mfma<T>::acc_t macc[MF ? 2 * NB16 : 1];
+  T vacc[MF ? 1 : 2 * NV];
+  mv_range<T, NV, NB16, mv_sums<NB16, LD>(), false>(q, tiles, in, nrhs, trans, w.o, w.lo + wv, w.hi, kRowWaves, mlist, zero, nullptr, macc, vacc);
+  const bool crow_out = w.o >= q.kI + q.kG;
+  const T* ad = crow_out ? add_c : add;
+  const T scale = crow_out ? alpha_c : alpha;
+  const int64_t base = (q.row_off + (int64_t)w.o * kNB) * nrhs;
+#pragma unroll
+  for (int mb = 0; mb < 2; ++mb) {
+    if (mb) __syncthreads();
+    if constexpr (MF) {
+#pragma unroll
+      for (int nb = 0; nb < NB16; ++nb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          red[(wv * 16 + Mfma<T>::row(l, v)) * NC + nb * 16 + i] = macc[mb * NB16 + nb][v];
+    } else if (g == 0) {
+#pragma unroll
+      for (int r = 0; r < NV; ++r) red[(wv * 16 + i) * NC + r] = vacc[mb * NV + r];
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < 16 * NC; e += blockDim.x) {
+      const int col = e % NC;
+      T v = red[e];
+#pragma unroll
+      for (int u = 1; u < kRowWaves; ++u) v += red[u * 16 * NC + e];
+      if (col < nrhs) {
+        const int64_t x = base + (int64_t)(mb * 16 + e / NC) * nrhs + col;
+        v *= scale;
+        if (ad) v += ad[x];
+        out[x] = v;
+      }
+    }
+  }
 }
 
 // Row-pair form of k_tile_mv for the full passes (MFMA path, 9..32 RHS):

@@ -52,3 +52,10 @@ def test_reductions_of_a_few_workgroups(nrhs, precision):
 @pytest.mark.parametrize("nrhs", [1, 5])
 def test_reductions_of_the_other_solvers(opt, nrhs):
     assert _steps(5, (1, 2, 2), nrhs, "fp64", **opt) <= BAR["fp64"]
+
+
+@pytest.mark.parametrize("nrhs", [1, 2, 5, 16, 19])
+@pytest.mark.parametrize("precision", ["fp64", "fp32_refine"])
+def test_rows_shared_by_four_waves(nrhs, precision):
+    # 16^3 in 64 boxes: coarse rows of up to 16 tiles, a few dozen rows
+    assert _steps(16, (4, 4, 4), nrhs, precision) <= BAR[precision]
