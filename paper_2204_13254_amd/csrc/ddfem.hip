@@ -198,13 +198,31 @@ struct Ctx {
   void* d_partial_mv = nullptr;
   int64_t max_slots = 0;        // largest slot count of any work list
   int64_t partial_slots = 0;    // slots d_partial_mv holds
-  void* d_scratch = nullptr;
-  int64_t* d_scratch_off = nullptr;
-  // per factor-store tile: L tile nonzero / inverse tile nonzero (every flag
-  // a factorization reads it has written before)
+  // per factor-store tile: L tile nonzero / inverse tile nonzero (written for
+  // the tiles of the symbolic pattern, zero elsewhere)
   uint8_t* d_nzl = nullptr;
   uint8_t* d_nzi = nullptr;
-  int* d_err = nullptr;
+  int* d_err = nullptr;           // [0] first block with a bad pivot, [1] zero pattern changed
+  int32_t* d_tinfo = nullptr;     // per tile: nonzeros | nonzero quarters << 16 (k_pack_tiles)
+  bool pattern_valid = false;     // the tile lists were built from d_tinfo
+  // symbolic factorisation (until the first dd_factor): per tile kSymL where L
+  // may be nonzero, kSymInv where the inverse of its diagonal block may be; per
+  // tile column its level; and the work lists made from them
+  std::vector<uint8_t> sym_tile;
+  std::vector<std::vector<int32_t>> sym_level;
+  struct FacStep {
+    int64_t first = 0;             // offset in d_fac
+    int nd = 0, no = 0, ninv = 0;  // diagonal, off-diagonal (and corner), inverse items
+  };
+  struct FacList {
+    std::vector<FacStep> steps;
+    int64_t pack = 0, n_pack = 0;    // range of d_pack
+    int max_rows = 0;                // longest chain list
+  } fac_sub, fac_coarse;
+  FacItem* d_fac = nullptr;
+  int64_t psi_first = 0, n_psi = 0;  // Psi_Gamma items in d_fac
+  int64_t *d_pack = nullptr, *d_clear = nullptr;
+  int64_t n_clear = 0;
   // particle steps: per-tetrahedron geometry, face neighbours, edges, and
   // the counters of one launch (built on the first particle call)
   double* d_pic_geo = nullptr;
@@ -559,6 +577,91 @@ static void make_sym_list(Ctx& C, int pw, size_t wsz) {
   C.sym.zero = p;
 }
 
+// Symbolic factorisation of block s from the positions of its assembled
+// entries (lower triangle, tile store positions): on single rows, since a tile
+// holds rows of several dissection pieces and tile-level fill would be dense.
+// Elimination tree: the parent of column c is the first row below c in its
+// pattern and inherits the rest.  L(i, k): any entry of the tile; level of tile
+// column k: one more than the largest level of the columns m < k with L(k, m);
+// the inverse of a diagonal block (I or Gamma; the coarse block whole) is
+// nonzero at (row, column) for the ancestors of the column within the block.
+enum : uint8_t { kSymL = 1, kSymInv = 2 };
+
+// row-major positions in the tile store -> operand-order positions
+static std::vector<int64_t> operand_positions(const Ctx& C, std::vector<int64_t> pos) {
+  for (int64_t& p : pos) {
+    const int e = (int)(p % kTile), r = e / kNB, c = e % kNB;
+    p += (C.fp32 ? swz<float>(r, c) : swz<double>(r, c)) - e;
+  }
+  return pos;
+}
+
+static void symbolic_block(Ctx& C, int s, const int64_t* pos, int64_t npos) {
+  const SubDev& q = C.subs_h[s];
+  const int K = q.K, kI = q.kI, kr = q.kI + q.kG;
+  const int n = K * NB, nr = kr * NB;
+  const size_t W = (size_t)(n + 63) / 64;
+  std::vector<uint64_t> col((size_t)nr * W, 0);
+  {
+    // (tile row, column) of every tile, walked along with the sorted positions
+    int i = 0, j = 0;
+    int64_t t = 0;
+    for (int64_t e = 0; e < npos; ++e) {
+      const int64_t te = pos[e] / kTile - q.tile_off;
+      const int in = (int)(pos[e] % kTile);
+      while (t < te) {
+        ++t;
+        if (++j > i) {
+          ++i;
+          j = 0;
+        }
+      }
+      const int r = i * NB + in / NB, c = j * NB + in % NB;
+      if (c < nr && r > c) col[(size_t)c * W + r / 64] |= 1ull << (r & 63);
+    }
+  }
+  std::vector<int32_t> parent(nr, -1), up(nr), &lev = C.sym_level[s];
+  lev.assign(kr, 0);
+  auto flag = [&](int i, int j) -> uint8_t& { return C.sym_tile[q.tile_off + (int64_t)i * (i + 1) / 2 + j]; };
+  for (int c = 0; c < nr; ++c) {
+    const uint64_t* p = &col[(size_t)c * W];
+    size_t x = (size_t)c / 64;
+    for (; x < W; ++x)
+      if (p[x]) {
+        parent[c] = (int)(64 * x) + __builtin_ctzll(p[x]);
+        break;
+      }
+    for (; x < W; ++x) {
+      if ((uint32_t)p[x]) flag((int)(2 * x), c / NB) |= kSymL;
+      if (p[x] >> 32) flag((int)(2 * x + 1), c / NB) |= kSymL;
+    }
+    const int pc = parent[c];
+    if (pc >= 0 && pc < nr) {
+      uint64_t* d = &col[(size_t)pc * W];
+      for (size_t y = (size_t)pc / 64; y < W; ++y) d[y] |= p[y];
+      d[pc / 64] &= ~(1ull << (pc & 63));
+    }
+  }
+  for (int k = 0; k < kr; ++k) {
+    flag(k, k) |= kSymL | kSymInv;
+    for (int m = 0; m < k; ++m)
+      if (flag(k, m) & kSymL) lev[k] = std::max(lev[k], lev[m] + 1);
+  }
+  for (int i = kr; i < K; ++i)
+    for (int j = kr; j <= i; ++j) flag(i, j) |= kSymL;  // corner blocks
+  // ancestors of the rows of tile column j, each walked until a row already
+  // seen for this tile column
+  std::fill(up.begin(), up.end(), -1);
+  for (int j = 0; j < kr; ++j) {
+    const int end = (j < kI ? kI : kr) * NB;
+    for (int c = j * NB; c < (j + 1) * NB; ++c)
+      for (int r = c; r >= 0 && r < end && up[r] != j; r = parent[r]) {
+        up[r] = j;
+        flag(r / NB, j) |= kSymInv;
+      }
+  }
+}
+
 static void build_device(Ctx& C, const double* coords) {
   Plan& P = C.P;
   hipStream_t st = C.st;
@@ -596,8 +699,8 @@ static void build_device(Ctx& C, const double* coords) {
   C.rows_total = roff;
   const size_t wsz = C.fp32 ? 4 : 8;
   for (const SubDev& q : C.subs_h)
-    if (q.K - 1 > kColList)
-      throw DDError{DD_ERR_OOM, "a factor block has more than " + std::to_string(kColList + 1) + " tile rows"};
+    if (q.K > kMaxBlockRows)
+      throw DDError{DD_ERR_OOM, "a factor block has more than " + std::to_string(kMaxBlockRows) + " tile rows"};
   C.d_subs = upload(C.subs_h, C.owned, st);
   {
     void* p = nullptr;
@@ -614,6 +717,12 @@ static void build_device(Ctx& C, const double* coords) {
     C.d_tilesT = p;
     C.d_nzl = dalloc<uint8_t>(std::max<int64_t>(1, C.ntiles), C.owned);
     C.d_nzi = dalloc<uint8_t>(std::max<int64_t>(1, C.ntiles), C.owned);
+    C.d_tinfo = dalloc<int32_t>(std::max<int64_t>(1, C.ntiles), C.owned);
+    HIPCHK(hipMemsetAsync(C.d_nzl, 0, std::max<int64_t>(1, C.ntiles), st));
+    HIPCHK(hipMemsetAsync(C.d_nzi, 0, std::max<int64_t>(1, C.ntiles), st));
+    HIPCHK(hipMemsetAsync(C.d_tinfo, 0, std::max<int64_t>(1, C.ntiles) * sizeof(int32_t), st));
+    C.sym_tile.assign(C.ntiles, 0);
+    C.sym_level.resize(nsub + 1);
     std::vector<int64_t> mo(nsub);
     int64_t acc = 0;
     for (int s = 0; s < nsub; ++s) {
@@ -644,21 +753,7 @@ static void build_device(Ctx& C, const double* coords) {
     (void)nr;
   }
   C.coarse_bytes = nc * (nc + 1) / 2 * (int64_t)wsz;
-  // scratch rows for the triangular inversion
-  {
-    std::vector<int64_t> so(nsub + 1);
-    int64_t acc = 0;
-    for (int s = 0; s <= nsub; ++s) {
-      so[s] = acc;
-      acc += C.subs_h[s].kI + C.subs_h[s].kG;
-    }
-    C.d_scratch_off = upload(so, C.owned, st);
-    void* p = nullptr;
-    HIPCHK(hipMalloc(&p, std::max<int64_t>(1, acc) * kTile * wsz));
-    C.owned.push_back(p);
-    C.d_scratch = p;
-  }
-  C.d_err = dalloc<int>(1, C.owned);
+  C.d_err = dalloc<int>(2, C.owned);
 
   // ---- mesh arrays ------------------------------------------------------------
   std::vector<double> ch(coords, coords + 3 * P.nv);
@@ -698,6 +793,7 @@ static void build_device(Ctx& C, const double* coords) {
         }
       }
     std::sort(pairs.begin(), pairs.end());
+    const size_t ld0 = ldest.size();
     for (size_t i = 0; i < pairs.size();) {
       size_t j = i;
       while (j < pairs.size() && pairs[j].first == pairs[i].first) {
@@ -709,6 +805,7 @@ static void build_device(Ctx& C, const double* coords) {
       i = j;
     }
     for (int32_t p : L) dof2row[p] = -1;
+    symbolic_block(C, s, ldest.data() + ld0, (int64_t)(ldest.size() - ld0));
     // padding diagonals
     auto add_pad = [&](int32_t r0, int32_t r1) {
       for (int32_t r = r0; r < r1; ++r) {
@@ -729,12 +826,11 @@ static void build_device(Ctx& C, const double* coords) {
   }
   C.n_lent = (int64_t)ldest.size();
   C.d_lptr = upload(lptr, C.owned, st);
-  C.d_ldest = upload(ldest, C.owned, st);
+  C.d_ldest = upload(operand_positions(C, std::move(ldest)), C.owned, st);
   C.d_lcon = upload(lcon, C.owned, st);
   C.n_pad = (int64_t)padpos.size();
-  C.d_padpos = upload(padpos, C.owned, st);
+  C.d_padpos = upload(operand_positions(C, std::move(padpos)), C.owned, st);
   std::vector<int64_t>().swap(lptr);
-  std::vector<int64_t>().swap(ldest);
   std::vector<int32_t>().swap(lcon);
 
   // ---- coarse assembly pull lists --------------------------------------------------
@@ -772,9 +868,10 @@ static void build_device(Ctx& C, const double* coords) {
       i = j;
     }
     C.n_cent = (int64_t)cdest.size();
+    symbolic_block(C, nsub, cdest.data(), (int64_t)cdest.size());
     C.d_cptr = upload(cptr, C.owned, st);
-    C.d_csrc = upload(csrc, C.owned, st);
-    C.d_cdest = upload(cdest, C.owned, st);
+    C.d_csrc = upload(operand_positions(C, std::move(csrc)), C.owned, st);
+    C.d_cdest = upload(operand_positions(C, std::move(cdest)), C.owned, st);
   }
 
   // ---- global CSR pattern of (T, S) and its pull list ------------------------------
@@ -1072,76 +1169,117 @@ static void drop_graphs(Ctx& C) {
 // dynamic LDS of a tile-chain kernel: the list of up to n term indices
 static inline unsigned chain_lds(int n) { return (unsigned)(std::max(n, 2) * sizeof(uint16_t) + 15) & ~15u; }
 
-// Blocked Cholesky of the [I|Gamma] rows of blocks s0 .. s0+cnt-1 (corner
-// rows get L_cr and the Schur complement K_s = A_cc - L_cr L_cr^T).
-template <class T>
-static void factor_chol(Ctx& C, int s0, int cnt, hipStream_t st) {
-  T* tiles = (T*)C.d_tiles;
-  int max_kr = 0;
-  for (int s = s0; s < s0 + cnt; ++s)
-    max_kr = std::max(max_kr, C.subs_h[s].kI + C.subs_h[s].kG);
-  for (int k = 0; k < max_kr; ++k) {
-    int tmax = 0;
-    for (int s = s0; s < s0 + cnt; ++s) {
+// Work lists of the factorisation from the symbolic patterns (once per
+// context).
+static void factor_lists(Ctx& C) {
+  if (C.d_fac) return;
+  std::vector<FacItem> fac;
+  std::vector<int64_t> pack, clear;
+  // items of one list placed by XCD: workgroup b runs on XCD b % 8, and the
+  // tiles of a block are read by many of its items
+  auto place = [&](const std::vector<FacItem>& v) -> int {
+    std::vector<std::vector<FacItem>> q(kXcds);
+    int rr = 0;
+    for (const FacItem& it : v) q[(it.s < C.nsub ? it.s : rr++) % kXcds].push_back(it);
+    size_t n = 0;
+    for (auto& x : q) n = std::max(n, x.size());
+    for (size_t k = 0; k < n; ++k)
+      for (auto& x : q) fac.push_back(k < x.size() ? x[k] : FacItem{-1, 0});
+    return (int)(n * kXcds);
+  };
+  auto ik = [](int i, int k) { return (uint32_t)i << 16 | (uint32_t)k; };
+  std::vector<FacItem> psi;
+  auto blocks = [&](int s0, int s1, Ctx::FacList& F) {
+    std::vector<std::vector<FacItem>> diag, off, inv;
+    std::vector<FacItem> corner;
+    F.pack = (int64_t)pack.size();
+    for (int s = s0; s < s1; ++s) {
       const SubDev& q = C.subs_h[s];
-      if (k < q.kI + q.kG) tmax = std::max(tmax, q.K - k - 1);
+      const int K = q.K, kI = q.kI, kr = q.kI + q.kG;
+      auto tile = [&](int i, int j) { return q.tile_off + (int64_t)i * (i + 1) / 2 + j; };
+      const std::vector<int32_t>& lev = C.sym_level[s];
+      for (int k = 0; k < kr; ++k)
+        if ((size_t)lev[k] >= diag.size()) {
+          diag.resize(lev[k] + 1);
+          off.resize(lev[k] + 1);
+          inv.resize(lev[k] + 1);
+        }
+      for (int i = 0; i < K; ++i)
+        for (int j = 0; j <= i; ++j) {
+          const uint8_t f = C.sym_tile[tile(i, j)];
+          if (f & kSymL) clear.push_back(tile(i, j));
+          if (j >= kr) {
+            corner.push_back({s, ik(i, j)});
+          } else if (i == j) {
+            diag[lev[j]].push_back({s, ik(i, j)});
+            if (j < kI) pack.push_back(tile(i, j) << 1 | 1);
+          } else {
+            if (f & kSymL) off[lev[j]].push_back({s, ik(i, j)});
+            if (f & kSymInv) inv[lev[i]].push_back({s, ik(i, j)});
+            if (j < kI) {
+              // L_II^-1; L_GI and L_cI as factored
+              if (i < kI && (f & kSymInv)) pack.push_back(tile(i, j) << 1 | 1);
+              if (i >= kI && (f & kSymL)) pack.push_back(tile(i, j) << 1);
+            } else if (i >= kr) {
+              psi.push_back({s, ik(i, j)});
+              pack.push_back(tile(i, j) << 1 | 1);
+            }
+          }
+        }
+      F.max_rows = std::max(F.max_rows, K);
     }
-    hipLaunchKernelGGL(k_potrf<T>, dim3(cnt), dim3(256), 0, st, k, s0, tiles, C.d_subs, C.d_err,
-                       C.d_nzl, C.d_nzi);
-    if (tmax > 0) {
-      hipLaunchKernelGGL(k_trsm<T>, dim3(tmax, cnt), dim3(256), 0, st, k, s0, tiles, C.d_subs, C.d_nzl);
-      // pairs of nonzero column tiles, strided over at most 64K workgroups
-      // (2048 for one block: its nonzero pairs per step are a few thousand)
-      const int64_t np = (int64_t)tmax * (tmax + 1) / 2;
-      const unsigned gx = (unsigned)std::max<int64_t>(1, std::min<int64_t>({np, 65536 / cnt, 2048}));
-      hipLaunchKernelGGL(k_syrk<T>, dim3(gx, cnt), dim3(256), 0, st, k, s0, tiles, C.d_subs,
-                         (const uint8_t*)C.d_nzl);
+    F.n_pack = (int64_t)pack.size() - F.pack;
+    // step l: the columns of level l and the inverse rows of level l - 1; after
+    // the last level its inverse rows and the corner blocks
+    for (size_t l = 0; l <= diag.size(); ++l) {
+      Ctx::FacStep st;
+      st.first = (int64_t)fac.size();
+      if (l < diag.size()) {
+        st.nd = place(diag[l]);
+        st.no = place(off[l]);
+      } else {
+        st.no = place(corner);
+      }
+      if (l > 0) st.ninv = place(inv[l - 1]);
+      F.steps.push_back(st);
     }
+  };
+  blocks(0, C.nsub, C.fac_sub);
+  blocks(C.nsub, C.nsub + (C.Kc > 0 ? 1 : 0), C.fac_coarse);
+  C.psi_first = (int64_t)fac.size();
+  C.n_psi = place(psi);
+  if (fac.size() >= (size_t)INT32_MAX || pack.size() >= (size_t)INT32_MAX)
+    throw DDError{DD_ERR_OOM, "factorisation work lists exceed 2^31 entries"};
+  C.d_pack = upload(pack, C.owned, C.st);
+  C.d_clear = upload(clear, C.owned, C.st);
+  C.n_clear = (int64_t)clear.size();
+  C.d_fac = upload(fac, C.owned, C.st);
+  std::vector<uint8_t>().swap(C.sym_tile);
+  std::vector<std::vector<int32_t>>().swap(C.sym_level);
+}
+
+// Factor and inverse factor of the blocks of F.
+template <class T>
+static void factor_blocks(Ctx& C, const Ctx::FacList& F, hipStream_t st) {
+  T *tiles = (T*)C.d_tiles, *inv = (T*)C.d_tilesT;
+  const unsigned lds = chain_lds(F.max_rows);
+  for (const Ctx::FacStep& f : F.steps) {
+    const FacItem* it = C.d_fac + f.first;
+    const int n = f.nd + f.no + f.ninv;
+    if (n > 0)
+      hipLaunchKernelGGL(k_chol_step<T>, dim3((unsigned)n), dim3(256), lds, st, f.nd, f.no, it, tiles, inv, C.d_subs,
+                         C.d_err, C.d_nzl, C.d_nzi);
+    if (f.nd > 0 && f.no > 0)
+      hipLaunchKernelGGL(k_chol_trsm<T>, dim3((unsigned)f.no), dim3(256), 0, st, it + f.nd, tiles, C.d_subs, C.d_nzl);
   }
   HIPCHK(hipGetLastError());
 }
 
-// Inverse factor Linv_rr row by row, then Psi = L_cr Linv_rr.
 template <class T>
-static void factor_inv(Ctx& C, int s0, int cnt, hipStream_t st) {
-  T* tiles = (T*)C.d_tiles;
-  int max_kr = 0;
-  for (int s = s0; s < s0 + cnt; ++s)
-    max_kr = std::max(max_kr, C.subs_h[s].kI + C.subs_h[s].kG);
-  for (int i = 1; i < max_kr; ++i) {
-    hipLaunchKernelGGL(k_trtri_row<T>, dim3(i, cnt), dim3(256), chain_lds(i), st, i, s0, (const T*)tiles, C.d_subs,
-                       C.d_scratch_off, (T*)C.d_scratch, (const uint8_t*)C.d_nzl, C.d_nzi);
-    hipLaunchKernelGGL(k_trtri_copy<T>, dim3(i, cnt), dim3(256), 0, st, i, s0, tiles, C.d_subs,
-                       C.d_scratch_off, (const T*)C.d_scratch);
-  }
-  int max_kc = 0;
-  for (int s = s0; s < s0 + cnt; ++s) max_kc = std::max(max_kc, C.subs_h[s].kC);
-  for (int c = 0; c < max_kc && max_kr > 0; ++c) {
-    hipLaunchKernelGGL(k_psi_row<T>, dim3(max_kr, cnt), dim3(256), chain_lds(max_kr), st, c, s0, (const T*)tiles, C.d_subs,
-                       C.d_scratch_off, (T*)C.d_scratch, (const uint8_t*)C.d_nzl, (const uint8_t*)C.d_nzi);
-    hipLaunchKernelGGL(k_psi_copy<T>, dim3(max_kr, cnt), dim3(256), 0, st, c, s0, tiles, C.d_subs,
-                       C.d_scratch_off, (const T*)C.d_scratch);
-  }
-  HIPCHK(hipGetLastError());
-}
-
-// nonzero count of every tile in [t0, t0 + n) of the factor store
-template <class T>
-// (and, with qmask, the nonzero 16 x 16 quarters of every tile, operand order)
-static std::vector<int32_t> tile_nnz(Ctx& C, int64_t t0, int64_t n, std::vector<int32_t>* qmask = nullptr) {
-  std::vector<int32_t> nnz(n);
-  if (qmask) qmask->assign(n, 0);
-  if (n == 0) return nnz;
-  int32_t* d_nnz = nullptr;
-  HIPCHK(hipMalloc((void**)&d_nnz, 2 * n * sizeof(int32_t)));
-  hipLaunchKernelGGL(k_tile_nnz<T>, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, C.st, t0, n, (const T*)C.d_tiles, d_nnz,
-                     qmask ? d_nnz + n : (int32_t*)nullptr);
-  HIPCHK(hipMemcpyAsync(nnz.data(), d_nnz, n * sizeof(int32_t), hipMemcpyDeviceToHost, C.st));
-  if (qmask)
-    HIPCHK(hipMemcpyAsync(qmask->data(), d_nnz + n, n * sizeof(int32_t), hipMemcpyDeviceToHost, C.st));
-  HIPCHK(hipStreamSynchronize(C.st));
-  HIPCHK(hipFree(d_nnz));
-  return nnz;
+static void pack_blocks(Ctx& C, const Ctx::FacList& F, hipStream_t st) {
+  if (F.n_pack > 0)
+    hipLaunchKernelGGL(k_pack_tiles<T>, dim3((unsigned)F.n_pack), dim3(256), 0, st, (const int64_t*)C.d_pack + F.pack,
+                       (T*)C.d_tiles, (T*)C.d_tilesT, C.d_tinfo, C.d_err + 1);
 }
 
 static void release(Ctx& C, void* p) {
@@ -1171,14 +1309,12 @@ static void ensure_partial(Ctx& C) {
 }
 
 // Replace the coarse work lists by lists of the nonzero tiles of the coarse
-// inverse factor (fixed by the corner order, so built once).
+// inverse factor (info: nonzero counts and quarters of every tile).
 template <class T>
-static void coarse_tile_lists(Ctx& C) {
+static void coarse_tile_lists(Ctx& C, const std::vector<int32_t>& info) {
   const SubDev& qc = C.subs_h[C.nsub];
   const int K = qc.K;
-  const int64_t nt = (int64_t)K * (K + 1) / 2;
-  std::vector<int32_t> nnz = tile_nnz<T>(C, qc.tile_off, nt);
-  auto at = [&](int i, int j) { return nnz[(int64_t)i * (i + 1) / 2 + j]; };
+  auto at = [&](int i, int j) { return info[qc.tile_off + (int64_t)i * (i + 1) / 2 + j] & 0xffff; };
   std::vector<int32_t> ln, lt;
   std::vector<MvItem> bn, bt;
   int64_t entries = 0;
@@ -1320,20 +1456,18 @@ static void build_full_items(Ctx& C) {
 // transposed passes: the I x I block (L_II^-1, "full") and the [Gamma; c] x I
 // block (L_GI and L_cI, "cross").  The interior nested-dissection order
 // leaves whole tiles of L_II^-1 zero, and L_GI, L_cI keep the factor's
-// sparsity.  The pattern is checked after every factorisation and the lists
-// rebuilt when it changed, so a tile is skipped only while it is exactly zero.
+// sparsity.  The pattern is checked after every factorisation (on the device)
+// and the lists rebuilt when it changed, so a tile is skipped only while it is
+// exactly zero.
 template <class T>
-static void full_tile_lists(Ctx& C) {
+static void full_tile_lists(Ctx& C, const std::vector<int32_t>& info) {
   const int64_t nt = C.subs_h[C.nsub].tile_off;  // subdomain tiles come first
-  std::vector<int32_t> qm;
-  std::vector<int32_t> nnz = tile_nnz<T>(C, 0, nt, &qm);
   std::vector<uint8_t> pat(nt);
-  for (int64_t t = 0; t < nt; ++t) pat[t] = (uint8_t)(nnz[t] != 0 ? 16 | qm[t] : 0);
-  if (pat == C.full_pattern && C.full_N.d) return;
+  for (int64_t t = 0; t < nt; ++t) pat[t] = (uint8_t)((info[t] & 0xffff) ? 16 | info[t] >> 16 : 0);
   // zero quarters of a listed tile, in the layout of the store read: the
   // transposed store swaps the off-diagonal quarters
   auto zq = [&](int64_t t, bool transposed) -> int32_t {
-    int32_t z = ~qm[t] & 15;
+    int32_t z = ~(info[t] >> 16) & 15;
     if (transposed) z = (z & 9) | ((z & 2) << 1) | ((z & 4) >> 1);
     return z;
   };
@@ -1344,7 +1478,7 @@ static void full_tile_lists(Ctx& C) {
     const SubDev& q = C.subs_h[s];
     const int kI = q.kI;
     auto tid = [&](int i, int j) { return q.tile_off + (int64_t)i * (i + 1) / 2 + j; };
-    auto at = [&](int i, int j) { return nnz[tid(i, j)]; };
+    auto at = [&](int i, int j) { return info[tid(i, j)] & 0xffff; };
     if (q.K >= kPairMask) throw DDError{DD_ERR_OOM, "too many tile rows in a subdomain"};
     if (kI == 0) continue;
     // forward: I rows over I columns; [Gamma; c] rows over I columns
@@ -1398,12 +1532,10 @@ static void factor_sequence(Ctx& C, hipStream_t st, hipStream_t side) {
   Plan& P = C.P;
   T* tiles = (T*)C.d_tiles;
   // (fills by kernel: the sequence is captured into a graph)
-  {
-    const int64_t n16 = std::max<int64_t>(1, C.ntiles) * kTile * (int64_t)sizeof(T) / 16;
-    hipLaunchKernelGGL(k_clear16, dim3((unsigned)std::min<int64_t>(nblk(n16), 65536)), dim3(256), 0, st, n16,
-                       (uint4*)tiles);
-    hipLaunchKernelGGL(k_set_int, dim3(1), dim3(64), 0, st, C.d_err, (int)INT32_MAX);
-  }
+  if (C.n_clear)
+    hipLaunchKernelGGL(k_clear_tiles<T>, dim3((unsigned)std::min<int64_t>(C.n_clear, 65536)), dim3(256), 0, st,
+                       C.n_clear, (const int64_t*)C.d_clear, tiles);
+  hipLaunchKernelGGL(k_set_int, dim3(1), dim3(64), 0, st, C.d_err, (int)INT32_MAX);
   hipLaunchKernelGGL(k_element, dim3(nblk(P.nt)), dim3(256), 0, st, (int64_t)P.nt, C.d_coords, C.d_tsort,
                      C.d_mu, C.d_Te, C.d_Se);
   hipLaunchKernelGGL(k_pull_local<T>, dim3(nblk(C.n_lent)), dim3(256), 0, st, C.n_lent, C.d_lptr, C.d_lcon,
@@ -1413,41 +1545,46 @@ static void factor_sequence(Ctx& C, hipStream_t st, hipStream_t side) {
   if (C.n_radd)
     hipLaunchKernelGGL(k_add_entries<T>, dim3(nblk(C.n_radd)), dim3(256), 0, st, C.n_radd, C.d_radd_pos,
                        C.d_radd_val, C.robin_alpha, tiles);
-  hipLaunchKernelGGL(k_pull_csr, dim3(nblk(C.nnz)), dim3(256), 0, st, C.nnz, C.d_gptr, C.d_gcon, C.d_Te,
+  HIPCHK(hipGetLastError());
+  // The global (T, S) values and the preconditioner need only the element
+  // matrices: on the side stream beside the factorisation.
+  HIPCHK(hipEventRecord(C.ev_ffork, st));
+  HIPCHK(hipStreamWaitEvent(side, C.ev_ffork, 0));
+  hipLaunchKernelGGL(k_pull_csr, dim3(nblk(C.nnz)), dim3(256), 0, side, C.nnz, C.d_gptr, C.d_gcon, C.d_Te,
                      C.d_Se, C.d_eps, C.d_vals);
   if (C.lam_nnz)
-    hipLaunchKernelGGL(k_pull_lam, dim3(nblk(C.lam_nnz)), dim3(256), 0, st, C.lam_nnz, C.d_lgptr, C.d_lgcon,
+    hipLaunchKernelGGL(k_pull_lam, dim3(nblk(C.lam_nnz)), dim3(256), 0, side, C.lam_nnz, C.d_lgptr, C.d_lgcon,
                        C.d_Te, C.d_Se, C.d_eps, C.beta * C.dt * C.dt, C.d_lvals);
   HIPCHK(hipGetLastError());
-  factor_chol<T>(C, 0, C.nsub, st);
+  factor_blocks<T>(C, C.fac_sub, st);
   // The coarse matrix needs only the subdomains' Schur corner blocks: its
   // assembly and factorisation (a chain of small launches) run on the side
-  // stream while the subdomains' inverse factors are formed on st.  The two
-  // touch disjoint tiles (corner blocks are read; r rows, corner rows of the
-  // r columns and the coarse block are written) and disjoint scratch rows.
-  if (C.Kc > 0) HIPCHK(hipEventRecord(C.ev_ffork, st));
-  factor_inv<T>(C, 0, C.nsub, st);
+  // stream beside Psi_Gamma, M and the packing of the subdomains' tiles.  They
+  // touch disjoint tiles (corner blocks are read, the coarse block written).
+  if (C.Kc > 0) {
+    HIPCHK(hipEventRecord(C.ev_ffork, st));
+    HIPCHK(hipStreamWaitEvent(side, C.ev_ffork, 0));
+    if (C.n_cent)
+      hipLaunchKernelGGL(k_pull_coarse<T>, dim3(nblk(C.n_cent)), dim3(256), 0, side, C.n_cent, C.d_cptr,
+                         C.d_csrc, C.d_cdest, tiles);
+    factor_blocks<T>(C, C.fac_coarse, side);
+    pack_blocks<T>(C, C.fac_coarse, side);
+  }
+  if (C.n_psi)
+    hipLaunchKernelGGL(k_psi<T>, dim3((unsigned)C.n_psi), dim3(256), chain_lds(C.max_kr), st,
+                       (const FacItem*)C.d_fac + C.psi_first, (const T*)tiles, (T*)C.d_tilesT, C.d_subs,
+                       (const uint8_t*)C.d_nzl, (const uint8_t*)C.d_nzi);
   {
     int max_kg = 0;
     for (int s = 0; s < C.nsub; ++s) max_kg = std::max(max_kg, C.subs_h[s].kG);
     if (max_kg > 0)
       hipLaunchKernelGGL(k_schur_inv<T>, dim3((unsigned)(max_kg * (max_kg + 1) / 2), C.nsub), dim3(256),
                          chain_lds(max_kg), st, 0,
-                         (const T*)tiles, C.d_subs, C.d_m_off, (T*)C.d_mtri, (const uint8_t*)C.d_nzi);
+                         (const T*)C.d_tilesT, C.d_subs, C.d_m_off, (T*)C.d_mtri, (const uint8_t*)C.d_nzi);
   }
-  if (C.Kc > 0) {
-    HIPCHK(hipStreamWaitEvent(side, C.ev_ffork, 0));
-    if (C.n_cent)
-      hipLaunchKernelGGL(k_pull_coarse<T>, dim3(nblk(C.n_cent)), dim3(256), 0, side, C.n_cent, C.d_cptr,
-                         C.d_csrc, C.d_cdest, tiles);
-    factor_chol<T>(C, C.nsub, 1, side);
-    factor_inv<T>(C, C.nsub, 1, side);
-    HIPCHK(hipEventRecord(C.ev_fjoin, side));
-    HIPCHK(hipStreamWaitEvent(st, C.ev_fjoin, 0));
-  }
-  if (C.ntiles > 0)
-    hipLaunchKernelGGL(k_pack_tiles<T>, dim3((unsigned)C.ntiles), dim3(256), 0, st, C.ntiles, tiles,
-                       (T*)C.d_tilesT);
+  pack_blocks<T>(C, C.fac_sub, st);
+  HIPCHK(hipEventRecord(C.ev_fjoin, side));
+  HIPCHK(hipStreamWaitEvent(st, C.ev_fjoin, 0));
   HIPCHK(hipGetLastError());
 }
 
@@ -1461,6 +1598,7 @@ static int factor_impl(Ctx& C) {
   C.need_iters = C.need_sweeps = 0;
   HIPCHK(hipEventRecord(C.ev_fa, st));
   HIPCHK(hipStreamWaitEvent(C.fa, C.ev_fa, 0));
+  factor_lists(C);
   if (!C.factor_graph) {
     HIPCHK(hipStreamBeginCapture(C.fa, hipStreamCaptureModeThreadLocal));
     hipGraph_t g = nullptr;
@@ -1479,11 +1617,19 @@ static int factor_impl(Ctx& C) {
   HIPCHK(hipEventRecord(C.ev_fb, C.fa));
   HIPCHK(hipStreamWaitEvent(st, C.ev_fb, 0));
   HIPCHK(hipGetLastError());
-  if (C.Kc > 0 && !C.coarse_lists) coarse_tile_lists<T>(C);
-  full_tile_lists<T>(C);
-  int err = 0;
-  HIPCHK(hipMemcpyAsync(&err, C.d_err, sizeof(int), hipMemcpyDeviceToHost, st));
+  int flags[2] = {0, 0};
+  HIPCHK(hipMemcpyAsync(flags, C.d_err, sizeof(flags), hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
+  const int err = flags[0];
+  if (flags[1] || !C.pattern_valid) {
+    C.pattern_valid = false;
+    std::vector<int32_t> info(C.ntiles);
+    HIPCHK(hipMemcpyAsync(info.data(), C.d_tinfo, C.ntiles * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
+    if (C.Kc > 0) coarse_tile_lists<T>(C, info);
+    full_tile_lists<T>(C, info);
+    C.pattern_valid = true;
+  }
   if (err != INT32_MAX) {
     C.factored = false;
     if (err == C.nsub) throw DDError{DD_ERR_NOT_SPD, "coarse corner matrix is not positive definite"};
@@ -3349,7 +3495,7 @@ static void build_dp2(Ctx& C, const double* coords, const double* eps, const dou
   }
   C.d_rval = upload(rval, C.owned, st);
   C.n_radd = (int64_t)apos.size();
-  C.d_radd_pos = upload(apos, C.owned, st);
+  C.d_radd_pos = upload(operand_positions(C, std::move(apos)), C.owned, st);
   C.d_radd_val = upload(aval, C.owned, st);
   const int64_t nv = ns * nr;
   C.d_gmV = dalloc<double>((size_t)(kGmresRestart + 1) * nv, C.owned);

@@ -90,44 +90,107 @@ __device__ __forceinline__ int chain_list(int m0, int m1, Ok ok, uint16_t* list,
   return nn;
 }
 
-// acc += sum over the listed m of A_m B_m (B_m^T with BT; A_m staged
-// transposed with AT), ptr(m, a, b) giving the two tiles.  The next term's
-// tiles are loaded into registers while the current product runs.
-template <class T, bool AT, bool BT, class Ptr>
-__device__ __forceinline__ void chain_mma(const uint16_t* list, int nn, Ptr ptr, T (*A)[kNB + 1],
-                                          T (*B)[kNB + 1], typename Mfma<T>::acc_t& acc) {
-  constexpr int E = kTile / 256;
-  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, mb = w >> 1, nb = w & 1;
-  if (nn == 0) return;
-  T ra[E], rb[E];
-  const T* ap;
-  const T* bp;
-  ptr((int)list[0], ap, bp);
-#pragma unroll
-  for (int u = 0; u < E; ++u) {
-    ra[u] = ap[tid + 256 * u];
-    rb[u] = bp[tid + 256 * u];
+// Operand order of a 32 x 32 tile: lane l = 16g + i of a wave holds the 8
+// values (row mb*16 + i, columns 8g .. 8g+7) of row block mb, laid out so that
+// each 16-byte load instruction of the wave reads one contiguous kilobyte.
+// Within one 16x16x4 product the reduction index of lane group g at step ks is
+// column 8g + ks, so P Q^T of two tiles takes each lane's chunks as they are.
+// operand-order position of logical element (r, c) of a tile: row block
+// mb = r/16, lane l = 16*(c/8) + r%16, value k = c%8 of that lane, stored
+// as vector q = k/V, component k%V, V = 16/sizeof(T) (see load_chunk8)
+template <class T>
+__host__ __device__ __forceinline__ int swz(int r, int c) {
+  constexpr int V = 16 / sizeof(T);
+  const int l = 16 * (c >> 3) + (r & 15), k = c & 7;
+  return (r >> 4) * 512 + (k / V) * 64 * V + l * V + (k % V);
+}
+
+// the element (r, c) at operand-order position e
+template <class T>
+__device__ __forceinline__ void unswz(int e, int& r, int& c) {
+  constexpr int V = 16 / sizeof(T);
+  const int y = e & 511, ln = (y / V) & 63;
+  r = (e >> 9) * 16 + (ln & 15);
+  c = 8 * (ln >> 4) + (y / (64 * V)) * V + (y % V);
+}
+
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+typedef double f64x2v __attribute__((ext_vector_type(2)));
+
+// 8 values of lane l from one row block (512 elements) in operand order:
+// the q-th 16-byte vector of every lane sits at q*64*V + l*V (V = 16/sizeof(T)),
+// so each load instruction of the wave reads one contiguous kilobyte.
+// (Non-temporal hints on these loads were measured slower.)
+template <class T>
+__device__ __forceinline__ void load_chunk8(const T* __restrict__ blk, int l, T* v) {
+  if constexpr (sizeof(T) == 4) {
+    const f32x4v* q = reinterpret_cast<const f32x4v*>(blk);
+    f32x4v a = q[l], b = q[64 + l];
+    v[0] = a[0]; v[1] = a[1]; v[2] = a[2]; v[3] = a[3];
+    v[4] = b[0]; v[5] = b[1]; v[6] = b[2]; v[7] = b[3];
+  } else {
+    const f64x2v* q = reinterpret_cast<const f64x2v*>(blk);
+    f64x2v a = q[l], b = q[64 + l], c = q[128 + l], d = q[192 + l];
+    v[0] = a[0]; v[1] = a[1]; v[2] = b[0]; v[3] = b[1];
+    v[4] = c[0]; v[5] = c[1]; v[6] = d[0]; v[7] = d[1];
   }
-  for (int t = 0; t < nn; ++t) {
-    __syncthreads();  // the previous product has read A and B
+}
+
+// Sum over the listed m of P_m Q_m^T (ptr(m, p, q): two operand-order tiles) by
+// the 256-thread workgroup: out[u] = the entry at operand-order position tid +
+// 256u of the sum (TR: of its transpose).  Wave w takes the terms w, w + 4, ...
+// whole (32 products of 16x16x4 each), its operands loaded straight into
+// registers one term ahead: no barrier and no LDS inside the chain, whose
+// length bounds the levels of few columns.  The four sums meet in red in wave
+// order.  Ends with red free to use (barrier).
+constexpr int kChainLds = 4 * kNB * (kNB + 1);  // entries of red
+template <class T, bool TR, class Ptr>
+__device__ __forceinline__ void chain_rows(const uint16_t* list, int nn, Ptr ptr, T* __restrict__ red,
+                                           T (&out)[kTile / 256]) {
+  const int tid = threadIdx.x, l = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  typedef typename Mfma<T>::acc_t acc_t;
+  acc_t acc[2][2];
 #pragma unroll
-    for (int u = 0; u < E; ++u) {
-      const int e = tid + 256 * u;
-      if (AT) A[e % kNB][e / kNB] = ra[u];
-      else A[e / kNB][e % kNB] = ra[u];
-      B[e / kNB][e % kNB] = rb[u];
-    }
-    __syncthreads();
-    if (t + 1 < nn) {
-      ptr((int)list[t + 1], ap, bp);
+  for (int h = 0; h < 4; ++h) acc[h >> 1][h & 1] = acc_t{0, 0, 0, 0};
+  T a[2][16], b[2][16];
+  auto ld = [&](int t, int u) {
+    const T *p, *q;
+    ptr(__builtin_amdgcn_readfirstlane((int)list[t]), p, q);
+    load_chunk8(p, l, a[u]);
+    load_chunk8(p + 512, l, a[u] + 8);
+    load_chunk8(q, l, b[u]);
+    load_chunk8(q + 512, l, b[u] + 8);
+  };
+  auto mm = [&](int u) {
 #pragma unroll
-      for (int u = 0; u < E; ++u) {
-        ra[u] = ap[tid + 256 * u];
-        rb[u] = bp[tid + 256 * u];
-      }
-    }
-    tile_mma<T, BT>(A, B, mb, nb, l, acc);
+    for (int ks = 0; ks < 8; ++ks)
+#pragma unroll
+      for (int h = 0; h < 4; ++h)
+        acc[h >> 1][h & 1] = Mfma<T>::op(a[u][(h >> 1) * 8 + ks], b[u][(h & 1) * 8 + ks], acc[h >> 1][h & 1]);
+  };
+  if (w < nn) ld(w, 0);
+  for (int t = w; t < nn; t += 8) {
+    if (t + 4 < nn) ld(t + 4, 1);
+    mm(0);
+    if (t + 8 < nn) ld(t + 8, 0);
+    if (t + 4 < nn) mm(1);
   }
+  T(*rw)[kNB][kNB + 1] = reinterpret_cast<T(*)[kNB][kNB + 1]>(red);
+#pragma unroll
+  for (int h = 0; h < 4; ++h)
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      rw[w][(h >> 1) * 16 + Mfma<T>::row(l, v)][(h & 1) * 16 + (l & 15)] = acc[h >> 1][h & 1][v];
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kTile / 256; ++u) {
+    int r, c;
+    unswz<T>(tid + 256 * u, r, c);
+    const int x = TR ? c : r, y = TR ? r : c;
+    out[u] = ((rw[0][x][y] + rw[1][x][y]) + rw[2][x][y]) + rw[3][x][y];
+  }
+  __syncthreads();
 }
 
 // --------------------------------------------------------------------------
@@ -260,36 +323,61 @@ __global__ void k_pad_diag(int64_t n, const int64_t* __restrict__ pos, T* __rest
 }
 
 // --------------------------------------------------------------------------
-// K2: right-looking tiled partial Cholesky.  For panel k of every subdomain
-// with k < kr: (1) factor the diagonal tile and replace it by the inverse of
-// its Cholesky factor; (2) panel tiles (i, k) <- A_ik Dinv_k^T for i > k
-// (interface and corner rows alike, so corner rows become L_cr);
-// (3) trailing tiles (i, j), k < j <= i, -= L_ik L_jk^T (corner block
-// becomes K_s = A_cc - L_cr L_cr^T).  Arithmetic in the storage type T
-// except the diagonal tile, which is factored and inverted in FP64.
+// K2: tiled partial Cholesky of the [I | Gamma] columns of every block and the
+// inverses of its I x I and Gamma x Gamma diagonal blocks, left-looking and by
+// levels of the tile elimination tree.  Column k of a block needs the columns
+// of its descendants only, so all columns of one level, of all blocks, go
+// together:
+//   k_chol_step: C_ik = A_ik - sum_{m<k} L_im L_km^T over the nonzero tiles of
+//     the level's columns (one workgroup each, the sum in registers: a tile is
+//     read and written once instead of once per earlier column); the diagonal
+//     tile is then factored and replaced by the inverse of its factor Dinv_k.
+//     The same launch forms the inverse rows of the level before,
+//     Linv_ij = -Dinv_i sum_{m=j}^{i-1} L_im Linv_mj, and after the last level
+//     the corner blocks K_s = A_cc - L_cr L_cr^T.
+//   k_chol_trsm: L_ik = C_ik Dinv_k^T (interface and corner rows alike).
+// Only I x I and Gamma x Gamma are inverted; the coupling L_GI stays, so that
+// L_rr^-1 w = [L_II^-1 w_I ; L_GG^-1 (w_G - L_GI L_II^-1 w_I)] is applied as
+// three products (L_GI has far fewer nonzero tiles than the Gamma x I block of
+// L_rr^-1, which is dense).  A block with kG = 0 (the coarse block) is inverted
+// whole.  Inverse tiles go to a second store (inv), so that no row is copied
+// back and L stays readable.  Work lists come from the symbolic factorisation
+// of the tile pattern; the chains skip tiles whose numeric flag is zero
+// (nzl: L, nzi: inverse; flags outside the pattern stay zero).
+// Bound by FP64 MFMA on the wide levels (32^3, 64 boxes: 1472 tiles of 100
+// terms in 115 us, 83 TFLOP/s with the skipped zero tiles counted) and by the
+// latency of one diagonal tile (13 us) on the narrow ones.  Measured there (FP64
+// / FP32 dd_factor): 29.5 / 19.7 ms with a right-looking panel per tile column
+// (C read and written by every earlier column) and row-by-row inverses, 11.4 /
+// 7.4 ms now; 64^3, 1000 boxes, FP32: 86.5 -> 39.6 ms.  Arithmetic in the storage type T except the diagonal
+// tile, which is factored and inverted in FP64.
 // --------------------------------------------------------------------------
-template <class T>
-__global__ void __launch_bounds__(256) k_potrf(int k, int s0, T* __restrict__ tiles,
-                                               const SubDev* __restrict__ subs, int* __restrict__ err,
-                                               uint8_t* __restrict__ nzl, uint8_t* __restrict__ nzi) {
-  const SubDev q = subs[s0 + blockIdx.x];
-  if (k >= q.kI + q.kG) return;
-  if (threadIdx.x == 0) nzl[tile_index(q, k, k)] = nzi[tile_index(q, k, k)] = 1;
-  __shared__ double a[kNB][kNB + 1];
-  __shared__ double x[kNB][kNB + 1];
-  __shared__ double piv[kNB];
-  T* tp = tiles + tile_index(q, k, k) * kTile;
-  const int tid = threadIdx.x;
-  // thread (rb, c) = (tid / 32, tid % 32) owns entries (rb + 8 u, c), u < 4,
-  // kept in registers; LDS holds what other threads read
+struct FacItem {
+  int32_t s;    // block (-1: padding)
+  uint32_t ik;  // tile row << 16 | tile column
+};
+
+// 1 / d to FP64 rounding (hardware estimate and two Newton steps): a division
+// in the chain of the 32 pivots cost a third of the diagonal tile's time.
+__device__ __forceinline__ double recip64(double d) {
+  double r = __builtin_amdgcn_rcp(d);
+  r = __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
+  return __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
+}
+
+// Cholesky factor of the symmetric tile held in a (lower part used), its
+// inverse returned as xv: thread (rb, c) = (tid / 32, tid % 32) of 256 gets
+// entries (rb + 8u, c) of L^-1 (zero above the diagonal).  Returns nonzero when
+// a pivot is not positive and finite (the same in every thread).
+__device__ __forceinline__ int potrf_inv_tile(double (*a)[kNB + 1], double (*x)[kNB + 1], double* piv,
+                                              double (&xv)[kTile / 256]) {
   constexpr int U = kTile / 256;
-  const int c = tid & 31, rb = tid >> 5;
-  double v[U], xv[U];
+  const int tid = threadIdx.x, c = tid & 31, rb = tid >> 5;
+  double v[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int r = rb + 8 * u;
-    v[u] = (double)tp[r * kNB + c];
-    a[r][c] = v[u];
+    v[u] = a[r][c];
     xv[u] = r == c ? 1.0 : 0.0;
     x[r][c] = xv[u];
   }
@@ -310,7 +398,7 @@ __global__ void __launch_bounds__(256) k_potrf(int k, int s0, T* __restrict__ ti
       bad = 1;
       d = 1.0;
     }
-    const double f = acj / d;
+    const double f = acj * recip64(d);
     if (tid == 0) piv[j] = d;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -320,12 +408,14 @@ __global__ void __launch_bounds__(256) k_potrf(int k, int s0, T* __restrict__ ti
     }
     __syncthreads();
   }
-  // L = unscaled columns / sqrt(d)
-  const double sd = sqrt(piv[c]);
+  // L = unscaled columns / sqrt(d); piv becomes 1 / L_jj
+  const double rd = 1.0 / sqrt(piv[c]);
+  __syncthreads();
+  if (rb == 0) piv[c] = rd;
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int r = rb + 8 * u;
-    a[r][c] = r < c ? 0.0 : (r == c ? sd : v[u] / sd);
+    a[r][c] = r > c ? v[u] * rd : 0.0;
   }
   __syncthreads();
   // L^-1 by forward substitution on the identity, all columns at once: at
@@ -333,7 +423,7 @@ __global__ void __launch_bounds__(256) k_potrf(int k, int s0, T* __restrict__ ti
   // take L_rm X_mc / L_mm; the owners of row m + 1 publish it (again one
   // barrier per step)
   for (int m = 0; m < kNB; ++m) {
-    const double g = x[m][c] / a[m][m];
+    const double g = x[m][c] * piv[m];
     double arm[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) arm[u] = a[rb + 8 * u][m];
@@ -348,215 +438,175 @@ __global__ void __launch_bounds__(256) k_potrf(int k, int s0, T* __restrict__ ti
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int r = rb + 8 * u;
-    tp[r * kNB + c] = (T)(c <= r ? xv[u] / a[r][r] : 0.0);
+    xv[u] = c <= r ? xv[u] * piv[r] : 0.0;
   }
-  if (tid == 0 && bad) atomicMin(err, s0 + (int)blockIdx.x);
+  return bad;
+}
+
+// Items [0, nd): diagonal tiles; [nd, nd + no): off-diagonal tiles (i, k) and
+// corner tiles; the rest: inverse tiles (i, j).  All tiles are in operand order
+// and inverse tiles transposed (inv tile (i, j) = Linv_ij^T), so that every
+// product of the factorisation has the form P Q^T of two tiles whose lanes read
+// contiguous kilobytes (from row-major tiles, 64-byte pieces of 16 rows: the
+// steps took 1.4 times as long), and the solves' transposed store is final.
+template <class T>
+__global__ void __launch_bounds__(256) k_chol_step(int nd, int no, const FacItem* __restrict__ items,
+                                                   T* __restrict__ tiles, T* __restrict__ inv,
+                                                   const SubDev* __restrict__ subs, int* __restrict__ err,
+                                                   uint8_t* __restrict__ nzl, uint8_t* __restrict__ nzi) {
+  const int b = blockIdx.x;
+  const FacItem it = items[b];
+  if (it.s < 0) return;
+  const SubDev q = subs[it.s];
+  const int i = (int)(it.ik >> 16), k = (int)(it.ik & 0xffffu);
+  // the chain's four sums; the diagonal tile's FP64 work and the product with
+  // Dinv reuse them (two FP64 tiles)
+  __shared__ __align__(16) unsigned char lds[sizeof(T) == 8 ? kChainLds * 8 : 2 * kNB * (kNB + 1) * 8];
+  static_assert(sizeof(lds) >= kChainLds * sizeof(T), "chain sums");
+  __shared__ double piv[kNB];
+  __shared__ int wcnt[4];
+  extern __shared__ uint16_t list[];
+  T* red = reinterpret_cast<T*>(lds);
+  constexpr int U = kTile / 256;
+  const int tid = threadIdx.x, c = tid & 31, rb = tid >> 5;
+  T sum[U];
+  const uint8_t* fi = nzl + tile_index(q, i, 0);
+  const T* ri = tiles + tile_index(q, i, 0) * kTile;
+  if (b < nd + no) {
+    // columns past r (corner blocks) take all of r
+    const int m1 = min(k, q.kI + q.kG);
+    const uint8_t* fk = nzl + tile_index(q, k, 0);
+    const int nn = chain_list(0, m1, [&](int m) { return fi[m] && fk[m]; }, list, wcnt);
+    if (b >= nd && nn == 0) return;
+    const T* rk = tiles + tile_index(q, k, 0) * kTile;
+    chain_rows<T, false>(
+        list, nn,
+        [&](int m, const T*& ap, const T*& bp) {
+          ap = ri + (int64_t)m * kTile;  // L_im
+          bp = rk + (int64_t)m * kTile;  // L_km
+        },
+        red, sum);
+    T* cp = tiles + tile_index(q, i, k) * kTile;
+    if (b >= nd) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) cp[tid + 256 * u] -= sum[u];
+      return;
+    }
+    double(*a)[kNB + 1] = reinterpret_cast<double(*)[kNB + 1]>(lds);
+    double(*x)[kNB + 1] = a + kNB;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      int r0, c0;
+      unswz<T>(tid + 256 * u, r0, c0);
+      a[r0][c0] = (double)cp[tid + 256 * u] - (double)sum[u];
+    }
+    __syncthreads();
+    double xv[U];
+    const int bad = potrf_inv_tile(a, x, piv, xv);
+    T* dp = inv + tile_index(q, k, k) * kTile;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      cp[swz<T>(rb + 8 * u, c)] = (T)xv[u];
+      dp[swz<T>(c, rb + 8 * u)] = (T)xv[u];
+    }
+    if (tid == 0) {
+      nzl[tile_index(q, k, k)] = nzi[tile_index(q, k, k)] = 1;
+      if (bad) atomicMin(err, it.s);
+    }
+    return;
+  }
+  // inverse tile (i, j = k): -Dinv_i sum_m L_im Linv_mj, formed transposed
+  const int nn = chain_list(k, i, [&](int m) { return fi[m] && nzi[tile_index(q, m, k)]; }, list, wcnt);
+  chain_rows<T, false>(
+      list, nn,
+      [&](int m, const T*& ap, const T*& bp) {
+        ap = ri + (int64_t)m * kTile;            // L_im
+        bp = inv + tile_index(q, m, k) * kTile;  // Linv_mj^T
+      },
+      red, sum);
+  T(*S)[kNB + 1] = reinterpret_cast<T(*)[kNB + 1]>(red);  // the sum, transposed
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    int r0, c0;
+    unswz<T>(tid + 256 * u, r0, c0);
+    S[c0][r0] = sum[u];
+  }
+  const int w = tid >> 6, l = tid & 63, mb = w >> 1, nb = w & 1;
+  T d[8];
+  load_chunk8(tiles + tile_index(q, i, i) * kTile + mb * 512, l, d);
+  __syncthreads();
+  typename Mfma<T>::acc_t out = {0, 0, 0, 0};
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) out = Mfma<T>::op(d[ks], S[nb * 16 + (l & 15)][8 * (l >> 4) + ks], out);
+  T* sp = inv + tile_index(q, i, k) * kTile;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) sp[swz<T>(nb * 16 + (l & 15), mb * 16 + Mfma<T>::row(l, v))] = -out[v];
+  const int nz = __syncthreads_or(out[0] != (T)0 || out[1] != (T)0 || out[2] != (T)0 || out[3] != (T)0);
+  if (tid == 0) nzi[tile_index(q, i, k)] = (uint8_t)(nz != 0);
 }
 
 template <class T>
-__global__ void __launch_bounds__(256) k_trsm(int k, int s0, T* __restrict__ tiles,
-                                              const SubDev* __restrict__ subs, uint8_t* __restrict__ nzl) {
-  const SubDev q = subs[s0 + blockIdx.y];
-  const int i = k + 1 + blockIdx.x;
-  if (k >= q.kI + q.kG || i >= q.K) return;
-  __shared__ T A[kNB][kNB + 1];
-  __shared__ T Dv[kNB][kNB + 1];
+__global__ void __launch_bounds__(256) k_chol_trsm(const FacItem* __restrict__ items, T* __restrict__ tiles,
+                                                   const SubDev* __restrict__ subs, uint8_t* __restrict__ nzl) {
+  const FacItem it = items[blockIdx.x];
+  if (it.s < 0) return;
+  const SubDev q = subs[it.s];
+  const int i = (int)(it.ik >> 16), k = (int)(it.ik & 0xffffu);
   T* ap = tiles + tile_index(q, i, k) * kTile;
   const T* dp = tiles + tile_index(q, k, k) * kTile;
   const int tid = threadIdx.x;
-  for (int e = tid; e < kTile; e += 256) {
-    A[e / kNB][e % kNB] = ap[e];
-    Dv[e / kNB][e % kNB] = dp[e];
-  }
-  __syncthreads();
-  // L_ik = A_ik Dinv_k^T on MFMA: wave w computes block (w/2, w%2)
+  // L_ik^T = Dinv_k C_ik^T on MFMA: wave w computes columns mb, rows nb of
+  // L_ik from operands loaded straight into registers (in this orientation a
+  // lane's four results lie next to each other in operand order)
   const int w = tid >> 6, l = tid & 63, mb = w >> 1, nb = w & 1;
+  T a[8], d[8];
+  load_chunk8(ap + nb * 512, l, a);
+  load_chunk8(dp + mb * 512, l, d);
   typename Mfma<T>::acc_t acc = {0, 0, 0, 0};
-  tile_mma<T, true>(A, Dv, mb, nb, l, acc);
 #pragma unroll
-  for (int v = 0; v < 4; ++v) ap[(mb * 16 + Mfma<T>::row(l, v)) * kNB + nb * 16 + (l & 15)] = acc[v];
-  // nonzero flag of L_ik (a zero tile takes no part in later products)
+  for (int ks = 0; ks < 8; ++ks) acc = Mfma<T>::op(d[ks], a[ks], acc);
+  // nonzero flag of L_ik (a zero tile takes no part in later products); the
+  // barrier also orders every wave's reads of the tile before the writes
   const int nz = __syncthreads_or(acc[0] != (T)0 || acc[1] != (T)0 || acc[2] != (T)0 || acc[3] != (T)0);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) ap[swz<T>(nb * 16 + (l & 15), mb * 16 + Mfma<T>::row(l, v))] = acc[v];
   if (tid == 0) nzl[tile_index(q, i, k)] = (uint8_t)(nz != 0);
 }
 
-// Tile rows of one factor column held by the trailing-update kernel's list.
-constexpr int kColList = 8192;
-
-// Trailing update of step k over the nonzero tiles of column k only: every
-// workgroup of a subdomain compacts the rows i > k with L_ik != 0 into an LDS
-// list, then takes the pairs (a >= b) of that list strided by the grid's x
-// size: C_ij -= L_ik L_jk^T.  (A grid over all pairs would dispatch one
-// workgroup per trailing tile per step, nearly all of them on zero tiles of
-// the nested-dissection order.)  Requires K - k - 1 <= kColList.
-template <class T>
-__global__ void __launch_bounds__(256) k_syrk(int k, int s0, T* __restrict__ tiles,
-                                              const SubDev* __restrict__ subs, const uint8_t* __restrict__ nzl) {
-  const SubDev q = subs[s0 + blockIdx.y];
-  if (k >= q.kI + q.kG) return;
-  const int Tn = q.K - k - 1;
-  __shared__ uint16_t list[kColList];
-  __shared__ int wcnt[4];
-  __shared__ T A[kNB][kNB + 1];
-  __shared__ T B[kNB][kNB + 1];
-  const int tid = threadIdx.x;
-  const int w = tid >> 6, l = tid & 63, mb = w >> 1, nb = w & 1;
-  int nn = 0;
-  for (int b0 = 0; b0 < Tn; b0 += 256) {
-    const int ii = b0 + tid;
-    const bool nz = ii < Tn && nzl[tile_index(q, k + 1 + ii, k)];
-    const unsigned long long bal = __ballot(nz);
-    if (l == 0) wcnt[w] = __popcll(bal);
-    __syncthreads();
-    int off = nn;
-    for (int x = 0; x < w; ++x) off += wcnt[x];
-    if (nz) list[off + __popcll(bal & ((1ull << l) - 1ull))] = (uint16_t)ii;
-    nn += wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
-    __syncthreads();
-  }
-  const int64_t npair = (int64_t)nn * (nn + 1) / 2;
-  for (int64_t p = blockIdx.x; p < npair; p += gridDim.x) {
-    int a = (int)((sqrt(8.0 * (double)p + 1.0) - 1.0) * 0.5);
-    while ((int64_t)(a + 1) * (a + 2) / 2 <= p) ++a;
-    while ((int64_t)a * (a + 1) / 2 > p) --a;
-    const int bb = (int)(p - (int64_t)a * (a + 1) / 2);
-    const int i = k + 1 + list[a], j = k + 1 + list[bb];
-    const T* ap = tiles + tile_index(q, i, k) * kTile;
-    const T* bp = tiles + tile_index(q, j, k) * kTile;
-    T* cp = tiles + tile_index(q, i, j) * kTile;
-    __syncthreads();
-    for (int e = tid; e < kTile; e += 256) {
-      A[e / kNB][e % kNB] = ap[e];
-      B[e / kNB][e % kNB] = bp[e];
-    }
-    __syncthreads();
-    // C_ij -= L_ik L_jk^T on MFMA: wave w computes block (w/2, w%2)
-    typename Mfma<T>::acc_t acc = {0, 0, 0, 0};
-    tile_mma<T, true>(A, B, mb, nb, l, acc);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) cp[(mb * 16 + Mfma<T>::row(l, v)) * kNB + nb * 16 + (l & 15)] -= acc[v];
-  }
-}
-
-// --------------------------------------------------------------------------
-// Inversion of the diagonal blocks of the r-block Cholesky factor, one block
-// row at a time: Linv_ij = -Dinv_i sum_{m=j}^{i-1} L_im Linv_mj (rows < i
-// already inverted, row i still holds L), written to a scratch row, then
-// copied back.  Only the I x I block (L_II^-1) and the Gamma x Gamma block
-// (L_GG^-1) are inverted; the coupling L_GI stays as the factor left it, so
-// that L_rr^-1 w = [L_II^-1 w_I ; L_GG^-1 (w_G - L_GI L_II^-1 w_I)] is applied
-// as three products (L_GI has far fewer nonzero tiles than the Gamma x I
-// block of L_rr^-1, which is dense).  A block with kG = 0 (the coarse block)
-// is inverted whole.
-// --------------------------------------------------------------------------
-template <class T>
-__global__ void __launch_bounds__(256) k_trtri_row(int i, int s0, const T* __restrict__ tiles,
-                                                   const SubDev* __restrict__ subs,
-                                                   const int64_t* __restrict__ scratch_off,
-                                                   T* __restrict__ scratch, const uint8_t* __restrict__ nzl,
-                                                   uint8_t* __restrict__ nzi) {
-  const int sidx = s0 + blockIdx.y;
-  const SubDev q = subs[sidx];
-  const int j = blockIdx.x;
-  const int kr = q.kI + q.kG;
-  if (i >= kr || j >= i) return;
-  if (i >= q.kI && j < q.kI) return;  // L_GI is kept
-  __shared__ T A[kNB][kNB + 1];
-  __shared__ T B[kNB][kNB + 1];
-  const int tid = threadIdx.x;
-  const int w = tid >> 6, l = tid & 63, mb = w >> 1, nb = w & 1;
-  typename Mfma<T>::acc_t acc = {0, 0, 0, 0};
-  // terms with a zero L_im or Linv_mj are skipped
-  extern __shared__ uint16_t list[];
-  __shared__ int wcnt[4];
-  const int nn = chain_list(
-      j, i, [&](int m) { return nzl[tile_index(q, i, m)] && nzi[tile_index(q, m, j)]; }, list, wcnt);
-  chain_mma<T, false, false>(
-      list, nn,
-      [&](int m, const T*& ap, const T*& bp) {
-        ap = tiles + tile_index(q, i, m) * kTile;  // L_im
-        bp = tiles + tile_index(q, m, j) * kTile;  // Linv_mj
-      },
-      A, B, acc);
-  // multiply by -Dinv_i (MFMA again, the sum staged in LDS)
-  __syncthreads();
-  const T* dp = tiles + tile_index(q, i, i) * kTile;
-  for (int e = tid; e < kTile; e += 256) A[e / kNB][e % kNB] = dp[e];
-#pragma unroll
-  for (int v = 0; v < 4; ++v) B[mb * 16 + Mfma<T>::row(l, v)][nb * 16 + (l & 15)] = acc[v];
-  __syncthreads();
-  typename Mfma<T>::acc_t out = {0, 0, 0, 0};
-  tile_mma<T, false>(A, B, mb, nb, l, out);
-  T* sp = scratch + (scratch_off[sidx] + j) * kTile;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) sp[(mb * 16 + Mfma<T>::row(l, v)) * kNB + nb * 16 + (l & 15)] = -out[v];
-  // Linv_ij's flag (rows below i read it; row i's own terms do not)
-  const int nz = __syncthreads_or(out[0] != (T)0 || out[1] != (T)0 || out[2] != (T)0 || out[3] != (T)0);
-  if (tid == 0) nzi[tile_index(q, i, j)] = (uint8_t)(nz != 0);
-}
-
-template <class T>
-__global__ void k_trtri_copy(int i, int s0, T* __restrict__ tiles, const SubDev* __restrict__ subs,
-                             const int64_t* __restrict__ scratch_off, const T* __restrict__ scratch) {
-  const int sidx = s0 + blockIdx.y;
-  const SubDev q = subs[sidx];
-  const int j = blockIdx.x;
-  if (i >= q.kI + q.kG || j >= i) return;
-  if (i >= q.kI && j < q.kI) return;  // L_GI is kept
-  T* dst = tiles + tile_index(q, i, j) * kTile;
-  const T* src = scratch + (scratch_off[sidx] + j) * kTile;
-  for (int e = threadIdx.x; e < kTile; e += blockDim.x) dst[e] = src[e];
-}
+// Most tile rows of a block (16-bit rows of the work lists and of the chain
+// lists in LDS).
+constexpr int kMaxBlockRows = 8193;
 
 // Corner coupling premultiplied by the interface inverse factor: in corner
-// tile row i = kr + c the Gamma columns become Psi_G(i, j) = sum_{m=j}^{kr-1}
-// L_cG(i, m) Linv_GG(m, j), kI <= j < kr, i.e. Psi_G = L_cG L_GG^-1 (with
-// t = L_rr^-1 w, L_cG t_G = Psi_G y_G for y_G = w_G - L_GI t_I); the I columns
-// keep L_cI.  A block with kG = 0 (the coarse block) has no corner rows.
-// Written to scratch, then copied.
+// tile row i the Gamma columns give Psi_G(i, j) = sum_{m=j}^{kr-1} L_cG(i, m)
+// Linv_GG(m, j), kI <= j < kr, i.e. Psi_G = L_cG L_GG^-1 (with t = L_rr^-1 w,
+// L_cG t_G = Psi_G y_G for y_G = w_G - L_GI t_I), written transposed to the
+// inverse store; the I columns keep L_cI.
 template <class T>
-__global__ void __launch_bounds__(256) k_psi_row(int c, int s0, const T* __restrict__ tiles,
-                                                 const SubDev* __restrict__ subs,
-                                                 const int64_t* __restrict__ scratch_off, T* __restrict__ scratch,
-                                                 const uint8_t* __restrict__ nzl, const uint8_t* __restrict__ nzi) {
-  const int sidx = s0 + blockIdx.y;
-  const SubDev q = subs[sidx];
-  const int j = blockIdx.x;
+__global__ void __launch_bounds__(256) k_psi(const FacItem* __restrict__ items, const T* __restrict__ tiles,
+                                             T* __restrict__ inv, const SubDev* __restrict__ subs,
+                                             const uint8_t* __restrict__ nzl, const uint8_t* __restrict__ nzi) {
+  const FacItem it = items[blockIdx.x];
+  if (it.s < 0) return;
+  const SubDev q = subs[it.s];
+  const int i = (int)(it.ik >> 16), j = (int)(it.ik & 0xffffu);
   const int kr = q.kI + q.kG;
-  if (c >= q.kC || j >= kr || j < q.kI) return;
-  const int i = kr + c;
-  __shared__ T A[kNB][kNB + 1];
-  __shared__ T B[kNB][kNB + 1];
-  const int tid = threadIdx.x;
-  const int w = tid >> 6, l = tid & 63, mb = w >> 1, nb = w & 1;
-  typename Mfma<T>::acc_t acc = {0, 0, 0, 0};
-  extern __shared__ uint16_t list[];
+  __shared__ T red[kChainLds];
   __shared__ int wcnt[4];
+  extern __shared__ uint16_t list[];
   const int nn = chain_list(
       j, kr, [&](int m) { return nzl[tile_index(q, i, m)] && nzi[tile_index(q, m, j)]; }, list, wcnt);
-  chain_mma<T, false, false>(
+  T sum[kTile / 256];
+  chain_rows<T, true>(
       list, nn,
       [&](int m, const T*& ap, const T*& bp) {
         ap = tiles + tile_index(q, i, m) * kTile;  // L_cr(i, m)
-        bp = tiles + tile_index(q, m, j) * kTile;  // Linv(m, j)
+        bp = inv + tile_index(q, m, j) * kTile;    // Linv(m, j)^T
       },
-      A, B, acc);
-  T* sp = scratch + (scratch_off[sidx] + j) * kTile;
+      red, sum);
+  T* sp = inv + tile_index(q, i, j) * kTile;
 #pragma unroll
-  for (int v = 0; v < 4; ++v) sp[(mb * 16 + Mfma<T>::row(l, v)) * kNB + nb * 16 + (l & 15)] = acc[v];
-}
-
-template <class T>
-__global__ void k_psi_copy(int c, int s0, T* __restrict__ tiles, const SubDev* __restrict__ subs,
-                           const int64_t* __restrict__ scratch_off, const T* __restrict__ scratch) {
-  const int sidx = s0 + blockIdx.y;
-  const SubDev q = subs[sidx];
-  const int j = blockIdx.x;
-  const int kr = q.kI + q.kG;
-  if (c >= q.kC || j >= kr || j < q.kI) return;
-  T* dst = tiles + tile_index(q, kr + c, j) * kTile;
-  const T* src = scratch + (scratch_off[sidx] + j) * kTile;
-  for (int e = threadIdx.x; e < kTile; e += blockDim.x) dst[e] = src[e];
+  for (int u = 0; u < kTile / 256; ++u) sp[threadIdx.x + 256 * u] = sum[u];
 }
 
 // Coarse corner matrix K_cc = sum_s B_c^T K_s B_c by pull (fixed order).
@@ -574,14 +624,10 @@ __global__ void k_pull_coarse(int64_t n, const int64_t* __restrict__ ptr, const 
 // Batched tile products for the solves (the substitutions, applied through
 // the stored inverse factors).
 //
-// Solve-phase tile layout ("operand order"): lane l = 16g + i of a wave
-// holds the 8 values (row mb*16+i, columns 8g..8g+7) of row block mb, laid
-// out so that each 16-byte load instruction of the wave reads one contiguous
-// kilobyte (swz / load_chunk8): a whole tile is one fully coalesced sweep.  The store used for products with the tile
-// itself (NOTRANS) holds each tile in this order; a second store holds the
-// transposed tiles in the same order (TRANS).  Within one 16x16x4 MFMA the
-// reduction index of lane group g at step ks is column 8g + ks, so the
-// operand of every lane is a register of its contiguous chunk.
+// Tiles are in operand order (swz / load_chunk8): a whole tile is one fully
+// coalesced sweep.  The store used for products with the tile itself (NOTRANS)
+// holds each tile in this order; a second store holds the transposed tiles in
+// the same order (TRANS).
 //
 // One work item = one wave = (subdomain, output block o, tile range
 // [lo, hi)); with a tile list (mlist != null, used for the sparse coarse
@@ -700,39 +746,6 @@ __device__ __forceinline__ void block_rhs_sum_v(const double (&s)[V], int nrhs, 
 struct MvOut {
   int32_t s, o, slot0, nslot;
 };
-
-// operand-order position of logical element (r, c) of a tile: row block
-// mb = r/16, lane l = 16*(c/8) + r%16, value k = c%8 of that lane, stored
-// as vector q = k/V, component k%V, V = 16/sizeof(T) (see load_chunk8)
-template <class T>
-__device__ __forceinline__ int swz(int r, int c) {
-  constexpr int V = 16 / sizeof(T);
-  const int l = 16 * (c >> 3) + (r & 15), k = c & 7;
-  return (r >> 4) * 512 + (k / V) * 64 * V + l * V + (k % V);
-}
-
-
-typedef float f32x4v __attribute__((ext_vector_type(4)));
-typedef double f64x2v __attribute__((ext_vector_type(2)));
-
-// 8 values of lane l from one row block (512 elements) in operand order:
-// the q-th 16-byte vector of every lane sits at q*64*V + l*V (V = 16/sizeof(T)),
-// so each load instruction of the wave reads one contiguous kilobyte.
-// (Non-temporal hints on these loads were measured slower.)
-template <class T>
-__device__ __forceinline__ void load_chunk8(const T* __restrict__ blk, int l, T* v) {
-  if constexpr (sizeof(T) == 4) {
-    const f32x4v* q = reinterpret_cast<const f32x4v*>(blk);
-    f32x4v a = q[l], b = q[64 + l];
-    v[0] = a[0]; v[1] = a[1]; v[2] = a[2]; v[3] = a[3];
-    v[4] = b[0]; v[5] = b[1]; v[6] = b[2]; v[7] = b[3];
-  } else {
-    const f64x2v* q = reinterpret_cast<const f64x2v*>(blk);
-    f64x2v a = q[l], b = q[64 + l], c = q[128 + l], d = q[192 + l];
-    v[0] = a[0]; v[1] = a[1]; v[2] = b[0]; v[3] = b[1];
-    v[4] = c[0]; v[5] = c[1]; v[6] = d[0]; v[7] = d[1];
-  }
-}
 
 // Sum over the tiles k = lo, lo + step, ... < hi of one output block's range by
 // one wave.  NV > 0: vector path for nrhs <= NV, vacc[mb NV + r]; NV == 0:
@@ -1519,43 +1532,6 @@ __global__ void __launch_bounds__(256) k_mv_reduce(int64_t n_out, const MvOut* _
   }
 }
 
-// Nonzero count of every tile in [t0, t0 + n) (structural zeros of a
-// nested-dissection-ordered factor and of its inverse are exact zeros).
-template <class T>
-__global__ void __launch_bounds__(256) k_tile_nnz(int64_t t0, int64_t n, const T* __restrict__ tiles,
-                                                  int32_t* __restrict__ nnz, int32_t* __restrict__ qmask) {
-  // one wave per tile: nonzeros of the tile (operand order), and per 16 x 16
-  // quarter (bit 2 * row half + column half set when the quarter holds a
-  // nonzero).  Lane l's 16-byte load k covers entries e = V (l + 64 k), whose
-  // operand lane is l, so the quarter is 2 (e / 512) + l / 32: per-lane
-  // counts and a shuffle sum per quarter, no atomics.
-  const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (t >= n) return;
-  constexpr int V = 16 / sizeof(T);
-  constexpr int L = kTile / (64 * V);  // loads per lane
-  constexpr int P = 512 / (64 * V);    // loads per 512-entry half
-  const int l = threadIdx.x & 63;
-  typedef T vec_t __attribute__((ext_vector_type(V)));
-  const vec_t* p = (const vec_t*)(tiles + (t0 + t) * kTile) + l;
-  int a[2] = {0, 0};  // this lane's nonzeros in the row halves
-#pragma unroll
-  for (int k = 0; k < L; ++k) {
-    const vec_t v = p[64 * k];
-#pragma unroll
-    for (int j = 0; j < V; ++j) a[k / P] += v[j] != (T)0;
-  }
-  // quarter 2 h + l / 32: sum over the lanes of each column half
-  int c[4] = {l < 32 ? a[0] : 0, l < 32 ? 0 : a[0], l < 32 ? a[1] : 0, l < 32 ? 0 : a[1]};
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) c[q] += __shfl_xor(c[q], o);
-  if (l == 0) {
-    nnz[t] = c[0] + c[1] + c[2] + c[3];
-    if (qmask) qmask[t] = (c[0] > 0) | (c[1] > 0) << 1 | (c[2] > 0) << 2 | (c[3] > 0) << 3;
-  }
-}
-
 // Interface block of the local inverse K_rr^-1 = Linv_rr^T Linv_rr (the
 // local inverses stored for the substitutions, Sec. III-C).  Linv_rr is lower
 // triangular with Gamma ordered last in r, so the block is
@@ -1563,9 +1539,9 @@ __global__ void __launch_bounds__(256) k_tile_nnz(int64_t t0, int64_t n, const T
 // (k_symv).  One workgroup per tile (o, m), o >= m (interface tile indices):
 //     M_om = sum_{k >= o} Linv_ko^T Linv_km,
 // written in operand order to tile o(o+1)/2 + m of the subdomain's packed
-// lower triangle (from tile m_off[s]).  Reads the row-major factor store.
+// lower triangle (from tile m_off[s]).  Reads the (transposed) inverse tiles.
 template <class T>
-__global__ void __launch_bounds__(256) k_schur_inv(int s0, const T* __restrict__ tiles,
+__global__ void __launch_bounds__(256) k_schur_inv(int s0, const T* __restrict__ inv,
                                                    const SubDev* __restrict__ subs,
                                                    const int64_t* __restrict__ m_off, T* __restrict__ msq,
                                                    const uint8_t* __restrict__ nzi) {
@@ -1577,47 +1553,93 @@ __global__ void __launch_bounds__(256) k_schur_inv(int s0, const T* __restrict__
   while (o * (o + 1) / 2 > p) --o;
   const int m = p - o * (o + 1) / 2;
   if (o >= q.kG) return;
-  __shared__ T A[kNB][kNB + 1];
-  __shared__ T B[kNB][kNB + 1];
-  const int tid = threadIdx.x;
-  const int w = tid >> 6, l = tid & 63, mb = w >> 1, nb = w & 1;
-  typename Mfma<T>::acc_t acc = {0, 0, 0, 0};
-  extern __shared__ uint16_t list[];
+  __shared__ T red[kChainLds];
   __shared__ int wcnt[4];
+  extern __shared__ uint16_t list[];
   const int nn = chain_list(
       o, q.kG,
       [&](int k) { return nzi[tile_index(q, q.kI + k, q.kI + o)] && nzi[tile_index(q, q.kI + k, q.kI + m)]; },
       list, wcnt);
-  chain_mma<T, true, false>(
+  T sum[kTile / 256];
+  chain_rows<T, false>(
       list, nn,
       [&](int k, const T*& ap, const T*& bp) {
-        ap = tiles + tile_index(q, q.kI + k, q.kI + o) * kTile;  // Linv_ko (staged transposed)
-        bp = tiles + tile_index(q, q.kI + k, q.kI + m) * kTile;  // Linv_km
+        ap = inv + tile_index(q, q.kI + k, q.kI + o) * kTile;  // Linv_ko^T
+        bp = inv + tile_index(q, q.kI + k, q.kI + m) * kTile;  // Linv_km^T
       },
-      A, B, acc);
+      red, sum);
   T* d = msq + (m_off[sidx] + (int64_t)o * (o + 1) / 2 + m) * kTile;
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int r = mb * 16 + Mfma<T>::row(l, v), c = nb * 16 + (l & 15);
-    d[swz<T>(r, c)] = acc[v];
+  for (int u = 0; u < kTile / 256; ++u) d[threadIdx.x + 256 * u] = sum[u];
+}
+
+// The other orientation of the tiles that the solves read: tile t = list >> 1 is
+// transposed from tN to tT (low bit 0: L as factored) or from tT to tN (1: the
+// inverse tiles and Psi_G), both in operand order.  Tiles outside the factor's
+// symbolic pattern, Linv_GG (only M and Psi_G are applied) and the corner
+// blocks are never read by a solve and are left out: packing every tile moved
+// 9.4 GB at 32^3, 64 boxes, FP64 (2.8 ms, and 0.7 ms for a separate count of
+// the nonzeros, which is taken here), this 3 GB (0.6 ms).
+// info[t] = nonzeros | nonzero 16 x 16 quarters << 16 (bit 2 * row half +
+// column half); *changed is set when a tile's zero pattern differs from the
+// info of the factorisation before.
+template <class T>
+__global__ void __launch_bounds__(256) k_pack_tiles(const int64_t* __restrict__ list, T* __restrict__ tN,
+                                                    T* __restrict__ tT, int32_t* __restrict__ info,
+                                                    int* __restrict__ changed) {
+  const int64_t ent = list[blockIdx.x], t = ent >> 1;
+  const bool inv = ent & 1;
+  __shared__ T a[kNB][kNB + 1];
+  __shared__ int cnt[4];
+  const T* src = (inv ? tT : tN) + t * kTile;
+  T* dst = (inv ? tN : tT) + t * kTile;
+  const int tid = threadIdx.x, l = tid & 63;
+  if (tid < 4) cnt[tid] = 0;
+  // position tid + 256u: row half u / 2; the column half is the same for a wave
+  int n[2] = {0, 0};
+#pragma unroll
+  for (int u = 0; u < kTile / 256; ++u) {
+    int r, c;
+    unswz<T>(tid + 256 * u, r, c);
+    const T v = src[tid + 256 * u];
+    a[r][c] = v;
+    n[u / 2] += (int)__popcll(__ballot(v != (T)0));
+  }
+  __syncthreads();
+  if (l == 0) {
+    int r0, c0;
+    unswz<T>(tid, r0, c0);
+    atomicAdd(&cnt[c0 >> 4], n[0]);
+    atomicAdd(&cnt[2 + (c0 >> 4)], n[1]);
+  }
+#pragma unroll
+  for (int u = 0; u < kTile / 256; ++u) {
+    int r, c;
+    unswz<T>(tid + 256 * u, r, c);
+    dst[tid + 256 * u] = a[c][r];
+  }
+  __syncthreads();
+  if (tid == 0) {
+    // quarters of the tile itself: the transposed source swaps the off-diagonal ones
+    const int q1 = inv ? cnt[2] : cnt[1], q2 = inv ? cnt[1] : cnt[2];
+    const int nn = cnt[0] + cnt[1] + cnt[2] + cnt[3];
+    const int qm = (cnt[0] > 0) | (q1 > 0) << 1 | (q2 > 0) << 2 | (cnt[3] > 0) << 3;
+    const int32_t now = nn | qm << 16, was = info[t];
+    if ((now >> 16) != (was >> 16)) atomicOr(changed, 1);
+    info[t] = now;
   }
 }
 
-// Reorder every tile of a store from row-major into operand order, and
-// write the operand-order transposed copy into tT.
+// zero the listed tiles (16-byte stores)
 template <class T>
-__global__ void __launch_bounds__(256) k_pack_tiles(int64_t ntiles, T* __restrict__ tN, T* __restrict__ tT) {
-  const int64_t t = blockIdx.x;
-  if (t >= ntiles) return;
-  __shared__ T a[kNB][kNB + 1];
-  T* p = tN + t * kTile;
-  for (int e = threadIdx.x; e < kTile; e += 256) a[e / kNB][e % kNB] = p[e];
-  __syncthreads();
-  T* q = tT + t * kTile;
-  for (int e = threadIdx.x; e < kTile; e += 256) {
-    const int r = e / kNB, c = e % kNB;
-    p[swz<T>(r, c)] = a[r][c];
-    q[swz<T>(r, c)] = a[c][r];
+__global__ void __launch_bounds__(256) k_clear_tiles(int64_t n, const int64_t* __restrict__ list,
+                                                     T* __restrict__ tiles) {
+  constexpr int Q = kTile * sizeof(T) / 16;  // 16-byte words of a tile
+  const uint4 z = {0u, 0u, 0u, 0u};
+  for (int64_t t = blockIdx.x; t < n; t += gridDim.x) {
+    uint4* p = reinterpret_cast<uint4*>(tiles + list[t] * kTile);
+#pragma unroll
+    for (int e = threadIdx.x; e < Q; e += 256) p[e] = z;
   }
 }
 
@@ -2859,15 +2881,12 @@ __global__ void k_zero(int64_t n, T* __restrict__ y, const int* __restrict__ ski
   if (i < n) y[i] = (T)0;
 }
 
-// y[0 .. n16) = 0 in 16-byte stores (grid-stride)
-__global__ void k_clear16(int64_t n16, uint4* __restrict__ y) {
-  const uint4 z = {0u, 0u, 0u, 0u};
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (int64_t)gridDim.x * blockDim.x)
-    y[i] = z;
-}
-
+// p[0] = v, p[1] = 0
 __global__ void k_set_int(int* __restrict__ p, int v) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *p = v;
+  if (threadIdx.x == 0 && blockIdx.x == 0) {
+    p[0] = v;
+    p[1] = 0;
+  }
 }
 
 __global__ void k_fill(int64_t n, double v, double* __restrict__ y) {

@@ -59,3 +59,27 @@ def test_reductions_of_the_other_solvers(opt, nrhs):
 def test_rows_shared_by_four_waves(nrhs, precision):
     # 16^3 in 64 boxes: coarse rows of up to 16 tiles, a few dozen rows
     assert _steps(16, (4, 4, 4), nrhs, precision) <= BAR[precision]
+
+
+@pytest.mark.parametrize("n,parts", [(3, (1, 1, 1)), (4, (2, 1, 1)), (9, (2, 2, 2)), (14, (2, 1, 2))])
+@pytest.mark.parametrize("precision", ["fp64", "fp32_refine"])
+def test_factorisation_levels(n, parts, precision):
+    # one block without interface or corners; no corners; several levels with
+    # corner rows; blocks of 30 and more tile rows; then new materials on the
+    # same context (the work lists are kept, the zero pattern may change)
+    from paper_2204_13254_amd.solver import DDSolver
+    c, t, _ = cube_mesh(n)
+    p = box_partition(n, parts)
+    dt = 0.4 / n
+    rng = np.random.default_rng(n)
+    s = DDSolver(c, t, p, np.ones(len(t)), dt=dt, nrhs=2, precision=precision,
+                 cg_tol=1e-13 if precision == "fp64" else 1e-6)
+    for eps in (np.ones(len(t)), rng.uniform(1, 4, len(t)), np.ones(len(t))):
+        s.set_eps(eps)
+        s.factor()
+        o = NewmarkOracle(c, t, eps=eps, dt=dt)
+        J = dense_random_source(o.d.n_e, ~o.d.pec, 1, dt, dt, dt, seed=2, nrhs=2)
+        want = o.run(J)[1]
+        z = torch.zeros((2, s.n_edges), dtype=torch.float64, device="cuda")
+        got = s.step(torch.tensor(J[0], device="cuda"), z, z, z.clone()).cpu().numpy()
+        assert np.linalg.norm(got - want) <= BAR[precision] * np.linalg.norm(want)
