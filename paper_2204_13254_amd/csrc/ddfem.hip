@@ -320,6 +320,8 @@ struct Ctx {
   double* d_p2 = nullptr;  // p of odd CG iterations (even ones use d_p)
   double* d_z = nullptr;   // preconditioned residual
   double* d_partial2 = nullptr;  // second partial-sum array (r.r next to r.z)
+  double* d_partial3 = nullptr;  // third one, and r of odd iterations (short form of the iteration)
+  double* d_res2 = nullptr;
   // lumped preconditioner K_lam (CSR in multiplier space) and its pull list
   int64_t lam_nnz = 0;
   int64_t *d_lrp = nullptr, *d_lgptr = nullptr;
@@ -576,6 +578,21 @@ static void make_sym_list(Ctx& C, int pw, size_t wsz) {
   HIPCHK(hipMemsetAsync(p, 0, kTile * wsz, C.st));
   C.sym.zero = p;
 }
+
+// Right-hand sides per lane in the vector forms of the multiplier-space
+// kernels (k_*_v): 4 when nrhs is a multiple of 4, else 2 when even, else
+// the scalar forms.
+static int vec_width(int nr) { return nr % 4 == 0 ? 4 : (nr % 2 == 0 ? 2 : 1); }
+
+// Workgroups of a reduction over n rows [n][nrhs] with w right-hand sides to a
+// lane: one row to a lane while that takes fewer than kDotBlocks (a small
+// problem's reduction is bound by the chain over the block partials, not by
+// its rows; all kernels that share a partial buffer use the same count).
+static int dot_blocks(int64_t n, int nrhs, int w) {
+  const int lpr = 256 / (nrhs / w);
+  return (int)std::max<int64_t>(1, std::min<int64_t>(kDotBlocks, (n + lpr - 1) / lpr));
+}
+static int dot_blocks(const Ctx& C, int64_t n) { return dot_blocks(n, C.nrhs, vec_width(C.nrhs)); }
 
 // Symbolic factorisation of block s from the positions of its assembled
 // entries (lower triangle, tile store positions): on single rows, since a tile
@@ -1130,7 +1147,11 @@ static void build_device(Ctx& C, const double* coords) {
   C.d_p2 = dalloc<double>(nl, C.owned);
   C.d_z = dalloc<double>(nl, C.owned);
   C.d_partial2 = dalloc<double>(kDotBlocks * kMaxRhs, C.owned);
-  C.d_cg = dalloc<CgState>(1, C.owned);
+  if (dot_blocks(C, C.nlam) <= kShortBlocks) {
+    C.d_partial3 = dalloc<double>(kDotBlocks * kMaxRhs, C.owned);
+    C.d_res2 = dalloc<double>(nl, C.owned);
+  }
+  C.d_cg = dalloc<CgState>(2, C.owned);
   HIPCHK(hipHostMalloc((void**)&C.h_cg, sizeof(CgState), hipHostMallocDefault));
   HIPCHK(hipHostMalloc((void**)&C.h_partial, sizeof(double) * kDotBlocks * kMaxRhs, hipHostMallocDefault));
   C.d_rs = dalloc<RefineState>(1, C.owned);
@@ -1718,13 +1739,13 @@ static void mv_launch(Ctx& C, hipStream_t s, const Items& it, bool trans, const 
     if constexpr (CLS == DD_PROF_CORNER) {
       if (crow) {
         gathered = true;
-        hipLaunchKernelGGL((k_tile_mv<T, NV, NB16, CLS, LD, true>), dim3((unsigned)grid), dim3(256), 0, s, it.n, it.d,
+        hipLaunchKernelGGL((k_tile_mv<T, NV, NB16, CLS, LD, kInCoarse>), dim3((unsigned)grid), dim3(256), 0, s, it.n, it.d,
                            C.d_subs, tiles, (const T*)in, (T*)out, (const T*)add, alpha, (const T*)add_c, alpha_c,
                            C.nrhs, (int)trans, partial, (const int32_t*)it.mlist, skip, (const T*)C.d_zero_tile, crow);
       }
     }
     if (!gathered)
-      hipLaunchKernelGGL((k_tile_mv<T, NV, NB16, CLS, LD, false>), dim3((unsigned)grid), dim3(256), 0, s, it.n, it.d,
+      hipLaunchKernelGGL((k_tile_mv<T, NV, NB16, CLS, LD, kInRows>), dim3((unsigned)grid), dim3(256), 0, s, it.n, it.d,
                          C.d_subs, tiles, (const T*)in, (T*)out, (const T*)add, alpha, (const T*)add_c, alpha_c,
                          C.nrhs, (int)trans, partial, (const int32_t*)it.mlist, skip, (const T*)C.d_zero_tile,
                          (const int32_t*)nullptr);
@@ -1778,21 +1799,6 @@ static void mv(Ctx& C, const Items& it, bool trans, const void* in, void* out, c
 
 // fork: work queued on st so far is visible to the side stream; join: the
 // side stream's work is visible to everything queued on st afterwards
-// Right-hand sides per lane in the vector forms of the multiplier-space
-// kernels (k_*_v): 4 when nrhs is a multiple of 4, else 2 when even, else
-// the scalar forms.
-static int vec_width(int nr) { return nr % 4 == 0 ? 4 : (nr % 2 == 0 ? 2 : 1); }
-
-// Workgroups of a reduction over n rows [n][nrhs] with w right-hand sides to a
-// lane: one row to a lane while that takes fewer than kDotBlocks (a small
-// problem's reduction is bound by the chain over the block partials, not by
-// its rows; all kernels that share a partial buffer use the same count).
-static int dot_blocks(int64_t n, int nrhs, int w) {
-  const int lpr = 256 / (nrhs / w);
-  return (int)std::max<int64_t>(1, std::min<int64_t>(kDotBlocks, (n + lpr - 1) / lpr));
-}
-static int dot_blocks(const Ctx& C, int64_t n) { return dot_blocks(n, C.nrhs, vec_width(C.nrhs)); }
-
 // per-RHS block partials of x . y over n rows [n][nrhs] (dot_blocks blocks)
 static void dot_partial(Ctx& C, hipStream_t st, int64_t n, const double* x, const double* y, double* partial,
                         const int* skip) {
@@ -2341,7 +2347,10 @@ static int dd_solve_once(Ctx& C, const double* b, double* x, Ctx::Warm* warm, in
     // v = B_s^T p for the first F application, padding rows zeroed (later
     // ones are written by k_cg_p_scatter, which leaves padding rows alone)
     lambda_gather<T>(C, C.n_grow, C.d_glam, (const double*)C.d_p, (T*)X[5], gate);
-    const int* done = &C.d_cg->done;
+    // short form of the iteration (k_cg_rz, k_cg_pv): its state and r alternate,
+    // iteration k reading copy k & 1
+    const bool brief = pre && C.d_res2;
+    auto state_at = [&](int k) { return C.d_cg + (brief ? k & 1 : 0); };
     int it = 0;
     // an even block of iterations, so that every replay starts on p = d_p
     const int chk = std::max(2, (C.opt.check_every + 1) / 2 * 2);
@@ -2353,7 +2362,29 @@ static int dd_solve_once(Ctx& C, const double* b, double* x, Ctx::Warm* warm, in
     auto iteration = [&](int k) {
       double* pc = (k & 1) ? C.d_p2 : C.d_p;
       double* pn = (k & 1) ? C.d_p : C.d_p2;
+      CgState *cs = state_at(k), *cn = state_at(k + 1);
+      const int* done = &cs->done;
       apply_F<T>(C, pc, C.d_Fp, done, true, true);
+      if (brief) {
+        double *rc = (k & 1) ? C.d_res2 : C.d_res, *rn = (k & 1) ? C.d_res : C.d_res2;
+#define DD_SHORT(V)                                                                                                 \
+  do {                                                                                                              \
+    hipLaunchKernelGGL((k_cg_rz<V>), dim3(nb), dim3(256), 0, st, C.nlam, nb, C.d_lrp, C.d_lci, C.d_lvals,           \
+                       (const double*)rc, rn, (const double*)pc, (const double*)C.d_Fp, C.d_lam, C.d_z, nr,         \
+                       (const double*)C.d_partial, C.d_partial2, C.d_partial3, (const CgState*)cs, cn);             \
+    hipLaunchKernelGGL((k_cg_pv<T, V>), dim3(nb), dim3(256), 0, st, C.nlam, nb, C.d_lrow0, C.d_lrow1, nr,           \
+                       (const double*)C.d_partial2, (const double*)C.d_partial3, C.opt.cg_tol,                      \
+                       (const double*)C.d_z, (const double*)pc, pn, (T*)X[5], (const CgState*)cs, cn);              \
+  } while (0)
+        if (vec_width(nr) == 4)
+          DD_SHORT(4);
+        else if (vec_width(nr) == 2)
+          DD_SHORT(2);
+        else
+          DD_SHORT(1);
+#undef DD_SHORT
+        return;
+      }
       hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, st, 1, nr, nb, (const double*)C.d_partial,
                          (const double*)nullptr, C.d_cg, C.opt.cg_tol, (const int*)nullptr);
       if (pre) {
@@ -2392,7 +2423,8 @@ static int dd_solve_once(Ctx& C, const double* b, double* x, Ctx::Warm* warm, in
     // captured step: a fixed number of iterations, the state snapshotted
     if (captured) {
       for (int k = 0; k < fixed_iters; ++k) iteration(k);
-      hipLaunchKernelGGL(k_cg_snapshot, dim3(1), dim3(64), 0, st, slot, nr, (const CgState*)C.d_cg, C.d_rs, gate);
+      hipLaunchKernelGGL(k_cg_snapshot, dim3(1), dim3(64), 0, st, slot, nr, (const CgState*)state_at(fixed_iters), C.d_rs,
+                         gate);
       converged = true;
       have_state = true;
     }
@@ -2421,7 +2453,7 @@ static int dd_solve_once(Ctx& C, const double* b, double* x, Ctx::Warm* warm, in
       it += todo;
       HIPCHK(hipGetLastError());
       // the whole state, so that the last check also serves the report
-      HIPCHK(hipMemcpyAsync(C.h_cg, C.d_cg, sizeof(CgState), hipMemcpyDeviceToHost, st));
+      HIPCHK(hipMemcpyAsync(C.h_cg, state_at(it), sizeof(CgState), hipMemcpyDeviceToHost, st));
       HIPCHK(hipStreamSynchronize(st));
       have_state = true;
       converged = C.h_cg->done != 0;

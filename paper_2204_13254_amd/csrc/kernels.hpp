@@ -676,8 +676,10 @@ constexpr int32_t kPairMask = (1 << 21) - 1;
 // --------------------------------------------------------------------------
 template <class T, int V>
 __device__ __forceinline__ void vload(const T* __restrict__ p, T (&o)[V]) {
-  static_assert(V == 2 || V == 4, "vector width");
-  if constexpr (sizeof(T) == 4 && V == 4) {
+  static_assert(V == 1 || V == 2 || V == 4, "vector width");
+  if constexpr (V == 1) {
+    o[0] = *p;
+  } else if constexpr (sizeof(T) == 4 && V == 4) {
     const float4 t = *reinterpret_cast<const float4*>(p);
     o[0] = t.x; o[1] = t.y; o[2] = t.z; o[3] = t.w;
   } else if constexpr (sizeof(T) == 4) {
@@ -694,8 +696,10 @@ __device__ __forceinline__ void vload(const T* __restrict__ p, T (&o)[V]) {
 
 template <class T, int V>
 __device__ __forceinline__ void vstore(T* __restrict__ p, const T (&o)[V]) {
-  static_assert(V == 2 || V == 4, "vector width");
-  if constexpr (sizeof(T) == 4 && V == 4) {
+  static_assert(V == 1 || V == 2 || V == 4, "vector width");
+  if constexpr (V == 1) {
+    *p = o[0];
+  } else if constexpr (sizeof(T) == 4 && V == 4) {
     *reinterpret_cast<float4*>(p) = make_float4(o[0], o[1], o[2], o[3]);
   } else if constexpr (sizeof(T) == 4) {
     *reinterpret_cast<float2*>(p) = make_float2(o[0], o[1]);
@@ -747,15 +751,21 @@ struct MvOut {
   int32_t s, o, slot0, nslot;
 };
 
+// How a product reads its input block: kInRows the block's own rows of `in`;
+// kInCoarse row x of the subdomain is row crow[x] of `in` (-1: zero), the corner
+// rows read through B_c straight from the coarse solution, without a copy per
+// subdomain.  (The other way, sums over the corner rows of the subdomains while
+// the coarse forward pass reads its input, was slower than a gather kernel
+// before it: 17.8 us a pass against 4.7 + 6.7 at 24^3, 1 RHS.)
+enum { kInRows = 0, kInCoarse = 1 };
+
 // Sum over the tiles k = lo, lo + step, ... < hi of one output block's range by
 // one wave.  NV > 0: vector path for nrhs <= NV, vacc[mb NV + r]; NV == 0:
-// MFMA path with NB16 RHS blocks, macc[mb NB16 + nb].  GZ: input row x of the
-// subdomain is row crow[x] of `in` (-1: zero): the corner rows read through
-// B_c straight from the coarse solution, without a copy per subdomain.
+// MFMA path with NB16 RHS blocks, macc[mb NB16 + nb].
 // NS: separate MFMA sums, one to a ring slot, added at the end (three where the
 // form also serves 3..8 RHS: one chain over a row's tiles had up to twice the
 // rounding error of the four lane groups of a vector product).
-template <class T, int NV, int NB16, int NS, bool GZ>
+template <class T, int NV, int NB16, int NS, int IN>
 __device__ __forceinline__ void mv_range(const SubDev& q, const T* __restrict__ tiles, const T* __restrict__ in,
                                          int nrhs, int trans, int o, int lo, int hi, int step,
                                          const int32_t* __restrict__ mlist, const T* __restrict__ zero,
@@ -764,14 +774,17 @@ __device__ __forceinline__ void mv_range(const SubDev& q, const T* __restrict__ 
                                          T (&vacc)[NV ? 2 * NV : 1]) {
   const int l = threadIdx.x & 63;
   const int g = l >> 4, i = l & 15;
-  const T* xbase = GZ ? in : in + q.row_off * nrhs;
+  const T* xbase = IN == kInRows ? in + q.row_off * nrhs : in;
   constexpr bool MF = NV == 0;
-  typename Mfma<T>::acc_t ms[NS][MF ? 2 * NB16 : 1];
+  typename Mfma<T>::acc_t more[NS > 1 ? NS - 1 : 1][MF ? 2 * NB16 : 1];  // sums of ring slots 1 ..
   if constexpr (MF) {
 #pragma unroll
-    for (int u = 0; u < NS; ++u)
+    for (int a = 0; a < 2 * NB16; ++a) {
+      macc[a] = typename Mfma<T>::acc_t{0, 0, 0, 0};
+      if constexpr (NS > 1)
 #pragma unroll
-      for (int a = 0; a < 2 * NB16; ++a) ms[u][a] = typename Mfma<T>::acc_t{0, 0, 0, 0};
+        for (int u = 0; u < NS - 1; ++u) more[u][a] = typename Mfma<T>::acc_t{0, 0, 0, 0};
+    }
   } else {
 #pragma unroll
     for (int a = 0; a < 2 * NV; ++a) vacc[a] = 0;
@@ -786,7 +799,7 @@ __device__ __forceinline__ void mv_range(const SubDev& q, const T* __restrict__ 
   // for every load in flight.
   auto load_x = [&](int m, T* xv) {
     int32_t cr[8];
-    if constexpr (GZ) {
+    if constexpr (IN == kInCoarse) {
       const int4* cp = reinterpret_cast<const int4*>(crow + q.row_off + (int64_t)m * kNB + 8 * g);
       const int4 c0 = cp[0], c1 = cp[1];
       cr[0] = c0.x; cr[1] = c0.y; cr[2] = c0.z; cr[3] = c0.w;
@@ -806,7 +819,7 @@ __device__ __forceinline__ void mv_range(const SubDev& q, const T* __restrict__ 
 #pragma unroll
       for (int ks = 0; ks < 8; ++ks) {
         T v;
-        if constexpr (GZ) {
+        if constexpr (IN == kInCoarse) {
           v = xbase[(int64_t)(cr[ks] >= 0 ? cr[ks] : 0) * nrhs + cc];
           v = cr[ks] >= 0 ? v : (T)0;
         } else {
@@ -837,8 +850,10 @@ __device__ __forceinline__ void mv_range(const SubDev& q, const T* __restrict__ 
       for (int nb = 0; nb < NB16; ++nb)
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) {
-          ms[u % NS][nb] = Mfma<T>::op(rb[u][ks], rx[u][nb * 8 + ks], ms[u % NS][nb]);
-          ms[u % NS][NB16 + nb] = Mfma<T>::op(rb[u][8 + ks], rx[u][nb * 8 + ks], ms[u % NS][NB16 + nb]);
+          auto& s0 = u % NS ? more[u % NS - 1][nb] : macc[nb];
+          auto& s1 = u % NS ? more[u % NS - 1][NB16 + nb] : macc[NB16 + nb];
+          s0 = Mfma<T>::op(rb[u][ks], rx[u][nb * 8 + ks], s0);
+          s1 = Mfma<T>::op(rb[u][8 + ks], rx[u][nb * 8 + ks], s1);
         }
     } else {
 #pragma unroll
@@ -863,9 +878,9 @@ __device__ __forceinline__ void mv_range(const SubDev& q, const T* __restrict__ 
   if constexpr (MF) {
 #pragma unroll
     for (int a = 0; a < 2 * NB16; ++a) {
-      macc[a] = ms[0][a];
+      if constexpr (NS > 1)
 #pragma unroll
-      for (int u = 1; u < NS; ++u) macc[a] += ms[u][a];
+        for (int u = 0; u < NS - 1; ++u) macc[a] += more[u][a];
     }
   } else {
     // the four lane groups hold the column quarters of a row
@@ -886,7 +901,7 @@ constexpr int mv_sums() {
 
 // CLS only names the product class in kernel traces (1 interior blocks, 3
 // coarse, 4 corner rows, 5 couplings).
-template <class T, int NV, int NB16, int CLS, int LD, bool GZ>
+template <class T, int NV, int NB16, int CLS, int LD, int IN>
 __global__ void __launch_bounds__(256) k_tile_mv(int64_t n_items, const MvItem* __restrict__ items,
                                                  const SubDev* __restrict__ subs, const T* __restrict__ tiles,
                                                  const T* __restrict__ in, T* __restrict__ out,
@@ -914,7 +929,7 @@ __global__ void __launch_bounds__(256) k_tile_mv(int64_t n_items, const MvItem* 
     constexpr bool MF = NV == 0;
     typename Mfma<T>::acc_t macc[MF ? 2 * NB16 : 1];
     T vacc[MF ? 1 : 2 * NV];
-    mv_range<T, NV, NB16, mv_sums<NB16, LD>(), GZ>(q, tiles, in, nrhs, trans, w.o, w.lo, w.hi, 1, mlist, zero, crow, macc, vacc);
+    mv_range<T, NV, NB16, mv_sums<NB16, LD>(), IN>(q, tiles, in, nrhs, trans, w.o, w.lo, w.hi, 1, mlist, zero, crow, macc, vacc);
     // ---- epilogue ------------------------------------------------------------
     T* dst;
     const T* adp = nullptr;
@@ -993,7 +1008,8 @@ __global__ void __launch_bounds__(64 * kRowWaves) k_tile_mvw(const MvItem* __res
   const int l = threadIdx.x & 63, g = l >> 4, i = l & 15;
   typename Mfma<T>::acc_t macc[MF ? 2 * NB16 : 1];
   T vacc[MF ? 1 : 2 * NV];
-  mv_range<T, NV, NB16, mv_sums<NB16, LD>(), false>(q, tiles, in, nrhs, trans, w.o, w.lo + wv, w.hi, kRowWaves, mlist, zero, nullptr, macc, vacc);
+  mv_range<T, NV, NB16, mv_sums<NB16, LD>(), kInRows>(q, tiles, in, nrhs, trans, w.o, w.lo + wv, w.hi, kRowWaves,
+                                                       mlist, zero, nullptr, macc, vacc);
   const bool crow_out = w.o >= q.kI + q.kG;
   const T* ad = crow_out ? add_c : add;
   const T scale = crow_out ? alpha_c : alpha;
@@ -2487,6 +2503,7 @@ struct CgState {
   double alpha[kMaxRhs];
   double beta[kMaxRhs];
   int active[kMaxRhs];
+  int live[kMaxRhs];       // short form: active and without a breakdown in the iteration at hand
   int iters[kMaxRhs];
   int done;                // all right-hand sides converged (or broke down)
   int breakdown;
@@ -2850,6 +2867,187 @@ __global__ void k_cg_p_scatter_v(int64_t nlam, const int64_t* __restrict__ row0,
   vstore<double, V>(pnext + o, pn);
   vstore<T, V>(v + row0[l] * nrhs + q * V, yp);
   vstore<T, V>(v + row1[l] * nrhs + q * V, ym);
+}
+
+// --------------------------------------------------------------------------
+// Short form of a CG iteration's multiplier part, for problems whose
+// reductions take at most kShortBlocks workgroups: two kernels instead of five
+// (alpha; the updates; the preconditioner; beta; the new direction).  Such an
+// iteration is bound by its chain of launches, so every workgroup sums the
+// block partials itself (a few kilobytes) instead of waiting for a scalar
+// kernel, and the preconditioner takes r - alpha Fp at each of its columns
+// instead of waiting for the update.  The state alternates between two copies
+// (a workgroup reads st while workgroup 0 writes nxt), and so does r.  At 24^3,
+// 64 boxes, FP64, 1 RHS the five kernels take 20.4 us and four more gaps.
+// (A large problem keeps the five: there the second gather of the
+// preconditioner costs what the launches save, and 1024 partials are too many
+// to sum in every workgroup.)
+// --------------------------------------------------------------------------
+constexpr int kShortBlocks = 512;
+
+// sum over nb block partials of right-hand side threadIdx.x (< nrhs)
+__device__ __forceinline__ double short_total(const double* __restrict__ pa, int nb, int nrhs, double* red) {
+  const int t = threadIdx.x, lpr = min(256 / nrhs, nb), rr = t % nrhs, ln = t / nrhs;
+  double a = 0.0;
+  if (ln < lpr) {
+#pragma unroll 4
+    for (int b = ln; b < nb; b += lpr) a += pa[b * kMaxRhs + rr];
+  }
+  red[t] = a;
+  return lane_sum<256>(red, lpr, nrhs);
+}
+
+// alpha = r.z / p.Fp; lambda += alpha p; r' = r - alpha Fp; z = K_lam r', with
+// the block partials of r'.z and r'.r'.  One row to a lane group (G = nrhs / V
+// lanes), nb workgroups.  Workgroup 0 leaves alpha and the breakdown flags in
+// nxt.
+template <int V>
+__global__ void __launch_bounds__(256) k_cg_rz(int64_t nlam, int nb, const int64_t* __restrict__ rp,
+                                               const int32_t* __restrict__ ci, const double* __restrict__ val,
+                                               const double* __restrict__ res, double* __restrict__ resn,
+                                               const double* __restrict__ p, const double* __restrict__ Fp,
+                                               double* __restrict__ lam, double* __restrict__ z, int nrhs,
+                                               const double* __restrict__ part_pq, double* __restrict__ part_rz,
+                                               double* __restrict__ part_rr, const CgState* __restrict__ st,
+                                               CgState* __restrict__ nxt) {
+  if (st->done) return;
+  __shared__ double red[256];
+  __shared__ double al[kMaxRhs];
+  __shared__ int broke;
+  const int tid = threadIdx.x;
+  if (tid == 0) broke = 0;
+  const double s = short_total(part_pq, nb, nrhs, red);
+  if (tid < nrhs) {
+    const bool act = st->active[tid] != 0, bad = act && (!(s > 0.0) || !isfinite(s));
+    al[tid] = act && !bad ? st->rz[tid] / s : 0.0;
+    if (bad) atomicOr(&broke, 1);
+    if (blockIdx.x == 0) {
+      nxt->alpha[tid] = al[tid];
+      nxt->live[tid] = act && !bad;
+    }
+  }
+  __syncthreads();
+  if (blockIdx.x == 0 && tid == 0) nxt->breakdown = st->breakdown | broke;
+  const int G = nrhs / V, lpr = 256 / G, q = tid % G, lane = tid / G;
+  const int64_t l = (int64_t)blockIdx.x * lpr + lane;
+  double sz[V], sr[V];
+#pragma unroll
+  for (int v = 0; v < V; ++v) sz[v] = sr[v] = 0.0;
+  if (lane < lpr && l < nlam) {
+    double a[V], rv[V], fv[V], pv[V], lv[V], acc[V];
+    const int64_t o = l * nrhs + q * V;
+    const int64_t k0 = rp[l], k1 = rp[l + 1];
+    vload<double, V>(res + o, rv);
+    vload<double, V>(Fp + o, fv);
+    vload<double, V>(p + o, pv);
+    vload<double, V>(lam + o, lv);
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      a[v] = al[q * V + v];
+      rv[v] -= a[v] * fv[v];
+      lv[v] += a[v] * pv[v];
+      acc[v] = 0.0;
+    }
+    vstore<double, V>(resn + o, rv);
+    vstore<double, V>(lam + o, lv);
+    constexpr int KB = 4;  // nonzeros in flight (reads past the row are clamped and not used)
+    for (int64_t k = k0; k < k1; k += KB) {
+      int32_t c[KB];
+      double w[KB], x[KB][V], f[KB][V];
+#pragma unroll
+      for (int u = 0; u < KB; ++u) {
+        const int64_t kc = k + u < k1 ? k + u : k0;
+        c[u] = ci[kc];
+        w[u] = val[kc];
+      }
+#pragma unroll
+      for (int u = 0; u < KB; ++u) {
+        vload<double, V>(res + (int64_t)c[u] * nrhs + q * V, x[u]);
+        vload<double, V>(Fp + (int64_t)c[u] * nrhs + q * V, f[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < KB; ++u) {
+        const double wv = k + u < k1 ? w[u] : 0.0;
+#pragma unroll
+        for (int v = 0; v < V; ++v) acc[v] += wv * (x[u][v] - a[v] * f[u][v]);
+      }
+    }
+    vstore<double, V>(z + o, acc);
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      sz[v] = rv[v] * acc[v];
+      sr[v] = rv[v] * rv[v];
+    }
+  }
+  block_rhs_sum_v<V>(sz, nrhs, lpr, part_rz);
+  block_rhs_sum_v<V>(sr, nrhs, lpr, part_rr);
+}
+
+// beta = r'.z / r.z and the convergence test of every right-hand side; p' = z +
+// beta p for those still active (p kept otherwise) and v = B_s^T p' on its two
+// interface rows, as in k_cg_p_scatter.  Workgroup 0 completes nxt.
+template <class T, int V>
+__global__ void __launch_bounds__(256) k_cg_pv(int64_t nlam, int nb, const int64_t* __restrict__ row0,
+                                               const int64_t* __restrict__ row1, int nrhs,
+                                               const double* __restrict__ part_rz,
+                                               const double* __restrict__ part_rr, double tol,
+                                               const double* __restrict__ z, const double* __restrict__ pcur,
+                                               double* __restrict__ pnext, T* __restrict__ vout,
+                                               const CgState* __restrict__ st, CgState* __restrict__ nxt) {
+  const int tid = threadIdx.x;
+  if (st->done) {
+    if (blockIdx.x == 0) {
+      const int* a = reinterpret_cast<const int*>(st);
+      int* b = reinterpret_cast<int*>(nxt);
+      for (int k = tid; k < (int)(sizeof(CgState) / sizeof(int)); k += 256) b[k] = a[k];
+    }
+    return;
+  }
+  __shared__ double red[256];
+  __shared__ double be[kMaxRhs];
+  __shared__ int act[kMaxRhs];
+  __shared__ int any;
+  if (tid == 0) any = 0;
+  const double sz = short_total(part_rz, nb, nrhs, red);
+  const double sr = short_total(part_rr, nb, nrhs, red);
+  if (tid < nrhs) {
+    const bool live = nxt->live[tid] != 0;
+    const double rz0 = st->rz[tid], rr0 = st->rr0[tid];
+    const double b = live ? sz / rz0 : 0.0;
+    const int on = live && !(sr <= tol * tol * rr0);
+    be[tid] = b;
+    act[tid] = on;
+    if (on) atomicOr(&any, 1);
+    if (blockIdx.x == 0) {
+      nxt->rr[tid] = live ? sr : st->rr[tid];
+      nxt->rz[tid] = live ? sz : rz0;
+      nxt->rr0[tid] = rr0;
+      nxt->beta[tid] = b;
+      nxt->active[tid] = on;
+      nxt->iters[tid] = st->iters[tid] + (live ? 1 : 0);
+    }
+  }
+  __syncthreads();
+  if (blockIdx.x == 0 && tid == 0) nxt->done = any ? 0 : 1;
+  if (!any) return;
+  const int G = nrhs / V, lpr = 256 / G, q = tid % G, lane = tid / G;
+  const int64_t l = (int64_t)blockIdx.x * lpr + lane;
+  if (lane >= lpr || l >= nlam) return;
+  const int64_t o = l * nrhs + q * V;
+  double bv[V], pc[V], pn[V];
+  vload<double, V>(z + o, bv);
+  vload<double, V>(pcur + o, pc);
+  T yp[V], ym[V];
+#pragma unroll
+  for (int u = 0; u < V; ++u) {
+    const int r = q * V + u;
+    pn[u] = act[r] ? bv[u] + be[r] * pc[u] : pc[u];
+    yp[u] = (T)pn[u];
+    ym[u] = (T)(-pn[u]);
+  }
+  vstore<double, V>(pnext + o, pn);
+  vstore<T, V>(vout + row0[l] * nrhs + q * V, yp);
+  vstore<T, V>(vout + row1[l] * nrhs + q * V, ym);
 }
 
 __global__ void k_extrap(int64_t n, const double* __restrict__ a, const double* __restrict__ b,

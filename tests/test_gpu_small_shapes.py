@@ -83,3 +83,11 @@ def test_factorisation_levels(n, parts, precision):
         z = torch.zeros((2, s.n_edges), dtype=torch.float64, device="cuda")
         got = s.step(torch.tensor(J[0], device="cuda"), z, z, z.clone()).cpu().numpy()
         assert np.linalg.norm(got - want) <= BAR[precision] * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("n,parts,nrhs", [(12, 3, 1), (12, 3, 2), (12, 3, 31), (20, 4, 16), (20, 4, 19)])
+@pytest.mark.parametrize("precision", ["fp64", "fp32_refine"])
+def test_iteration_short_and_long(n, parts, nrhs, precision):
+    # 324 workgroups in a reduction at 12^3 and 31 RHS, 170 at 20^3 and 16 RHS:
+    # the short form; more than 512 at 19 RHS: the long one
+    assert _steps(n, (parts,) * 3, nrhs, precision) <= BAR[precision]
