@@ -98,7 +98,18 @@ struct Items {
   bool pair = false;         // row-pair items (k_tile_mv2)
   bool oct = false;          // row-octet workgroup items (k_tile_mv8)
   bool rows4 = false;        // one workgroup of kRowWaves waves per item (k_tile_mvw)
+  const void* square = nullptr;  // tiles of a square store (else the factor stores)
 };
+
+// Most tile rows of a coarse block that is solved through K_cc^-1 itself.  The
+// inverse is dense, while the inverse factor keeps 31% of its tiles at 64^3 (486
+// rows), but two passes of a small block are all latency: at 24^3, 64 boxes, FP64
+// (21 rows) 6.7 + 6.1 us and a gap, the one pass 7.3 us.  A step with two passes
+// and with one, us: 21 rows, FP64, 1 RHS 1142 -> 1065, FP32, 16 RHS 1480 -> 1409;
+// 45 rows 1460 -> 1388 and 2144 -> 2034; 54 rows 2305 -> 2261 and 3105 -> 3001;
+// from 32 RHS 1407 -> 1355 (6 rows) to 4712 -> 4588 (54 rows).  Beyond 64 rows the
+// dense rows are longer than a row group's rule allows.
+constexpr int kSquareCoarse = 64;
 
 // Work-list shapes (longest tile range of one wave per product class, and
 // the length buckets of the full passes).  Defaults measured on the 64^3
@@ -294,6 +305,9 @@ struct Ctx {
   // inverse factor; corner_N / corner_T: Psi_Gamma u on the corner rows /
   // Psi_Gamma^T z onto the interface rows
   Items full_N, full_T, cross_N, cross_T, co_N, co_T, corner_N, corner_T;
+  // K_cc^-1 of a coarse block of at most kSquareCoarse tile rows (its own store)
+  Items co_inv;
+  void* d_kinv = nullptr;
   // symmetric product M u (panel pairs, partial slots, fixed-order reduce)
   struct SymList {
     SymItem* d = nullptr;
@@ -1114,6 +1128,15 @@ static void build_device(Ctx& C, const double* coords) {
     C.corner_T = make_items(C, cT, C.tuning.chunk, false, 1, true);
     C.co_N = make_items(C, oN, C.tuning.chunk);
     C.co_T = make_items(C, oT, C.tuning.chunk);
+    if (C.Kc > 0 && C.Kc <= kSquareCoarse) {
+      std::vector<MvItem> sq;
+      for (int o = 0; o < C.Kc; ++o) sq.push_back({nsub, o, 0, C.Kc, -1, 0});
+      C.co_inv = make_items(C, sq, kSquareCoarse);
+      void* p = nullptr;
+      HIPCHK(hipMalloc(&p, (size_t)C.Kc * C.Kc * kTile * wsz));
+      C.owned.push_back(p);
+      C.co_inv.square = C.d_kinv = p;
+    }
     C.blk_corner_N.swap(cN);
     C.blk_corner_T.swap(cT);
     void* p = nullptr;
@@ -1589,6 +1612,9 @@ static void factor_sequence(Ctx& C, hipStream_t st, hipStream_t side) {
       hipLaunchKernelGGL(k_pull_coarse<T>, dim3(nblk(C.n_cent)), dim3(256), 0, side, C.n_cent, C.d_cptr,
                          C.d_csrc, C.d_cdest, tiles);
     factor_blocks<T>(C, C.fac_coarse, side);
+    if (C.d_kinv)
+      hipLaunchKernelGGL(k_coarse_inv<T>, dim3(C.Kc, C.Kc), dim3(256), chain_lds(C.Kc), side, C.nsub,
+                         (const T*)C.d_tilesT, C.d_subs, (T*)C.d_kinv, (const uint8_t*)C.d_nzi);
     pack_blocks<T>(C, C.fac_coarse, side);
   }
   if (C.n_psi)
@@ -1706,7 +1732,8 @@ template <class T, int NV, int NB16, int CLS, int LD>
 static void mv_launch(Ctx& C, hipStream_t s, const Items& it, bool trans, const void* in, void* out, const void* add,
                       T alpha, const void* add_c, T alpha_c, const int* skip, const int32_t* crow) {
   const bool split = it.n_out > 0;
-  const T* tiles = (const T*)(trans ? C.d_tilesT : C.d_tiles);
+  const T* tiles = (const T*)(it.square ? it.square : trans ? C.d_tilesT : C.d_tiles);
+  const int tr = it.square ? 2 : (int)trans;
   T* partial = (T*)(it.partial ? it.partial : C.d_partial_mv);
   // work groups come in multiples of 8 (one per XCD); a persistent grid is
   // a multiple of 8 too, so each workgroup stays on its groups' XCD
@@ -1719,19 +1746,19 @@ static void mv_launch(Ctx& C, hipStream_t s, const Items& it, bool trans, const 
       if (C.tuning.full_persist > 0) g8 = std::min<int64_t>(g8, C.tuning.full_persist);
       hipLaunchKernelGGL((k_tile_mv8<T, NB16, CLS, LD>), dim3((unsigned)g8), dim3(256), 0, s, it.n, it.d, C.d_subs,
                          tiles, (const T*)in, (T*)out, (const T*)add, alpha, (const T*)add_c, alpha_c, C.nrhs,
-                         (int)trans, (const int32_t*)it.mlist, skip, (const T*)C.d_zero_tile);
+                         tr, (const int32_t*)it.mlist, skip, (const T*)C.d_zero_tile);
       return;
     }
     if (it.pair) {
       hipLaunchKernelGGL((k_tile_mv2<T, NB16, CLS, LD>), dim3((unsigned)grid), dim3(256), 0, s, it.n, it.d, C.d_subs,
                          tiles, (const T*)in, (T*)out, (const T*)add, alpha, (const T*)add_c, alpha_c, C.nrhs,
-                         (int)trans, partial, (const int32_t*)it.mlist, skip, (const T*)C.d_zero_tile);
+                         tr, partial, (const int32_t*)it.mlist, skip, (const T*)C.d_zero_tile);
     }
   }
   if (it.rows4) {
     hipLaunchKernelGGL((k_tile_mvw<T, NV, NB16, CLS, LD>), dim3((unsigned)it.n), dim3(64 * kRowWaves), 0, s, it.d,
                        C.d_subs, tiles, (const T*)in, (T*)out, (const T*)add, alpha, (const T*)add_c, alpha_c, C.nrhs,
-                       (int)trans, (const int32_t*)it.mlist, skip, (const T*)C.d_zero_tile);
+                       tr, (const int32_t*)it.mlist, skip, (const T*)C.d_zero_tile);
     return;
   }
   if (!it.pair) {
@@ -1741,13 +1768,13 @@ static void mv_launch(Ctx& C, hipStream_t s, const Items& it, bool trans, const 
         gathered = true;
         hipLaunchKernelGGL((k_tile_mv<T, NV, NB16, CLS, LD, kInCoarse>), dim3((unsigned)grid), dim3(256), 0, s, it.n, it.d,
                            C.d_subs, tiles, (const T*)in, (T*)out, (const T*)add, alpha, (const T*)add_c, alpha_c,
-                           C.nrhs, (int)trans, partial, (const int32_t*)it.mlist, skip, (const T*)C.d_zero_tile, crow);
+                           C.nrhs, tr, partial, (const int32_t*)it.mlist, skip, (const T*)C.d_zero_tile, crow);
       }
     }
     if (!gathered)
       hipLaunchKernelGGL((k_tile_mv<T, NV, NB16, CLS, LD, kInRows>), dim3((unsigned)grid), dim3(256), 0, s, it.n, it.d,
                          C.d_subs, tiles, (const T*)in, (T*)out, (const T*)add, alpha, (const T*)add_c, alpha_c,
-                         C.nrhs, (int)trans, partial, (const int32_t*)it.mlist, skip, (const T*)C.d_zero_tile,
+                         C.nrhs, tr, partial, (const int32_t*)it.mlist, skip, (const T*)C.d_zero_tile,
                          (const int32_t*)nullptr);
   }
   if (split)
@@ -1954,10 +1981,15 @@ static void symv(Ctx& C, const void* in, void* out, const int* skip, bool side) 
   symv_reduce<T>(C, out, nullptr, skip, s);
 }
 
-// coarse: y rows of Xin (coarse block) -> Xout coarse rows = K_cc^-1 y via
-// Linv then Linv^T (tmp holds the intermediate)
+// coarse: y rows of Xin (coarse block) -> Xout coarse rows = K_cc^-1 y, a small
+// block in one product, else via Linv then Linv^T (tmp holds the intermediate);
+// Xout must not be Xin
 template <class T>
 static void coarse_solve(Ctx& C, void* Xin, void* Xtmp, void* Xout, const int* skip) {
+  if (C.d_kinv) {
+    mv<T>(C, C.co_inv, false, Xin, Xout, nullptr, (T)1, skip);
+    return;
+  }
   mv<T>(C, C.co_N, false, Xin, Xtmp, nullptr, (T)1, skip);
   mv<T>(C, C.co_T, true, Xtmp, Xout, nullptr, (T)1, skip);
 }

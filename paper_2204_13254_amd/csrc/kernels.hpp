@@ -835,7 +835,7 @@ __device__ __forceinline__ void mv_range(const SubDev& q, const T* __restrict__ 
   auto ld = [&](int k, T* c, T* xv) {
     const int32_t e = mlist ? mlist[k] : k;
     const int m = e & kListMask, zq = (e >> 25) & 15, ch = g >> 1;
-    const T* tp = tiles + tile_index(q, trans ? m : o, trans ? o : m) * kTile;
+    const T* tp = tiles + (trans == 2 ? (int64_t)o * q.K + m : tile_index(q, trans ? m : o, trans ? o : m)) * kTile;
     load_chunk8(((zq >> ch) & 1) ? zero : tp, l, c);
     load_chunk8((((zq >> (2 + ch)) & 1) ? zero : tp) + 512, l, c + 8);
     load_x(m, xv);
@@ -1585,6 +1585,33 @@ __global__ void __launch_bounds__(256) k_schur_inv(int s0, const T* __restrict__
       },
       red, sum);
   T* d = msq + (m_off[sidx] + (int64_t)o * (o + 1) / 2 + m) * kTile;
+#pragma unroll
+  for (int u = 0; u < kTile / 256; ++u) d[threadIdx.x + 256 * u] = sum[u];
+}
+
+// K_cc^-1 = Linv_cc^T Linv_cc of a small coarse block as a square store (tile
+// (o, m) at o K + m, operand order): one product per coarse solve instead of
+// two that wait for each other.  One workgroup per tile, as k_schur_inv.
+template <class T>
+__global__ void __launch_bounds__(256) k_coarse_inv(int sidx, const T* __restrict__ inv,
+                                                    const SubDev* __restrict__ subs, T* __restrict__ out,
+                                                    const uint8_t* __restrict__ nzi) {
+  const SubDev q = subs[sidx];
+  const int o = (int)blockIdx.y, m = (int)blockIdx.x;
+  __shared__ T red[kChainLds];
+  __shared__ int wcnt[4];
+  extern __shared__ uint16_t list[];
+  const int nn = chain_list(
+      max(o, m), q.K, [&](int k) { return nzi[tile_index(q, k, o)] && nzi[tile_index(q, k, m)]; }, list, wcnt);
+  T sum[kTile / 256];
+  chain_rows<T, false>(
+      list, nn,
+      [&](int k, const T*& ap, const T*& bp) {
+        ap = inv + tile_index(q, k, o) * kTile;  // Linv_ko^T
+        bp = inv + tile_index(q, k, m) * kTile;  // Linv_km^T
+      },
+      red, sum);
+  T* d = out + ((int64_t)o * q.K + m) * kTile;
 #pragma unroll
   for (int u = 0; u < kTile / 256; ++u) d[threadIdx.x + 256 * u] = sum[u];
 }
