@@ -153,15 +153,16 @@ struct Ctx {
   // captured refined solve of a step (pre-solve, CG, recovery, residual
   // checks and gated sweeps; FP32 factors with refinement, first variant):
   // CG iterations per solve and sweeps it holds, the last step's needs
-  // (two of them, keyed by their buffers: the resident step alternates its
-  // output slots)
+  // (keyed by their buffers, least recently used first out: the resident step
+  // alternates its output slots, dd_solve, dd_step_mixed and dd_adjoint_step
+  // have buffers of their own)
   struct StepGraph {
     hipGraphExec_t g = nullptr;
     const double* b = nullptr;
     double *x = nullptr, *tx = nullptr, *sx = nullptr;
     int iters = 0, sweeps = 0;
     uint64_t used = 0;
-  } step_graphs[2];
+  } step_graphs[6];
   uint64_t step_clock = 0;
   // resident Newmark state of dd_step_resident, unknown-major [nint][nrhs]:
   // slot rs_p holds e^n, the other e^{n-1}, each with its products T e and
@@ -171,7 +172,13 @@ struct Ctx {
   double* rs_j = nullptr;
   int rs_p = 0;
   bool rs_alloc = false, rs_stale = false;
-  int need_iters = 0, need_sweeps = 0;
+  // per kind of call: CG iterations of its last two refined solves, sweeps of the last
+  struct Need {
+    int iters = 0, before = 0, sweeps = 0;
+  } need[4];
+  // iterations of the last two eager CG solves: the smaller one is launched
+  // before the first convergence check of the next
+  int cg_last[2] = {0, 0};
   RefineState* d_rs = nullptr;
   RefineState* h_rs = nullptr;   // pinned
   double* d_rpart = nullptr;     // partial sums of the refinement norms [kDotBlocks][kMaxRhs]
@@ -1642,7 +1649,8 @@ static int factor_impl(Ctx& C) {
   // solves are dropped, and the next step runs eagerly to size its capture
   HIPCHK(hipStreamSynchronize(st));
   drop_graphs(C);
-  C.need_iters = C.need_sweeps = 0;
+  for (auto& nd : C.need) nd = Ctx::Need{};
+  C.cg_last[0] = C.cg_last[1] = 0;
   HIPCHK(hipEventRecord(C.ev_fa, st));
   HIPCHK(hipStreamWaitEvent(C.fa, C.ev_fa, 0));
   factor_lists(C);
@@ -2264,17 +2272,27 @@ static int dp2_gmres(Ctx& C, int* iters, double* relres) {
   return all ? DD_OK : DD_ERR_NO_CONVERGENCE;
 }
 
-static void dot_to_host(Ctx& C, const double* x, const double* y, int64_t n, double* out) {
-  const int nb = dot_blocks(C, n);
+// x . y per RHS to the host: dot_start enqueues the block partials and their
+// copy, dot_finish adds them once the stream has passed it
+static void dot_start(Ctx& C, const double* x, const double* y, int64_t n) {
   dot_partial(C, C.st, n, x, y, C.d_partial, nullptr);
-  HIPCHK(hipMemcpyAsync(C.h_partial, C.d_partial, sizeof(double) * nb * kMaxRhs, hipMemcpyDeviceToHost,
+  HIPCHK(hipMemcpyAsync(C.h_partial, C.d_partial, sizeof(double) * dot_blocks(C, n) * kMaxRhs, hipMemcpyDeviceToHost,
                         C.st));
-  HIPCHK(hipStreamSynchronize(C.st));
+}
+
+static void dot_finish(Ctx& C, int64_t n, double* out) {
+  const int nb = dot_blocks(C, n);
   for (int r = 0; r < C.nrhs; ++r) {
     double s = 0.0;
     for (int b = 0; b < nb; ++b) s += C.h_partial[b * kMaxRhs + r];
     out[r] = s;
   }
+}
+
+static void dot_to_host(Ctx& C, const double* x, const double* y, int64_t n, double* out) {
+  dot_start(C, x, y, n);
+  HIPCHK(hipStreamSynchronize(C.st));
+  dot_finish(C, n, out);
 }
 
 // z = K_lam r (the lumped preconditioner) with the r.z and r.r partials.
@@ -2475,14 +2493,22 @@ static int dd_solve_once(Ctx& C, const double* b, double* x, Ctx::Warm* warm, in
       HIPCHK(hipGraphDestroy(g));
       C.cg_graph_iters = chk;
     }
+    // Every check waits for the stream, which then stands idle until the next
+    // block arrives (20 to 30 us, three times in a solve of 12 iterations): the
+    // iterations that the last solves needed go out before the first check.
+    const int ahead = std::min(C.cg_last[0], C.cg_last[1]);
     while (!captured && !converged && it < C.opt.cg_max_iter) {
-      int todo = std::min(chk, C.opt.cg_max_iter - it);
-      if (graph && todo == chk && (it & 1) == 0) {
-        HIPCHK(hipGraphLaunch(C.cg_graph, st));
-      } else {
-        for (int k = 0; k < todo; ++k) iteration(it + k);
+      const int block = it == 0 ? std::max(chk, (ahead + chk - 1) / chk * chk) : chk;
+      const int end = std::min(it + block, C.opt.cg_max_iter);
+      while (it < end) {
+        const int todo = std::min(chk, end - it);
+        if (graph && todo == chk && (it & 1) == 0) {
+          HIPCHK(hipGraphLaunch(C.cg_graph, st));
+        } else {
+          for (int k = 0; k < todo; ++k) iteration(it + k);
+        }
+        it += todo;
       }
-      it += todo;
       HIPCHK(hipGetLastError());
       // the whole state, so that the last check also serves the report
       HIPCHK(hipMemcpyAsync(C.h_cg, state_at(it), sizeof(CgState), hipMemcpyDeviceToHost, st));
@@ -2501,6 +2527,8 @@ static int dd_solve_once(Ctx& C, const double* b, double* x, Ctx::Warm* warm, in
         relres[r] = hs.rr0[r] > 0 ? std::sqrt(hs.rr[r] / hs.rr0[r]) : 0.0;
       }
       if (!converged || hs.breakdown) status = DD_ERR_NO_CONVERGENCE;
+      C.cg_last[1] = C.cg_last[0];
+      C.cg_last[0] = *std::max_element(iters, iters + nr);
     }
     if (warm) {
       std::swap(warm->cur, warm->old);
@@ -2667,6 +2695,9 @@ static void capture_step(Ctx& C, Ctx::StepGraph& sg, const double* b, double* x,
   sg.sweeps = sweeps;
 }
 
+// calls that solve, each with buffers and iteration counts of its own
+enum { kStep = 0, kSolve = 1, kMixed = 2, kAdjoint = 3 };
+
 // A^-1 b with iterative refinement in the mixed form.  b, x: [nint][nrhs].
 // what names the input of b in the message of a non-finite load.  With
 // tx != nullptr the mixed form also leaves T x of the returned iterate there
@@ -2674,11 +2705,12 @@ static void capture_step(Ctx& C, Ctx::StepGraph& sg, const double* b, double* x,
 template <class T>
 static int solve_refined(Ctx& C, const double* b, double* x, Ctx::Warm* warm, dd_stats* stats,
                          const char* what = "b", double* tx = nullptr, bool* tx_done = nullptr,
-                         bool step = false, double* sx = nullptr) {
+                         int kind = kStep, double* sx = nullptr) {
   const int nr = C.nrhs;
   const int64_t n = C.P.nint * nr;
   hipStream_t st = C.st;
   const double ca = C.beta * C.dt * C.dt, cb = (2 * C.beta - 1) * C.dt * C.dt;
+  Ctx::Need& need = C.need[kind];
   int iters[kMaxRhs] = {0};
   double relres[kMaxRhs] = {0};
   int solve_iters[4] = {0, 0, 0, 0};
@@ -2695,17 +2727,23 @@ static int solve_refined(Ctx& C, const double* b, double* x, Ctx::Warm* warm, dd
   };
   const bool refine = C.fp32 && C.opt.refine_max > 0;
   if (tx_done) *tx_done = refine && tx != nullptr;
-  // The step as one captured graph once an eager step has shown how many CG
-  // iterations and sweeps it needs (first variant, no warm start, a
-  // capturable stream, no per-launch timing)
-  const bool graph = step && refine && !warm && C.opt.method == 0 && C.nlam > 0 && C.opt.use_graph &&
-                     st != nullptr && !C.prof && C.need_iters > 0;
+  // The solve as one captured graph once an eager one of its kind has shown how
+  // many CG iterations and sweeps it needs (first variant, no warm start, a
+  // capturable stream, no per-launch timing).  A graph of up to four iterations
+  // more serves as well: they return at once, and counts that differ by one or
+  // two from load to load do not capture again.  The larger of the last two
+  // counts is taken: an iteration too few costs a sweep (two to spare in every
+  // graph instead cost 130 us of 1330 at 21^3, 60 boxes, 7 RHS).
+  const bool graph = refine && !warm && C.opt.method == 0 && C.nlam > 0 && C.opt.use_graph &&
+                     st != nullptr && !C.prof && need.iters > 0;
   if (graph) {
-    const int I = std::min(C.opt.cg_max_iter, C.need_iters);
-    const int S = std::min({C.need_sweeps, C.opt.refine_max, kMaxGraphSweeps});
+    const int I = std::min(C.opt.cg_max_iter, std::max(need.iters, need.before));
+    const int S = std::min({need.sweeps, C.opt.refine_max, kMaxGraphSweeps});
     Ctx::StepGraph* sg = nullptr;
     for (auto& e : C.step_graphs)
-      if (e.g && e.b == b && e.x == x && e.tx == tx && e.sx == sx && e.iters == I && e.sweeps == S) sg = &e;
+      if (e.g && e.b == b && e.x == x && e.tx == tx && e.sx == sx && e.iters >= I && e.iters <= I + 4 &&
+          e.sweeps == S)
+        sg = &e;
     if (!sg) {  // the least recently used slot
       sg = &C.step_graphs[0];
       for (auto& e : C.step_graphs)
@@ -2739,14 +2777,27 @@ static int solve_refined(Ctx& C, const double* b, double* x, Ctx::Warm* warm, dd
         break;
       }
     ok = R.gate[S + 1] != 0;
-    C.need_iters = capped ? std::min(C.opt.cg_max_iter, 2 * I) : std::max(need_it, 1);
+    need.before = need.iters;
+    need.iters = capped ? std::min(C.opt.cg_max_iter, 2 * sg->iters) : std::max(need_it, 1);
     // g_r holds b - A x of the last iterate whenever the last check failed
   } else {
     // |b|^2 per RHS before the solve: the reference of the refinement, and a
     // non-finite load is reported instead of being iterated on
-    dot_to_host(C, b, b, C.P.nint, bn);
-    nonfinite(bn);
+    // (read back with the CG's first check where nothing but scratch has
+    // changed by then: no warm start, no resident state, and not GMRES, which
+    // would iterate on it)
+    const bool defer = !warm && !sx && C.opt.method == 0 && C.nlam > 0;
+    dot_start(C, b, b, C.P.nint);
+    if (!defer) {
+      HIPCHK(hipStreamSynchronize(st));
+      dot_finish(C, C.P.nint, bn);
+      nonfinite(bn);
+    }
     status = dd_solve_once<T>(C, b, x, warm, iters, relres);
+    if (defer) {
+      dot_finish(C, C.P.nint, bn);
+      nonfinite(bn);
+    }
     for (int r = 0; r < nr; ++r) solve_iters[0] = std::max(solve_iters[0], iters[r]);
     if (refine) {
       csr_launch(C, st, 1, x, nullptr, nullptr, nullptr, b, ca, cb, C.g_r, tx, nullptr, sx);
@@ -2785,14 +2836,15 @@ static int solve_refined(Ctx& C, const double* b, double* x, Ctx::Warm* warm, dd
       if (!(gres[r] <= C.opt.refine_tol)) ok = false;
     }
   }
-  if (step && refine) {
-    // what the captured form of the next step must hold
+  if (refine) {
+    // what the captured form of the next solve must hold
     if (!graph) {
       int m = 1;
       for (int k = 0; k < 4; ++k) m = std::max(m, solve_iters[k]);
-      C.need_iters = m;
+      need.before = 0;
+      need.iters = m;
     }
-    C.need_sweeps = sweeps;
+    need.sweeps = sweeps;
   }
   if (stats) {
     std::memset(stats, 0, sizeof(dd_stats));
@@ -2885,7 +2937,7 @@ static int step_impl(Ctx& C, const double* J1, const double* J0, const double* E
   const bool gauss = (C.opt.diagnostics & DD_DIAG_GAUSS) != 0;
   bool have_tx = false;
   int status = solve_refined<T>(C, C.g_b, C.g_e, C.opt.warm_start ? &C.warm_fw : nullptr, stats,
-                                "J, E_n or E_nm1", gauss ? C.g_t2 : nullptr, &have_tx, true);
+                                "J, E_n or E_nm1", gauss ? C.g_t2 : nullptr, &have_tx, kStep);
   hipLaunchKernelGGL(k_int_to_edges, dim3(nblk(ne, 64)), dim3(256), 0, st, ne, C.d_dof, (const double*)C.g_e,
                      Enext, nr, 0, 1.0);
   // (g_t3 still holds J^{n+1/2} per unknown, converted for the load)
@@ -2953,7 +3005,7 @@ static int step_resident_impl(Ctx& C, const double* J1, double* Enext, dd_stats*
                      (2 * C.beta - 1) * C.dt * C.dt, C.g_b);
   bool have_tx = false;
   int status = solve_refined<T>(C, C.g_b, C.rs_e[q], C.opt.warm_start ? &C.warm_fw : nullptr, stats, "J",
-                                C.rs_te[q], &have_tx, true, C.rs_se[q]);
+                                C.rs_te[q], &have_tx, kStep, C.rs_se[q]);
   if (!have_tx)
     csr_launch(C, st, 3, C.rs_e[q], nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, C.rs_te[q], C.rs_se[q]);
   hipLaunchKernelGGL(k_int_to_edges, dim3(nblk(ne, 64)), dim3(256), 0, st, ne, C.d_dof, (const double*)C.rs_e[q],
@@ -2973,7 +3025,7 @@ static int solve_api_impl(Ctx& C, const double* b, double* x, dd_stats* stats) {
   hipStream_t st = C.st;
   hipLaunchKernelGGL(k_edges_to_int, dim3(nblk(ni, 64)), dim3(256), 0, st, ni, C.d_interior, b, ne, C.g_t1, nr,
                      1.0);
-  int status = solve_refined<T>(C, C.g_t1, C.g_e, nullptr, stats, "b");
+  int status = solve_refined<T>(C, C.g_t1, C.g_e, nullptr, stats, "b", nullptr, nullptr, kSolve);
   hipLaunchKernelGGL(k_int_to_edges, dim3(nblk(ne, 64)), dim3(256), 0, st, ne, C.d_dof, (const double*)C.g_e, x,
                      nr, 0, 1.0);
   HIPCHK(hipGetLastError());
@@ -2990,7 +3042,8 @@ static int adjoint_impl(Ctx& C, const double* ebar_next, double* ebar_n, double*
   const int64_t n = ni * nr;
   hipLaunchKernelGGL(k_edges_to_int, dim3(nblk(ni, 64)), dim3(256), 0, st, ni, C.d_interior, ebar_next, ne, C.g_t1, nr,
                      1.0);
-  int status = solve_refined<T>(C, C.g_t1, C.g_x, C.opt.warm_start ? &C.warm_adj : nullptr, stats, "ebar_next");
+  int status = solve_refined<T>(C, C.g_t1, C.g_x, C.opt.warm_start ? &C.warm_adj : nullptr, stats, "ebar_next",
+                                nullptr, nullptr, kAdjoint);
   // B1 g -> g_t2, A g -> g_t3
   csr_launch(C, st, 2, C.g_x, nullptr, nullptr, nullptr, nullptr, C.beta * C.dt * C.dt, (2 * C.beta - 1) * C.dt * C.dt,
              C.g_t2, C.g_t3);
@@ -3678,7 +3731,7 @@ static int mixed_step_impl(Ctx& C, const double* J1, const double* En, const dou
                      (const int32_t*)C.d_e6list, (const double*)C.d_buf6, C.g_e);
   hipLaunchKernelGGL(k_mixed_rhs, dim3(nblk(n)), dim3(256), 0, st, n, (const double*)C.g_t2, (const double*)C.g_x,
                      (const double*)C.g_e, (const double*)C.g_t3, C.dt, C.g_b);
-  int status = solve_refined<T>(C, C.g_b, C.g_e, nullptr, stats);
+  int status = solve_refined<T>(C, C.g_b, C.g_e, nullptr, stats, "b", nullptr, nullptr, kMixed);
   hipLaunchKernelGGL(k_int_to_edges, dim3(nblk(ne, 64)), dim3(256), 0, st, ne, C.d_dof, (const double*)C.g_e,
                      Enext, nr, 0, 1.0);
   hipLaunchKernelGGL(k_face_update, dim3(nblk(nf * nr)), dim3(256), 0, st, nf, nr, ne,

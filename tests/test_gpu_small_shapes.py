@@ -91,3 +91,35 @@ def test_iteration_short_and_long(n, parts, nrhs, precision):
     # 324 workgroups in a reduction at 12^3 and 31 RHS, 170 at 20^3 and 16 RHS:
     # the short form; more than 512 at 19 RHS: the long one
     assert _steps(n, (parts,) * 3, nrhs, precision) <= BAR[precision]
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_refine"])
+def test_solves_repeat_with_other_loads(precision):
+    # dd_solve on one context with a graph-capable stream: eager, captured and
+    # replayed solves of loads that need different iteration counts (a smooth
+    # load, single entries, zero, a non-finite one between), each against the
+    # residual of the assembled matrix
+    from paper_2204_13254_amd.solver import DDSolver
+    n = 8
+    c, t, _ = cube_mesh(n)
+    dt = 0.4 / n
+    o = NewmarkOracle(c, t, dt=dt)
+    free = np.flatnonzero(~o.d.pec)
+    rng = np.random.default_rng(0)
+    loads = [rng.standard_normal((2, o.d.n_e)), np.zeros((2, o.d.n_e)), np.ones((2, o.d.n_e))]
+    loads[1][0, free[7]] = 1.0
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        s = DDSolver(c, t, box_partition(n, (2, 2, 2)), np.ones(len(t)), dt=dt, nrhs=2, precision=precision,
+                     cg_tol=1e-13 if precision == "fp64" else 1e-6, stream=st, use_graph=True)
+        for k in (0, 0, 0, 1, 0, 2, 2, 1, 0):
+            b = torch.tensor(loads[k], device="cuda")
+            x = s.solve(b).cpu().numpy()[:, free]
+            if k == 2:
+                bad = b.clone()
+                bad[1, free[3]] = float("nan")
+                with pytest.raises(Exception, match="non-finite"):
+                    s.solve(bad)
+            want = loads[k][:, free]
+            r = (o.A @ x.T).T - want
+            assert np.linalg.norm(r) <= BAR[precision] * np.linalg.norm(want)
