@@ -247,6 +247,8 @@ struct Ctx {
   int32_t *d_pic_nbr = nullptr, *d_pic_tedge = nullptr;
   unsigned long long* d_pic_cnt = nullptr;
   int32_t *d_pic_count = nullptr, *d_pic_bsum = nullptr;  // ordering by cell: [nt + 1], chunk totals
+  int32_t* d_pic_rank = nullptr;  // place of a particle in its cell, [pic_rank_cap]
+  int64_t pic_rank_cap = 0;
   // mixed E/B step (built on first use): canonical faces, their edges, the
   // faces of every tetrahedron, and the pull list unknown <- (tet, local edge)
   int64_t n_faces = 0;
@@ -3631,6 +3633,34 @@ static void build_dp2(Ctx& C, const double* coords, const double* eps, const dou
   HIPCHK(hipHostMalloc((void**)&C.h_gm_st, sizeof(GmState), hipHostMallocDefault));
 }
 
+// Room for the places of n particles, or null: inside a capture, and where the
+// device has no memory left, the ordering does without.  A smaller buffer is
+// kept until the context ends (a captured call may hold it); each is at least
+// twice the one before, the first holds eight particles a tetrahedron.
+static int32_t* pic_rank(Ctx& C, int64_t n) {
+  if (n <= C.pic_rank_cap) return C.d_pic_rank;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(C.st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  // (relaxed: the caller may be capturing another stream)
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  HIPCHK(hipThreadExchangeStreamCaptureMode(&mode));
+  const int64_t cap = std::max(n, 2 * C.pic_rank_cap);
+  int32_t* d = nullptr;
+  const hipError_t e = hipMalloc((void**)&d, (size_t)cap * sizeof(int32_t));
+  HIPCHK(hipThreadExchangeStreamCaptureMode(&mode));
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  C.owned.push_back(d);
+  C.d_pic_rank = d;
+  C.pic_rank_cap = cap;
+  return d;
+}
+
 // ---- particle tables (built on the first particle call) --------------------------
 static void pic_prepare(Ctx& C) {
   if (C.d_pic_geo) return;
@@ -3647,6 +3677,7 @@ static void pic_prepare(Ctx& C) {
   double* geo = dalloc<double>((size_t)P.nt * 12, C.owned);
   hipLaunchKernelGGL(k_tet_geo, dim3(nblk(P.nt)), dim3(256), 0, C.st, (int64_t)P.nt, C.d_coords, C.d_tsort, geo);
   HIPCHK(hipGetLastError());
+  pic_rank(C, 8 * (int64_t)P.nt);
   C.d_pic_geo = geo;
 }
 
@@ -4265,14 +4296,22 @@ int dd_pic_sort(void* ctx, int64_t n, const int32_t* cell, int32_t* perm) {
   pic_prepare(C);
   if (n == 0) return DD_OK;
   const int64_t nt = C.P.nt, m = nt + 1, nb = (m + kScanBlock - 1) / kScanBlock;
+  int32_t* rank = pic_rank(C, n);
   // a fill kernel, not a memset: this call may be captured into a graph
   hipLaunchKernelGGL(k_zero_i32, dim3(nblk(m)), dim3(256), 0, C.st, m, C.d_pic_count);
-  hipLaunchKernelGGL(k_cell_hist, dim3(nblk(n)), dim3(256), 0, C.st, n, nt, cell, C.d_pic_count);
+  if (rank)
+    hipLaunchKernelGGL(k_cell_hist<true>, dim3(nblk(n)), dim3(256), 0, C.st, n, nt, cell, C.d_pic_count, rank);
+  else
+    hipLaunchKernelGGL(k_cell_hist<false>, dim3(nblk(n)), dim3(256), 0, C.st, n, nt, cell, C.d_pic_count, rank);
   hipLaunchKernelGGL(k_scan_local, dim3((unsigned)nb), dim3(256), 0, C.st, m, C.d_pic_count, C.d_pic_bsum);
   hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(256), 0, C.st, nb, C.d_pic_bsum);
   hipLaunchKernelGGL(k_scan_add, dim3(nblk(m)), dim3(256), 0, C.st, m, C.d_pic_count,
                      (const int32_t*)C.d_pic_bsum);
-  hipLaunchKernelGGL(k_cell_scatter, dim3(nblk(n)), dim3(256), 0, C.st, n, nt, cell, C.d_pic_count, perm);
+  if (rank)
+    hipLaunchKernelGGL(k_cell_place, dim3(nblk(n)), dim3(256), 0, C.st, n, nt, cell, (const int32_t*)C.d_pic_count,
+                       (const int32_t*)rank, perm);
+  else
+    hipLaunchKernelGGL(k_cell_scatter, dim3(nblk(n)), dim3(256), 0, C.st, n, nt, cell, C.d_pic_count, perm);
   HIPCHK(hipGetLastError());
   return DD_OK;
   API_END
@@ -4297,7 +4336,7 @@ int dd_pic_sort_noalloc(void* ctx, int64_t n, const int32_t* cell, int32_t* perm
   // the previous call's counts are still there: clear them with a fill
   // kernel (no memset, so the call can be captured into a graph)
   hipLaunchKernelGGL(k_zero_i32, dim3(nblk(m)), dim3(256), 0, C.st, m, count);
-  hipLaunchKernelGGL(k_cell_hist, dim3(nblk(n)), dim3(256), 0, C.st, n, nt, cell, count);
+  hipLaunchKernelGGL(k_cell_hist<false>, dim3(nblk(n)), dim3(256), 0, C.st, n, nt, cell, count, (int32_t*)nullptr);
   hipLaunchKernelGGL(k_scan_local, dim3((unsigned)nb), dim3(256), 0, C.st, m, count, bsum);
   hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(256), 0, C.st, nb, bsum);
   hipLaunchKernelGGL(k_scan_add, dim3(nblk(m)), dim3(256), 0, C.st, m, count, (const int32_t*)bsum);

@@ -321,16 +321,28 @@ __device__ __forceinline__ void lane_run(int key, int lane, int& head, int& tail
 }
 
 // count[c] += number of particles in cell c (one atomic per run of a wave);
-// inactive particles (cell -1 or out of range) count in c = nt
+// inactive particles (cell -1 or out of range) count in c = nt.  RANK: also the
+// place of every particle among those of its cell, so that k_cell_place needs no
+// second round of atomics, which are what binds both: 1e6 particles in no order on
+// 32^3, 65 us here and 93 in k_cell_scatter; with the places 102 (the atomics then
+// return a value) and 13 in k_cell_place.
+template <bool RANK>
 __global__ void __launch_bounds__(256) k_cell_hist(int64_t n, int64_t nt, const int32_t* __restrict__ cell,
-                                                   int32_t* __restrict__ count) {
+                                                   int32_t* __restrict__ count, int32_t* __restrict__ rank) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int lane = threadIdx.x & 63;
   int64_t c = p < n ? (int64_t)cell[p] : -2 - lane;
   if (p < n && (c < 0 || c >= nt)) c = nt;
   int head, tail;
   lane_run((int)c, lane, head, tail);
-  if (p < n && lane == tail) atomicAdd(&count[c], tail - head + 1);
+  if constexpr (RANK) {
+    int base = 0;
+    if (p < n && lane == tail) base = atomicAdd(&count[c], tail - head + 1);
+    base = __shfl(base, tail);
+    if (p < n) rank[p] = base + lane - head;
+  } else {
+    if (p < n && lane == tail) atomicAdd(&count[c], tail - head + 1);
+  }
 }
 
 __global__ void __launch_bounds__(256) k_zero_i32(int64_t m, int32_t* __restrict__ x) {
@@ -396,6 +408,19 @@ __global__ void __launch_bounds__(256) k_scan_add(int64_t m, int32_t* __restrict
   if (i < m) x[i] += bsum[i / kScanBlock];
 }
 
+// perm from the offsets of the cells and the places of k_cell_hist
+__global__ void __launch_bounds__(256) k_cell_place(int64_t n, int64_t nt, const int32_t* __restrict__ cell,
+                                                    const int32_t* __restrict__ offset,
+                                                    const int32_t* __restrict__ rank, int32_t* __restrict__ perm) {
+  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= n) return;
+  const int32_t r = rank[p];
+  int64_t c = cell[p];
+  if (c < 0 || c >= nt) c = nt;
+  perm[offset[c] + r] = (int32_t)p;
+}
+
+// the same with the offsets as cursors, where there is no room for the places
 __global__ void __launch_bounds__(256) k_cell_scatter(int64_t n, int64_t nt, const int32_t* __restrict__ cell,
                                                       int32_t* __restrict__ cursor, int32_t* __restrict__ perm) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

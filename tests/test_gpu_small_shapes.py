@@ -123,3 +123,47 @@ def test_solves_repeat_with_other_loads(precision):
             want = loads[k][:, free]
             r = (o.A @ x.T).T - want
             assert np.linalg.norm(r) <= BAR[precision] * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("m", [1, 63, 64, 65, 1000, 40001])
+def test_ordering_with_and_without_room_for_places(m):
+    # a first call, one within the room of the last, one captured that needs
+    # more than the context has (it does without), replayed beside eager calls
+    from paper_2204_13254_amd.solver import DDSolver
+    n = 5
+    c, t, _ = cube_mesh(n)
+    nt = len(t)
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        s = DDSolver(c, t, box_partition(n, 2), np.ones(nt), dt=0.05, factor=False, stream=st)
+        rng = np.random.default_rng(m)
+
+        def check(cell, perm):
+            cell, perm = cell.cpu().numpy(), perm.cpu().numpy()
+            assert np.array_equal(np.sort(perm), np.arange(len(cell)))
+            k = cell[perm]
+            k = np.where((k < 0) | (k >= nt), nt, k)
+            assert np.all(np.diff(k) >= 0)
+
+        def draw(size):
+            v = rng.integers(-2, nt + 3, size).astype(np.int32)
+            v[: size // 3] = np.sort(v[: size // 3])
+            return torch.tensor(v, device="cuda")
+
+        for size in (m, max(1, m // 2), m):
+            cell = draw(size)
+            check(cell, s.pic_sort(cell))
+        big = draw(2 * m + 5)
+        perm = torch.full((2 * m + 5,), -7, dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st):
+            from paper_2204_13254_amd.solver import _dev_i32
+            assert s.lib.dd_pic_sort(s.h, big.numel(), _dev_i32(big), _dev_i32(perm)) == 0
+        for _ in range(3):
+            big.copy_(draw(2 * m + 5))
+            perm.fill_(-7)
+            g.replay()
+            check(big, perm)
+            cell = draw(4 * m + 9)                 # the room grows between replays
+            check(cell, s.pic_sort(cell))
