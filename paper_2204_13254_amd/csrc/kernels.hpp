@@ -346,11 +346,11 @@ __global__ void k_pad_diag(int64_t n, const int64_t* __restrict__ pos, T* __rest
 // (nzl: L, nzi: inverse; flags outside the pattern stay zero).
 // Bound by FP64 MFMA on the wide levels (32^3, 64 boxes: 1472 tiles of 100
 // terms in 115 us, 83 TFLOP/s with the skipped zero tiles counted) and by the
-// latency of one diagonal tile (13 us) on the narrow ones.  Measured there (FP64
-// / FP32 dd_factor): 29.5 / 19.7 ms with a right-looking panel per tile column
-// (C read and written by every earlier column) and row-by-row inverses, 11.4 /
-// 7.4 ms now; 64^3, 1000 boxes, FP32: 86.5 -> 39.6 ms.  Arithmetic in the storage type T except the diagonal
-// tile, which is factored and inverted in FP64.
+// latency of one diagonal tile on the narrow ones.  Measured there (FP64 / FP32
+// dd_factor): 29.5 / 19.7 ms with a right-looking panel per tile column (C read
+// and written by every earlier column) and row-by-row inverses, 10.9 / 6.8 ms
+// now; 64^3, 1000 boxes, FP32: 86.5 -> 35.9 ms.  Arithmetic in the storage type
+// T except the diagonal tile, which is factored and inverted in FP64.
 // --------------------------------------------------------------------------
 struct FacItem {
   int32_t s;    // block (-1: padding)
@@ -365,82 +365,119 @@ __device__ __forceinline__ double recip64(double d) {
   return __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
 }
 
-// Cholesky factor of the symmetric tile held in a (lower part used), its
-// inverse returned as xv: thread (rb, c) = (tid / 32, tid % 32) of 256 gets
-// entries (rb + 8u, c) of L^-1 (zero above the diagonal).  Returns nonzero when
-// a pivot is not positive and finite (the same in every thread).
-__device__ __forceinline__ int potrf_inv_tile(double (*a)[kNB + 1], double (*x)[kNB + 1], double* piv,
-                                              double (&xv)[kTile / 256]) {
-  constexpr int U = kTile / 256;
-  const int tid = threadIdx.x, c = tid & 31, rb = tid >> 5;
-  double v[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int r = rb + 8 * u;
-    v[u] = a[r][c];
-    xv[u] = r == c ? 1.0 : 0.0;
-    x[r][c] = xv[u];
-  }
-  __syncthreads();
-  // Right-looking elimination with unscaled columns: step j subtracts
-  // a_rj a_cj / d_j from the trailing entries (c > j, r >= c) while column j
-  // is only read; the owners of column j + 1 publish it for the next step, so
-  // one barrier per column.  d_j = pivot; every thread reads the same pivot
-  // and takes the same decision on it.
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const int64_t u = __builtin_bit_cast(int64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((int)(u >> 32), lane);
+  return __builtin_bit_cast(double, (int64_t)((uint64_t)hi << 32 | lo));
+}
+
+// One wave; the lane of row r holds v[c], c < 16: row r of a symmetric 16 x 16
+// block (r < 16, lane r) or of the rows below it.  Elimination with unscaled
+// columns on [A | I]: step j subtracts f_r = a_rj / d_j times a_cj from the rows
+// below, with a_cj from lane c and the identity's row j from lane j.  Left in x:
+// the rows of L~^-1 (L~ the unit factor), below them -L~_r L~^-1; in v the
+// unscaled columns; rd = 1 / sqrt(d_r).  Returns nonzero when a pivot is not
+// positive and finite.
+__device__ __forceinline__ int eliminate_16(int r, double (&v)[16], double (&x)[16], double& rd) {
   int bad = 0;
-  for (int j = 0; j < kNB; ++j) {
-    double d = a[j][j];
-    const double acj = a[c][j];
-    double arj[U];
+  double dr = 1.0;
 #pragma unroll
-    for (int u = 0; u < U; ++u) arj[u] = a[rb + 8 * u][j];
+  for (int c = 0; c < 16; ++c) x[c] = r == c ? 1.0 : 0.0;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    double d = lane_value(v[j], j);
     if (!(d > 0.0) || !isfinite(d)) {
       bad = 1;
       d = 1.0;
     }
-    const double f = acj * recip64(d);
-    if (tid == 0) piv[j] = d;
+    if (r == j) dr = d;
+    const double f = r > j ? -(v[j] * recip64(d)) : 0.0;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int r = rb + 8 * u;
-      if (c > j && r >= c) v[u] -= arj[u] * f;
-      if (c == j + 1) a[r][c] = v[u];
+    for (int c = 0; c < 16; ++c) {
+      if (c > j) v[c] = __builtin_fma(f, lane_value(v[j], c), v[c]);
+      if (c < j) x[c] = __builtin_fma(f, lane_value(x[c], j), x[c]);
     }
-    __syncthreads();
+    if (r > j) x[j] = f;
   }
-  // L = unscaled columns / sqrt(d); piv becomes 1 / L_jj
-  const double rd = 1.0 / sqrt(piv[c]);
-  __syncthreads();
-  if (rb == 0) piv[c] = rd;
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int r = rb + 8 * u;
-    a[r][c] = r > c ? v[u] * rd : 0.0;
-  }
-  __syncthreads();
-  // L^-1 by forward substitution on the identity, all columns at once: at
-  // step m row m is complete up to its division by L_mm, and the rows below
-  // take L_rm X_mc / L_mm; the owners of row m + 1 publish it (again one
-  // barrier per step)
-  for (int m = 0; m < kNB; ++m) {
-    const double g = x[m][c] * piv[m];
-    double arm[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) arm[u] = a[rb + 8 * u][m];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int r = rb + 8 * u;
-      if (r > m && c <= m) xv[u] -= arm[u] * g;
-      if (r == m + 1) x[r][c] = xv[u];
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int r = rb + 8 * u;
-    xv[u] = c <= r ? xv[u] * piv[r] : 0.0;
-  }
+  rd = 1.0 / sqrt(dr);
   return bad;
+}
+
+// acc += P Q^T of two 16 x 16 blocks in LDS (Q: or its transpose), one wave
+template <bool QT>
+__device__ __forceinline__ Mfma<double>::acc_t mm16(const double (*p)[kNB + 1], int pr, int pc,
+                                                    const double (*q)[kNB + 1], int qr, int qc) {
+  const int l = threadIdx.x & 63, i = l & 15, g = l >> 4;
+  Mfma<double>::acc_t acc = {0, 0, 0, 0};
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks)
+    acc = Mfma<double>::op(p[pr + i][pc + 4 * g + ks],
+                           QT ? q[qr + 4 * g + ks][qc + i] : q[qr + i][qc + 4 * g + ks], acc);
+  return acc;
+}
+
+// Inverse of the Cholesky factor of the symmetric tile held in a (lower part
+// used; a is overwritten), returned as xv: thread (rb, c) = (tid / 32, tid % 32)
+// of 256 gets entries (rb + 8u, c) of L^-1 (zero above the diagonal).  Returns
+// nonzero when a pivot is not positive and finite (the same in every thread).
+// A chain of 32 pivots, so latency is all of it: one wave eliminates 16 columns at
+// a time in its registers and joins the halves on MFMA, without a barrier,
+//   A22 -= L21 L21^T, X21 = X22 (-L~21 L~11^-1).
+// (256 threads with two barriers a column, in LDS: dd_factor took 3.50 ms at 16^3, 8
+// boxes, FP64, 11.4 at 32^3, 64 boxes, and 39.4 in FP32 at 64^3, 1000 boxes; now
+// 2.85, 10.9 and 35.9.)
+__device__ __forceinline__ int potrf_inv_tile(double (*a)[kNB + 1], double (*x)[kNB + 1], double* piv,
+                                              double (&xv)[kTile / 256]) {
+  const int tid = threadIdx.x;
+  if (tid < 64) {
+    const int l = tid;
+    double v[16], y[16];
+    int bad = 0;
+    auto order = [] {  // LDS between the lanes of this wave
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    };
+    using Acc = Mfma<double>::acc_t;
+#pragma unroll 1
+    for (int h = 0; h < 2; ++h) {
+      const int o = 16 * h, r = h == 0 ? l & 31 : l & 15;  // rows o + r, columns o..
+#pragma unroll
+      for (int c = 0; c < 16; ++c) v[c] = a[o + max(r, c)][o + min(r, c)];
+      double rd;
+      bad |= eliminate_16(r, v, y, rd);
+      order();
+      if (l < 32 - o) {
+#pragma unroll
+        for (int c = 0; c < 16; ++c) {
+          const double rc = lane_value(rd, c);
+          x[o + r][o + c] = r < 16 ? y[c] * rd : y[c];
+          if (h == 0) {
+            if (r < 16)
+              x[r][16 + c] = 0.0;
+            else
+              a[r][c] = v[c] * rc;
+          }
+        }
+      }
+      order();
+      if (h == 0) {
+        const Acc s22 = mm16<false>(a, 16, 0, a, 16, 0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a[16 + Mfma<double>::row(l, u)][16 + (l & 15)] -= s22[u];
+        order();
+      }
+    }
+    const Acc z = mm16<true>(x, 16, 16, x, 16, 0);
+    order();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) x[16 + Mfma<double>::row(l, u)][l & 15] = z[u];
+    if (l == 0) piv[0] = bad ? 1.0 : 0.0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kTile / 256; ++u) xv[u] = x[(tid >> 5) + 8 * u][tid & 31];
+  return piv[0] != 0.0;
 }
 
 // Items [0, nd): diagonal tiles; [nd, nd + no): off-diagonal tiles (i, k) and
@@ -449,11 +486,13 @@ __device__ __forceinline__ int potrf_inv_tile(double (*a)[kNB + 1], double (*x)[
 // product of the factorisation has the form P Q^T of two tiles whose lanes read
 // contiguous kilobytes (from row-major tiles, 64-byte pieces of 16 rows: the
 // steps took 1.4 times as long), and the solves' transposed store is final.
+// In FP32 the chains want four waves per SIMD: without the bound the diagonal
+// tile's registers would leave three.
 template <class T>
-__global__ void __launch_bounds__(256) k_chol_step(int nd, int no, const FacItem* __restrict__ items,
-                                                   T* __restrict__ tiles, T* __restrict__ inv,
-                                                   const SubDev* __restrict__ subs, int* __restrict__ err,
-                                                   uint8_t* __restrict__ nzl, uint8_t* __restrict__ nzi) {
+__global__ void __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2)
+    k_chol_step(int nd, int no, const FacItem* __restrict__ items, T* __restrict__ tiles, T* __restrict__ inv,
+                const SubDev* __restrict__ subs, int* __restrict__ err, uint8_t* __restrict__ nzl,
+                uint8_t* __restrict__ nzi) {
   const int b = blockIdx.x;
   const FacItem it = items[b];
   if (it.s < 0) return;
