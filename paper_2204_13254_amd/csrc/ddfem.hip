@@ -1223,9 +1223,11 @@ static void drop_graphs(Ctx& C) {
 static inline unsigned chain_lds(int n) { return (unsigned)(std::max(n, 2) * sizeof(uint16_t) + 15) & ~15u; }
 
 // Work lists of the factorisation from the symbolic patterns (once per
-// context).
+// context; made aside and handed over whole, so that a call that ran out of
+// memory on the way can be repeated).
 static void factor_lists(Ctx& C) {
   if (C.d_fac) return;
+  Ctx::FacList sub, coarse;
   std::vector<FacItem> fac;
   std::vector<int64_t> pack, clear;
   // items of one list placed by XCD: workgroup b runs on XCD b % 8, and the
@@ -1297,16 +1299,19 @@ static void factor_lists(Ctx& C) {
       F.steps.push_back(st);
     }
   };
-  blocks(0, C.nsub, C.fac_sub);
-  blocks(C.nsub, C.nsub + (C.Kc > 0 ? 1 : 0), C.fac_coarse);
+  blocks(0, C.nsub, sub);
+  blocks(C.nsub, C.nsub + (C.Kc > 0 ? 1 : 0), coarse);
   C.psi_first = (int64_t)fac.size();
   C.n_psi = place(psi);
   if (fac.size() >= (size_t)INT32_MAX || pack.size() >= (size_t)INT32_MAX)
     throw DDError{DD_ERR_OOM, "factorisation work lists exceed 2^31 entries"};
-  C.d_pack = upload(pack, C.owned, C.st);
-  C.d_clear = upload(clear, C.owned, C.st);
+  // (the arrays of a repeated call are those of the one before)
+  if (!C.d_pack) C.d_pack = upload(pack, C.owned, C.st);
+  if (!C.d_clear) C.d_clear = upload(clear, C.owned, C.st);
   C.n_clear = (int64_t)clear.size();
   C.d_fac = upload(fac, C.owned, C.st);
+  C.fac_sub = std::move(sub);
+  C.fac_coarse = std::move(coarse);
   std::vector<uint8_t>().swap(C.sym_tile);
   std::vector<std::vector<int32_t>>().swap(C.sym_level);
 }

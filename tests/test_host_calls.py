@@ -1,0 +1,90 @@
+"""The library's host code behind the C ABI, run without a device: its HIP calls
+are bound to a stand-in runtime (tests/csrc/hip_stub.cpp) that counts kernels
+and allocations and can refuse one."""
+import os
+import shutil
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_2204_13254_amd", "libddfem.so")
+
+PRELUDE = """
+import ctypes as C, importlib.util, os, sys
+import numpy as np
+root, stub_path = sys.argv[1], sys.argv[2]
+sys.path.insert(0, root)
+stub = C.CDLL(stub_path, mode=C.RTLD_GLOBAL)
+stub.stub_fail_at.argtypes = [C.c_long]
+stub.stub_mallocs.restype = stub.stub_launches.restype = C.c_long
+spec = importlib.util.spec_from_file_location("ddlib", os.path.join(root, "paper_2204_13254_amd", "_lib.py"))
+dd = importlib.util.module_from_spec(spec)
+spec.loader.exec_module(dd)
+lib = dd.load()
+from workloads.mesh import cube_mesh
+from workloads.partition import box_partition
+
+def context(n, parts, **opt):
+    c, t, _ = cube_mesh(n)
+    c, t = np.ascontiguousarray(c, np.float64), np.ascontiguousarray(t, np.int32)
+    p = np.ascontiguousarray(box_partition(n, parts), np.int32)
+    eps = np.ones(len(t))
+    o = dd.Options()
+    lib.dd_default_options(C.byref(o))
+    for k, v in opt.items():
+        setattr(o, k, v)
+    ptr = lambda a: a.ctypes.data_as(C.c_void_p)
+    m = dd.Mesh(len(c), ptr(c), len(t), ptr(t))
+    h = C.c_void_p()
+    rc = lib.dd_setup(C.byref(h), C.byref(m), ptr(p), ptr(eps), None, 0.05, 0.25, C.byref(o))
+    assert rc == 0, rc
+    return h
+"""
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if gxx is None or not os.path.exists(LIB):
+        pytest.skip("needs a host C++ compiler and the built library")
+    so = str(tmp_path_factory.mktemp("stub") / "libhipstub.so")
+    r = subprocess.run([gxx, "-std=c++17", "-O1", "-shared", "-fPIC",
+                        os.path.join(ROOT, "tests", "csrc", "hip_stub.cpp"), "-o", so],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return so
+
+
+def _run(stub, body):
+    r = subprocess.run([sys.executable, "-c", PRELUDE + textwrap.dedent(body), ROOT, stub],
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-3000:]
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_factor_after_a_refused_allocation(stub, precision):
+    # an allocation of the first dd_factor is refused, each in turn: the call says
+    # so and the next one launches what an undisturbed context launches, once
+    _run(stub, f"""
+    OOM = -8
+    h = context(6, 2, precision={precision})
+    stub.stub_clear_counts()
+    stub.stub_fail_at(0)
+    assert lib.dd_factor(h) == 0
+    allocs, steps, trsm = stub.stub_mallocs(), stub.stub_launches(b"k_chol_step"), stub.stub_launches(b"k_chol_trsm")
+    assert allocs >= 3 and steps > 2
+    lib.dd_destroy(h)
+    for k in range(1, allocs + 1):
+        h = context(6, 2, precision={precision})
+        stub.stub_clear_counts()
+        stub.stub_fail_at(k)
+        assert lib.dd_factor(h) == OOM, k
+        stub.stub_fail_at(0)
+        assert lib.dd_factor(h) == 0, k
+        assert stub.stub_launches(b"k_chol_step") == steps, k
+        assert stub.stub_launches(b"k_chol_trsm") == trsm, k
+        lib.dd_destroy(h)
+    """)
