@@ -161,6 +161,7 @@ struct Ctx {
     const double* b = nullptr;
     double *x = nullptr, *tx = nullptr, *sx = nullptr;
     int iters = 0, sweeps = 0;
+    bool stop = false;
     uint64_t used = 0;
   } step_graphs[6];
   uint64_t step_clock = 0;
@@ -1183,7 +1184,7 @@ static void build_device(Ctx& C, const double* coords) {
     C.d_partial3 = dalloc<double>(kDotBlocks * kMaxRhs, C.owned);
     C.d_res2 = dalloc<double>(nl, C.owned);
   }
-  C.d_cg = dalloc<CgState>(2, C.owned);
+  C.d_cg = dalloc<CgState>(3, C.owned);  // (two copies, and one kept by k_cg_snapshot)
   HIPCHK(hipHostMalloc((void**)&C.h_cg, sizeof(CgState), hipHostMallocDefault));
   HIPCHK(hipHostMalloc((void**)&C.h_partial, sizeof(double) * kDotBlocks * kMaxRhs, hipHostMallocDefault));
   C.d_rs = dalloc<RefineState>(1, C.owned);
@@ -2321,24 +2322,13 @@ static void lam_precond(Ctx& C, const int* skip) {
                        C.d_lvals, (const double*)C.d_res, C.d_z, nr, C.d_partial, C.d_partial2, skip);
 }
 
-// x = A^-1 b (one decomposed solve, unknown-major [nint][nrhs] FP64).
-// Returns DD_OK or DD_ERR_NO_CONVERGENCE; fills iters/relres.
-// Captured form (fixed_iters > 0, inside a stream capture): exactly
-// fixed_iters CG iterations (kernels return at once after convergence), no
-// host synchronisation and no warm start; every kernel is skipped while
-// *gate != 0; the CG state is snapshotted into C.d_rs slot `slot` and
-// iters/relres are not filled (read back with the step).
+// Pre-solve of b through the column blocks of the factor store.
 template <class T>
-static int dd_solve_once(Ctx& C, const double* b, double* x, Ctx::Warm* warm, int* iters, double* relres,
-                         const int* gate = nullptr, int fixed_iters = 0, int slot = 0) {
+static void presolve(Ctx& C, const double* b, const int* gate) {
   const int nr = C.nrhs;
   hipStream_t st = C.st;
   void** X = C.X;
   const T one = 1, mone = -1;
-  // ---- pre-solve --------------------------------------------------------
-  const bool captured = fixed_iters > 0;
-  if (captured && (warm || C.opt.method == 1))
-    throw DDError{DD_ERR_STATE, "captured solve: no warm start, first variant only"};
   if (vec_width(nr) == 4)
     hipLaunchKernelGGL((k_split_v<T, 4>), dim3(nblk(C.rows_total * nr / 4)), dim3(256), 0, st, C.rows_total,
                        C.d_rowsrc, b, (T*)X[0], nr, gate);
@@ -2359,6 +2349,28 @@ static int dd_solve_once(Ctx& C, const double* b, double* x, Ctx::Warm* warm, in
   mv<T>(C, C.full_N, false, X[0], X[1], nullptr, one, gate);
   mv<T>(C, C.cross_N, false, X[1], X[2], X[0], mone, gate, X[0], mone);
   interface_local<T>(C, X[2], X[2], X[4], X[3], gate);
+}
+
+// x = A^-1 b (one decomposed solve, unknown-major [nint][nrhs] FP64).
+// Returns DD_OK or DD_ERR_NO_CONVERGENCE; fills iters/relres.
+// Captured form (fixed_iters > 0, inside a stream capture): exactly
+// fixed_iters CG iterations (kernels return at once after convergence), no
+// host synchronisation and no warm start; every kernel is skipped while
+// *gate != 0; the CG state is snapshotted into C.d_rs slot `slot` and
+// iters/relres are not filled (read back with the step).  With stop the graph
+// ends at a solve that fixed_iters left unfinished, and a call with from =
+// fixed_iters finishes it: no pre-solve, the iterations from there on, recovery.
+template <class T>
+static int dd_solve_once(Ctx& C, const double* b, double* x, Ctx::Warm* warm, int* iters, double* relres,
+                         int* gate = nullptr, int fixed_iters = 0, int slot = 0, bool stop = false, int from = 0) {
+  const int nr = C.nrhs;
+  hipStream_t st = C.st;
+  void** X = C.X;
+  const T one = 1, mone = -1;
+  const bool captured = fixed_iters > 0;
+  if (captured && (warm || C.opt.method == 1))
+    throw DDError{DD_ERR_STATE, "captured solve: no warm start, first variant only"};
+  if (from == 0) presolve<T>(C, b, gate);
   for (int r = 0; r < nr; ++r) {
     iters[r] = 0;
     relres[r] = 0.0;
@@ -2372,43 +2384,49 @@ static int dd_solve_once(Ctx& C, const double* b, double* x, Ctx::Warm* warm, in
   } else if (C.nlam > 0) {
     const int64_t nl = C.nlam * nr;
     const int nb = dot_blocks(C, C.nlam);
-    scatter_dot<T>(C, (const T*)X[4], (const T*)nullptr, C.d_d, (const double*)nullptr, gate);
-    // ---- CG on F lambda = d (stage 0 of k_cg_scalar resets the whole state) ----
-    dot_partial(C, st, C.nlam, C.d_d, C.d_d, C.d_partial, gate);
-    hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, st, 0, nr, nb, (const double*)C.d_partial,
-                       (const double*)nullptr, C.d_cg, C.opt.cg_tol, gate);
-    hipLaunchKernelGGL(k_copy, dim3(nblk(nl)), dim3(256), 0, st, nl, (const double*)C.d_d, C.d_res, gate);
-    if (warm && warm->have > 0) {
-      if (C.opt.warm_start == 2 && warm->have >= 2)
-        hipLaunchKernelGGL(k_extrap, dim3(nblk(nl)), dim3(256), 0, st, nl, (const double*)warm->cur,
-                           (const double*)warm->old, C.d_lam);
-      else
-        HIPCHK(hipMemcpyAsync(C.d_lam, warm->cur, nl * sizeof(double), hipMemcpyDeviceToDevice, st));
-      apply_F<T>(C, C.d_lam, C.d_Fp, nullptr);
-      hipLaunchKernelGGL(k_sub, dim3(nblk(nl)), dim3(256), 0, st, nl, C.d_d, C.d_Fp, C.d_res);
-      dot_partial(C, st, C.nlam, C.d_res, C.d_res, C.d_partial, nullptr);
-      hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, st, 3, nr, nb, (const double*)C.d_partial,
-                         (const double*)nullptr, C.d_cg, C.opt.cg_tol, (const int*)nullptr);
-    } else {
-      hipLaunchKernelGGL(k_zero<double>, dim3(nblk(nl)), dim3(256), 0, st, nl, C.d_lam, gate);
-    }
-    // p = z = K_lam r (lumped preconditioner), or p = r
     const bool pre = C.opt.precond == 1 && C.lam_nnz > 0;
-    if (pre) {
-      lam_precond(C, gate);
-      hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, st, 4, nr, nb, (const double*)C.d_partial,
-                         (const double*)nullptr, C.d_cg, C.opt.cg_tol, gate);
-    }
-    hipLaunchKernelGGL(k_copy, dim3(nblk(nl)), dim3(256), 0, st, nl, (const double*)(pre ? C.d_z : C.d_res), C.d_p,
-                       gate);
-    // v = B_s^T p for the first F application, padding rows zeroed (later
-    // ones are written by k_cg_p_scatter, which leaves padding rows alone)
-    lambda_gather<T>(C, C.n_grow, C.d_glam, (const double*)C.d_p, (T*)X[5], gate);
     // short form of the iteration (k_cg_rz, k_cg_pv): its state and r alternate,
     // iteration k reading copy k & 1
     const bool brief = pre && C.d_res2;
     auto state_at = [&](int k) { return C.d_cg + (brief ? k & 1 : 0); };
-    int it = 0;
+    auto start = [&] {
+      scatter_dot<T>(C, (const T*)X[4], (const T*)nullptr, C.d_d, (const double*)nullptr, gate);
+      // ---- CG on F lambda = d (stage 0 of k_cg_scalar resets the whole state) ----
+      dot_partial(C, st, C.nlam, C.d_d, C.d_d, C.d_partial, gate);
+      hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, st, 0, nr, nb, (const double*)C.d_partial,
+                         (const double*)nullptr, C.d_cg, C.opt.cg_tol, gate);
+      hipLaunchKernelGGL(k_copy, dim3(nblk(nl)), dim3(256), 0, st, nl, (const double*)C.d_d, C.d_res, gate);
+      if (warm && warm->have > 0) {
+        if (C.opt.warm_start == 2 && warm->have >= 2)
+          hipLaunchKernelGGL(k_extrap, dim3(nblk(nl)), dim3(256), 0, st, nl, (const double*)warm->cur,
+                             (const double*)warm->old, C.d_lam);
+        else
+          HIPCHK(hipMemcpyAsync(C.d_lam, warm->cur, nl * sizeof(double), hipMemcpyDeviceToDevice, st));
+        apply_F<T>(C, C.d_lam, C.d_Fp, nullptr);
+        hipLaunchKernelGGL(k_sub, dim3(nblk(nl)), dim3(256), 0, st, nl, C.d_d, C.d_Fp, C.d_res);
+        dot_partial(C, st, C.nlam, C.d_res, C.d_res, C.d_partial, nullptr);
+        hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, st, 3, nr, nb, (const double*)C.d_partial,
+                           (const double*)nullptr, C.d_cg, C.opt.cg_tol, (const int*)nullptr);
+      } else {
+        hipLaunchKernelGGL(k_zero<double>, dim3(nblk(nl)), dim3(256), 0, st, nl, C.d_lam, gate);
+      }
+      // p = z = K_lam r (lumped preconditioner), or p = r
+      if (pre) {
+        lam_precond(C, gate);
+        hipLaunchKernelGGL(k_cg_scalar, dim3(1), dim3(kScalarThreads), 0, st, 4, nr, nb, (const double*)C.d_partial,
+                           (const double*)nullptr, C.d_cg, C.opt.cg_tol, gate);
+      }
+      hipLaunchKernelGGL(k_copy, dim3(nblk(nl)), dim3(256), 0, st, nl, (const double*)(pre ? C.d_z : C.d_res), C.d_p,
+                         gate);
+      // v = B_s^T p for the first F application, padding rows zeroed (later
+      // ones are written by k_cg_p_scatter, which leaves padding rows alone)
+      lambda_gather<T>(C, C.n_grow, C.d_glam, (const double*)C.d_p, (T*)X[5], gate);
+    };
+    if (from == 0)
+      start();
+    else
+      HIPCHK(hipMemcpyAsync(state_at(from), C.d_cg + 2, sizeof(CgState), hipMemcpyDeviceToDevice, st));
+    int it = from;
     // an even block of iterations, so that every replay starts on p = d_p
     const int chk = std::max(2, (C.opt.check_every + 1) / 2 * 2);
     // no host check before the first block: its kernels return at once when
@@ -2480,8 +2498,8 @@ static int dd_solve_once(Ctx& C, const double* b, double* x, Ctx::Warm* warm, in
     // captured step: a fixed number of iterations, the state snapshotted
     if (captured) {
       for (int k = 0; k < fixed_iters; ++k) iteration(k);
-      hipLaunchKernelGGL(k_cg_snapshot, dim3(1), dim3(64), 0, st, slot, nr, (const CgState*)state_at(fixed_iters), C.d_rs,
-                         gate);
+      hipLaunchKernelGGL(k_cg_snapshot, dim3(1), dim3(64), 0, st, slot, nr, (const CgState*)state_at(fixed_iters),
+                         C.d_cg, stop ? C.d_cg + 2 : (CgState*)nullptr, C.d_rs, gate);
       converged = true;
       have_state = true;
     }
@@ -2524,7 +2542,7 @@ static int dd_solve_once(Ctx& C, const double* b, double* x, Ctx::Warm* warm, in
       converged = C.h_cg->done != 0;
     }
     if (!have_state) {
-      HIPCHK(hipMemcpyAsync(C.h_cg, C.d_cg, sizeof(CgState), hipMemcpyDeviceToHost, st));
+      HIPCHK(hipMemcpyAsync(C.h_cg, state_at(it), sizeof(CgState), hipMemcpyDeviceToHost, st));
       HIPCHK(hipStreamSynchronize(st));
     }
     if (!captured) {
@@ -2546,7 +2564,8 @@ static int dd_solve_once(Ctx& C, const double* b, double* x, Ctx::Warm* warm, in
     // u = y_G - B_s^T lambda on the interface rows of X5
     lambda_gather<T>(C, C.n_grow, C.d_glam, (const double*)C.d_lam, (T*)X[5], gate, (const T*)X[2]);
   } else if (captured) {
-    hipLaunchKernelGGL(k_cg_snapshot, dim3(1), dim3(64), 0, st, slot, nr, (const CgState*)C.d_cg, C.d_rs, gate);
+    hipLaunchKernelGGL(k_cg_snapshot, dim3(1), dim3(64), 0, st, slot, nr, (const CgState*)C.d_cg, C.d_cg,
+                       (CgState*)nullptr, C.d_rs, gate);
   }
   // x_c = K_cc^-1 sum B_c^T (g' - Psi_G u) (coarse rows of X5, where the
   // collect reads corner unknowns), x_G = M u - Psi_G^T x_c (interface rows
@@ -2648,9 +2667,10 @@ static void csr_launch(Ctx& C, hipStream_t st, int mode, const double* x1, const
 // graph gives the norms, the checks and every solve's CG state.  The
 // graph goes into slot sg (which keeps its buffers and counts).  tx, sx
 // (may be null): T x and S x of the accepted iterate, from its residual.
+// stop: the graph ends at a solve that needs more iterations (k_cg_snapshot).
 template <class T>
 static void capture_step(Ctx& C, Ctx::StepGraph& sg, const double* b, double* x, double* tx, double* sx, int iters,
-                         int sweeps) {
+                         int sweeps, bool stop) {
   hipStream_t st = C.st;
   const int nr = C.nrhs;
   const int64_t n = C.P.nint * nr;
@@ -2662,7 +2682,7 @@ static void capture_step(Ctx& C, Ctx::StepGraph& sg, const double* b, double* x,
     int* gate = reinterpret_cast<int*>(reinterpret_cast<char*>(C.d_rs) + offsetof(RefineState, gate));
     dot_partial(C, st, C.P.nint, b, b, C.d_rpart, nullptr);
     hipLaunchKernelGGL(k_refine_init, dim3(1), dim3(kScalarThreads), 0, st, nr, dot_blocks(C, C.P.nint), (const double*)C.d_rpart, C.d_rs);
-    dd_solve_once<T>(C, b, x, nullptr, it_dummy, rr_dummy, gate, iters, 0);
+    dd_solve_once<T>(C, b, x, nullptr, it_dummy, rr_dummy, gate, iters, 0, stop);
     for (int k = 1; k <= sweeps + 1; ++k) {
       // only the last residual writes T x and S x (460 MB less at 64^3 with
       // 16 RHS), and it runs even when an earlier check has passed (x is
@@ -2677,7 +2697,7 @@ static void capture_step(Ctx& C, Ctx::StepGraph& sg, const double* b, double* x,
       hipLaunchKernelGGL(k_refine_check, dim3(1), dim3(kScalarThreads), 0, st, k, nr, dot_blocks(C, C.P.nint), (const double*)C.d_rpart,
                          C.opt.refine_tol, C.d_rs, C.d_cg);
       if (k > sweeps) break;
-      dd_solve_once<T>(C, C.g_r, C.g_t4, nullptr, it_dummy, rr_dummy, gate + k, iters, k);
+      dd_solve_once<T>(C, C.g_r, C.g_t4, nullptr, it_dummy, rr_dummy, gate + k, iters, k, stop);
       hipLaunchKernelGGL(k_axpy, dim3(nblk(n)), dim3(256), 0, st, n, 1.0, (const double*)C.g_t4, x,
                          (const int*)(gate + k));
     }
@@ -2700,6 +2720,7 @@ static void capture_step(Ctx& C, Ctx::StepGraph& sg, const double* b, double* x,
   sg.sx = sx;
   sg.iters = iters;
   sg.sweeps = sweeps;
+  sg.stop = stop;
 }
 
 // calls that solve, each with buffers and iteration counts of its own
@@ -2732,6 +2753,36 @@ static int solve_refined(Ctx& C, const double* b, double* x, Ctx::Warm* warm, dd
         throw DDError{DD_ERR_NONFINITE, std::string("non-finite entry in the load of right-hand side ") +
                                             std::to_string(r) + " (" + what + ")"};
   };
+  // residual of x and its norm against refine_tol
+  auto check = [&] {
+    csr_launch(C, st, 1, x, nullptr, nullptr, nullptr, b, ca, cb, C.g_r, tx, nullptr, sx);
+    double rn[kMaxRhs];
+    dot_to_host(C, C.g_r, C.g_r, C.P.nint, rn);
+    ok = true;
+    for (int r = 0; r < nr; ++r) {
+      gres[r] = bn[r] > 0 ? std::sqrt(rn[r] / bn[r]) : 0.0;
+      if (!(gres[r] <= C.opt.refine_tol)) ok = false;
+    }
+  };
+  // solve k (0: of b, later ones: sweep k) from the host, after `from` iterations
+  // of a graph that ended there, and the check behind it
+  auto solve_and_check = [&](int k, int from) {
+    int it2[kMaxRhs];
+    double rr2[kMaxRhs];
+    int s2 = dd_solve_once<T>(C, k ? C.g_r : b, k ? C.g_t4 : x, nullptr, it2, rr2, nullptr, 0, 0, false, from);
+    if (s2 != DD_OK) status = s2;
+    for (int r = 0; r < nr; ++r) {
+      iters[r] += it2[r];
+      if (k == 0) relres[r] = rr2[r];
+      if (k < 4) solve_iters[k] = std::max(solve_iters[k], it2[r]);
+    }
+    if (k > 0) {
+      hipLaunchKernelGGL(k_axpy, dim3(nblk(n)), dim3(256), 0, st, n, 1.0, (const double*)C.g_t4, x,
+                         (const int*)nullptr);
+      ++sweeps;
+    }
+    check();
+  };
   const bool refine = C.fp32 && C.opt.refine_max > 0;
   if (tx_done) *tx_done = refine && tx != nullptr;
   // The solve as one captured graph once an eager one of its kind has shown how
@@ -2741,21 +2792,25 @@ static int solve_refined(Ctx& C, const double* b, double* x, Ctx::Warm* warm, dd
   // two from load to load do not capture again.  The larger of the last two
   // counts is taken: an iteration too few costs a sweep (two to spare in every
   // graph instead cost 130 us of 1330 at 21^3, 60 boxes, 7 RHS).
+  // In a step a solve that stops early leaves the rest to the refinement.  The
+  // other calls depend on their inputs alone, as an eager one does, in result and
+  // in status: the graph ends at such a solve and the host finishes it.
   const bool graph = refine && !warm && C.opt.method == 0 && C.nlam > 0 && C.opt.use_graph &&
                      st != nullptr && !C.prof && need.iters > 0;
   if (graph) {
     const int I = std::min(C.opt.cg_max_iter, std::max(need.iters, need.before));
     const int S = std::min({need.sweeps, C.opt.refine_max, kMaxGraphSweeps});
+    const bool stop = kind != kStep;
     Ctx::StepGraph* sg = nullptr;
     for (auto& e : C.step_graphs)
       if (e.g && e.b == b && e.x == x && e.tx == tx && e.sx == sx && e.iters >= I && e.iters <= I + 4 &&
-          e.sweeps == S)
+          e.sweeps == S && e.stop == stop)
         sg = &e;
     if (!sg) {  // the least recently used slot
       sg = &C.step_graphs[0];
       for (auto& e : C.step_graphs)
         if (e.used < sg->used) sg = &e;
-      capture_step<T>(C, *sg, b, x, tx, sx, I, S);
+      capture_step<T>(C, *sg, b, x, tx, sx, I, S, stop);
     }
     sg->used = ++C.step_clock;
     HIPCHK(hipGraphLaunch(sg->g, st));
@@ -2764,14 +2819,19 @@ static int solve_refined(Ctx& C, const double* b, double* x, Ctx::Warm* warm, dd
     const RefineState& R = *C.h_rs;
     for (int r = 0; r < nr; ++r) bn[r] = R.bn[r];
     nonfinite(bn);
-    int need_it = 0;
+    int need_it = 0, unfinished = -1;  // (the solve at which the graph ended)
     bool capped = false;
     for (int k = 0; k <= S; ++k) {
       if (!R.ran[k]) break;
+      if (!R.done[k] && stop) {
+        unfinished = k;
+        break;
+      }
       if (k > 0) ++sweeps;
       for (int r = 0; r < nr; ++r) {
         iters[r] += R.iters[k][r];
-        relres[r] = R.rr0[k][r] > 0 ? std::sqrt(R.rr[k][r] / R.rr0[k][r]) : 0.0;
+        // (of the first solve, as an eager call reports; of the last in a step)
+        if (k == 0 || !stop) relres[r] = R.rr0[k][r] > 0 ? std::sqrt(R.rr[k][r] / R.rr0[k][r]) : 0.0;
         need_it = std::max(need_it, R.iters[k][r]);
         if (k < 4) solve_iters[k] = std::max(solve_iters[k], R.iters[k][r]);
       }
@@ -2783,9 +2843,13 @@ static int solve_refined(Ctx& C, const double* b, double* x, Ctx::Warm* warm, dd
         for (int r = 0; r < nr; ++r) gres[r] = R.gres[k][r];
         break;
       }
-    ok = R.gate[S + 1] != 0;
+    ok = R.gate[S + 1] != 0 && unfinished < 0;
     need.before = need.iters;
     need.iters = capped ? std::min(C.opt.cg_max_iter, 2 * sg->iters) : std::max(need_it, 1);
+    if (unfinished >= 0) {
+      solve_and_check(unfinished, sg->iters);
+      need.iters = std::max(need.iters, solve_iters[std::min(unfinished, 3)]);
+    }
     // g_r holds b - A x of the last iterate whenever the last check failed
   } else {
     // |b|^2 per RHS before the solve: the reference of the refinement, and a
@@ -2806,16 +2870,7 @@ static int solve_refined(Ctx& C, const double* b, double* x, Ctx::Warm* warm, dd
       nonfinite(bn);
     }
     for (int r = 0; r < nr; ++r) solve_iters[0] = std::max(solve_iters[0], iters[r]);
-    if (refine) {
-      csr_launch(C, st, 1, x, nullptr, nullptr, nullptr, b, ca, cb, C.g_r, tx, nullptr, sx);
-      double rn[kMaxRhs];
-      dot_to_host(C, C.g_r, C.g_r, C.P.nint, rn);
-      ok = true;
-      for (int r = 0; r < nr; ++r) {
-        gres[r] = bn[r] > 0 ? std::sqrt(rn[r] / bn[r]) : 0.0;
-        if (!(gres[r] <= C.opt.refine_tol)) ok = false;
-      }
-    }
+    if (refine) check();
   }
   // eager sweeps: all of them without the graph, those beyond it with it
   while (refine && !ok) {
@@ -2823,25 +2878,7 @@ static int solve_refined(Ctx& C, const double* b, double* x, Ctx::Warm* warm, dd
       status = DD_ERR_NO_CONVERGENCE;
       break;
     }
-    int it2[kMaxRhs];
-    double rr2[kMaxRhs];
-    int s2 = dd_solve_once<T>(C, C.g_r, C.g_t4, nullptr, it2, rr2);
-    if (s2 != DD_OK) status = s2;
-    for (int r = 0; r < nr; ++r) {
-      iters[r] += it2[r];
-      if (sweeps + 1 < 4) solve_iters[sweeps + 1] = std::max(solve_iters[sweeps + 1], it2[r]);
-    }
-    hipLaunchKernelGGL(k_axpy, dim3(nblk(n)), dim3(256), 0, st, n, 1.0, (const double*)C.g_t4, x,
-                       (const int*)nullptr);
-    ++sweeps;
-    csr_launch(C, st, 1, x, nullptr, nullptr, nullptr, b, ca, cb, C.g_r, tx, nullptr, sx);
-    double rn[kMaxRhs];
-    dot_to_host(C, C.g_r, C.g_r, C.P.nint, rn);
-    ok = true;
-    for (int r = 0; r < nr; ++r) {
-      gres[r] = bn[r] > 0 ? std::sqrt(rn[r] / bn[r]) : 0.0;
-      if (!(gres[r] <= C.opt.refine_tol)) ok = false;
-    }
+    solve_and_check(sweeps + 1, 0);
   }
   if (refine) {
     // what the captured form of the next solve must hold

@@ -3501,9 +3501,14 @@ __global__ void __launch_bounds__(kScalarThreads) k_refine_check(int k, int nrhs
   }
 }
 
-// snapshot of solve k's CG state (skipped with the solve)
-__global__ void k_cg_snapshot(int k, int nrhs, const CgState* __restrict__ cg, RefineState* __restrict__ rs,
-                              const int* __restrict__ gate) {
+// snapshot of solve k's CG state (skipped with the solve).  With stop, a solve
+// whose iterations were too few ends the graph: its gate closes before the
+// recovery, so that every kernel behind it returns and the vectors of the
+// iteration stay as they are; cgs (the two copies of the state) is marked done
+// for the iterations of later solves, and the state as it stands is kept in
+// stop, from where the host carries on.
+__global__ void k_cg_snapshot(int k, int nrhs, const CgState* cg, CgState* cgs, CgState* __restrict__ stop,
+                              RefineState* __restrict__ rs, int* __restrict__ gate) {
   if (gate && *gate) return;
   const int r = threadIdx.x;
   if (r < nrhs) {
@@ -3515,6 +3520,15 @@ __global__ void k_cg_snapshot(int k, int nrhs, const CgState* __restrict__ cg, R
     rs->ran[k] = 1;
     rs->done[k] = cg->done;
     rs->breakdown[k] = cg->breakdown;
+  }
+  if (!stop || cg->done) return;
+  const int* a = reinterpret_cast<const int*>(cg);
+  int* b = reinterpret_cast<int*>(stop);
+  for (int w = r; w < (int)(sizeof(CgState) / sizeof(int)); w += blockDim.x) b[w] = a[w];
+  __syncthreads();
+  if (r == 0) {
+    cgs[0].done = cgs[1].done = 1;
+    *gate = 1;
   }
 }
 
