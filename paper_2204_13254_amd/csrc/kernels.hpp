@@ -357,12 +357,18 @@ struct FacItem {
   uint32_t ik;  // tile row << 16 | tile column
 };
 
-// 1 / d to FP64 rounding (hardware estimate and two Newton steps): a division
-// in the chain of the 32 pivots cost a third of the diagonal tile's time.
+// v / d from r = recip64(d) (hardware estimate and two Newton steps): the product
+// with the reciprocal and one step on its remainder, rounded as a division rounds
+// it, for normal d, 1 / d and v / d.  (A division with its scaling in the chain of
+// the 32 pivots: 2% of a factorisation at 32^3, 64 boxes, FP64.)
 __device__ __forceinline__ double recip64(double d) {
   double r = __builtin_amdgcn_rcp(d);
   r = __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
   return __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
+}
+__device__ __forceinline__ double quot64(double v, double d, double r) {
+  const double q = v * r;
+  return __builtin_fma(__builtin_fma(-d, q, v), r, q);
 }
 
 __device__ __forceinline__ double lane_value(double v, int lane) {
@@ -377,9 +383,10 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
 // columns on [A | I]: step j subtracts f_r = a_rj / d_j times a_cj from the rows
 // below, with a_cj from lane c and the identity's row j from lane j.  Left in x:
 // the rows of L~^-1 (L~ the unit factor), below them -L~_r L~^-1; in v the
-// unscaled columns; rd = 1 / sqrt(d_r).  Returns nonzero when a pivot is not
-// positive and finite.
-__device__ __forceinline__ int eliminate_16(int r, double (&v)[16], double (&x)[16], double& rd) {
+// unscaled columns; sd = sqrt(d_r).  Returns nonzero when a pivot is not
+// positive or lies towards the ends of the range, where 1 / d overflows or is not
+// normal (invert_wide).
+__device__ __forceinline__ int eliminate_16(int r, double (&v)[16], double (&x)[16], double& sd) {
   int bad = 0;
   double dr = 1.0;
 #pragma unroll
@@ -387,12 +394,13 @@ __device__ __forceinline__ int eliminate_16(int r, double (&v)[16], double (&x)[
 #pragma unroll
   for (int j = 0; j < 16; ++j) {
     double d = lane_value(v[j], j);
-    if (!(d > 0.0) || !isfinite(d)) {
+    if (!(d > 0x1p-900 && d < 0x1p900)) {
       bad = 1;
       d = 1.0;
     }
     if (r == j) dr = d;
-    const double f = r > j ? -(v[j] * recip64(d)) : 0.0;
+    const double u = quot64(v[j], d, recip64(d));
+    const double f = r > j ? -u : 0.0;
 #pragma unroll
     for (int c = 0; c < 16; ++c) {
       if (c > j) v[c] = __builtin_fma(f, lane_value(v[j], c), v[c]);
@@ -400,7 +408,7 @@ __device__ __forceinline__ int eliminate_16(int r, double (&v)[16], double (&x)[
     }
     if (r > j) x[j] = f;
   }
-  rd = 1.0 / sqrt(dr);
+  sd = sqrt(dr);
   return bad;
 }
 
@@ -420,7 +428,7 @@ __device__ __forceinline__ Mfma<double>::acc_t mm16(const double (*p)[kNB + 1], 
 // Inverse of the Cholesky factor of the symmetric tile held in a (lower part
 // used; a is overwritten), returned as xv: thread (rb, c) = (tid / 32, tid % 32)
 // of 256 gets entries (rb + 8u, c) of L^-1 (zero above the diagonal).  Returns
-// nonzero when a pivot is not positive and finite (the same in every thread).
+// nonzero, the same in every thread, as eliminate_16 does.
 // A chain of 32 pivots, so latency is all of it: one wave eliminates 16 columns at
 // a time in its registers and joins the halves on MFMA, without a barrier,
 //   A22 -= L21 L21^T, X21 = X22 (-L~21 L~11^-1).
@@ -444,19 +452,20 @@ __device__ __forceinline__ int potrf_inv_tile(double (*a)[kNB + 1], double (*x)[
       const int o = 16 * h, r = h == 0 ? l & 31 : l & 15;  // rows o + r, columns o..
 #pragma unroll
       for (int c = 0; c < 16; ++c) v[c] = a[o + max(r, c)][o + min(r, c)];
-      double rd;
-      bad |= eliminate_16(r, v, y, rd);
+      double sd;
+      bad |= eliminate_16(r, v, y, sd);
+      const double rd = recip64(sd);
       order();
       if (l < 32 - o) {
 #pragma unroll
         for (int c = 0; c < 16; ++c) {
-          const double rc = lane_value(rd, c);
-          x[o + r][o + c] = r < 16 ? y[c] * rd : y[c];
+          const double sc = lane_value(sd, c), rc = lane_value(rd, c);
+          x[o + r][o + c] = r < 16 ? quot64(y[c], sd, rd) : y[c];
           if (h == 0) {
             if (r < 16)
               x[r][16 + c] = 0.0;
             else
-              a[r][c] = v[c] * rc;
+              a[r][c] = quot64(v[c], sc, rc);
           }
         }
       }
@@ -478,6 +487,43 @@ __device__ __forceinline__ int potrf_inv_tile(double (*a)[kNB + 1], double (*x)[
 #pragma unroll
   for (int u = 0; u < kTile / 256; ++u) xv[u] = x[(tid >> 5) + 8 * u][tid & 31];
   return piv[0] != 0.0;
+}
+
+// The same for every pivot that is positive and finite (nonzero is returned for
+// others only): divisions, a row to a lane, all in LDS.  For the tiles that
+// potrf_inv_tile cannot do; they are rare, so the code is small rather than fast.
+__device__ __forceinline__ int invert_wide(double (*a)[kNB + 1], double (*x)[kNB + 1], double* piv,
+                                           double (&xv)[kTile / 256]) {
+  const int r = threadIdx.x;
+  int bad = 0;
+  if (r < kNB)
+    for (int c = 0; c < kNB; ++c) x[r][c] = r == c ? 1.0 : 0.0;
+  __syncthreads();
+#pragma unroll 1
+  for (int j = 0; j < kNB; ++j) {
+    double d = a[j][j];
+    if (!(d > 0.0) || !isfinite(d)) {
+      bad = 1;
+      d = 1.0;
+    }
+    __syncthreads();
+    if (r > j && r < kNB) {
+      const double f = -(a[r][j] / d);
+#pragma unroll 1
+      for (int c = j + 1; c <= r; ++c) a[r][c] = __builtin_fma(f, a[c][j], a[r][c]);
+#pragma unroll 1
+      for (int c = 0; c <= j; ++c) x[r][c] = __builtin_fma(f, x[j][c], x[r][c]);
+    }
+    if (r == j) piv[j] = sqrt(d);
+    __syncthreads();
+  }
+  if (r < kNB)
+#pragma unroll 1
+    for (int c = 0; c <= r; ++c) x[r][c] /= piv[r];
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kTile / 256; ++u) xv[u] = x[(threadIdx.x >> 5) + 8 * u][threadIdx.x & 31];
+  return bad;
 }
 
 // Items [0, nd): diagonal tiles; [nd, nd + no): off-diagonal tiles (i, k) and
@@ -518,6 +564,10 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2)
     const int nn = chain_list(0, m1, [&](int m) { return fi[m] && fk[m]; }, list, wcnt);
     if (b >= nd && nn == 0) return;
     const T* rk = tiles + tile_index(q, k, 0) * kTile;
+    T* cp = tiles + tile_index(q, i, k) * kTile;
+    T cv[U];  // A_ik, read before the chain (behind it: 2% of a factorisation)
+#pragma unroll
+    for (int u = 0; u < U; ++u) cv[u] = cp[tid + 256 * u];
     chain_rows<T, false>(
         list, nn,
         [&](int m, const T*& ap, const T*& bp) {
@@ -525,23 +575,30 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2)
           bp = rk + (int64_t)m * kTile;  // L_km
         },
         red, sum);
-    T* cp = tiles + tile_index(q, i, k) * kTile;
     if (b >= nd) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) cp[tid + 256 * u] -= sum[u];
+      for (int u = 0; u < U; ++u) cp[tid + 256 * u] = cv[u] - sum[u];
       return;
     }
     double(*a)[kNB + 1] = reinterpret_cast<double(*)[kNB + 1]>(lds);
     double(*x)[kNB + 1] = a + kNB;
+    auto fill = [&] {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      int r0, c0;
-      unswz<T>(tid + 256 * u, r0, c0);
-      a[r0][c0] = (double)cp[tid + 256 * u] - (double)sum[u];
-    }
-    __syncthreads();
+      for (int u = 0; u < U; ++u) {
+        int r0, c0;
+        unswz<T>(tid + 256 * u, r0, c0);
+        a[r0][c0] = (double)cv[u] - (double)sum[u];
+      }
+      __syncthreads();
+    };
+    fill();
     double xv[U];
-    const int bad = potrf_inv_tile(a, x, piv, xv);
+    int bad = potrf_inv_tile(a, x, piv, xv);
+    if (bad) {
+      __syncthreads();  // (piv is read)
+      fill();
+      bad = invert_wide(a, x, piv, xv);
+    }
     T* dp = inv + tile_index(q, k, k) * kTile;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
