@@ -97,7 +97,8 @@ typedef struct {
  * tuning). */
 typedef struct {
   int chunk;          /* longest tile range of one wave: interface-block and corner-row lists */
-  int coarse_chunk;   /* the same for the coarse inverse-factor lists */
+  int coarse_chunk;   /* the same for the coarse inverse-factor lists (left as it is where the
+                         coarse solve is one product with K_cc^-1) */
   int full_chunk;     /* the same for the full r-block lists */
   int full_bucket;    /* length buckets of the full lists' workgroup placement */
   int full_persist;   /* full passes: workgroups of a persistent grid that walks the work
@@ -158,7 +159,9 @@ typedef struct {
                               per CG iteration), unpadded */
   int64_t corner_bytes;    /* bytes of the corner rows Psi_Gamma (read twice per
                               CG iteration), unpadded */
-  int64_t coarse_bytes;    /* bytes of the coarse inverse factor, unpadded */
+  int64_t coarse_bytes;    /* bytes of the coarse inverse factor, unpadded (its nonzero entries
+                              once factored); with up to 64 tile rows those of K_cc^-1, which
+                              a coarse solve then applies in one product */
   int64_t full_bytes;      /* bytes of the interior blocks L_II^-1 (their nonzero tiles' nonzero
                               entries once factored; dense before) */
   int64_t cross_bytes;     /* bytes of the couplings L_GammaI and L_cI of the interface and

@@ -1136,9 +1136,10 @@ static void build_device(Ctx& C, const double* coords) {
     // (summing the symmetric partials inside this pass instead of a reduce on
     // the side stream measured slower: it lengthens the main-stream chain)
     C.corner_T = make_items(C, cT, C.tuning.chunk, false, 1, true);
-    C.co_N = make_items(C, oN, C.tuning.chunk);
-    C.co_T = make_items(C, oT, C.tuning.chunk);
-    if (C.Kc > 0 && C.Kc <= kSquareCoarse) {
+    if (C.Kc > kSquareCoarse) {
+      C.co_N = make_items(C, oN, C.tuning.chunk);
+      C.co_T = make_items(C, oT, C.tuning.chunk);
+    } else if (C.Kc > 0) {
       std::vector<MvItem> sq;
       for (int o = 0; o < C.Kc; ++o) sq.push_back({nsub, o, 0, C.Kc, -1, 0});
       C.co_inv = make_items(C, sq, kSquareCoarse);
@@ -1146,6 +1147,8 @@ static void build_device(Ctx& C, const double* coords) {
       HIPCHK(hipMalloc(&p, (size_t)C.Kc * C.Kc * kTile * wsz));
       C.owned.push_back(p);
       C.co_inv.square = C.d_kinv = p;
+      C.factor_bytes += (int64_t)C.Kc * C.Kc * kTile * (int64_t)wsz;
+      C.coarse_bytes = nc * nc * (int64_t)wsz;
     }
     C.blk_corner_N.swap(cN);
     C.blk_corner_T.swap(cT);
@@ -1245,7 +1248,8 @@ static void factor_lists(Ctx& C) {
   };
   auto ik = [](int i, int k) { return (uint32_t)i << 16 | (uint32_t)k; };
   std::vector<FacItem> psi;
-  auto blocks = [&](int s0, int s1, Ctx::FacList& F) {
+  // pk: the tiles of the block are read by solves
+  auto blocks = [&](int s0, int s1, bool pk, Ctx::FacList& F) {
     std::vector<std::vector<FacItem>> diag, off, inv;
     std::vector<FacItem> corner;
     F.pack = (int64_t)pack.size();
@@ -1268,11 +1272,11 @@ static void factor_lists(Ctx& C) {
             corner.push_back({s, ik(i, j)});
           } else if (i == j) {
             diag[lev[j]].push_back({s, ik(i, j)});
-            if (j < kI) pack.push_back(tile(i, j) << 1 | 1);
+            if (pk && j < kI) pack.push_back(tile(i, j) << 1 | 1);
           } else {
             if (f & kSymL) off[lev[j]].push_back({s, ik(i, j)});
             if (f & kSymInv) inv[lev[i]].push_back({s, ik(i, j)});
-            if (j < kI) {
+            if (pk && j < kI) {
               // L_II^-1; L_GI and L_cI as factored
               if (i < kI && (f & kSymInv)) pack.push_back(tile(i, j) << 1 | 1);
               if (i >= kI && (f & kSymL)) pack.push_back(tile(i, j) << 1);
@@ -1300,8 +1304,8 @@ static void factor_lists(Ctx& C) {
       F.steps.push_back(st);
     }
   };
-  blocks(0, C.nsub, sub);
-  blocks(C.nsub, C.nsub + (C.Kc > 0 ? 1 : 0), coarse);
+  blocks(0, C.nsub, true, sub);
+  blocks(C.nsub, C.nsub + (C.Kc > 0 ? 1 : 0), !C.d_kinv, coarse);
   C.psi_first = (int64_t)fac.size();
   C.n_psi = place(psi);
   if (fac.size() >= (size_t)INT32_MAX || pack.size() >= (size_t)INT32_MAX)
@@ -1689,7 +1693,7 @@ static int factor_impl(Ctx& C) {
     std::vector<int32_t> info(C.ntiles);
     HIPCHK(hipMemcpyAsync(info.data(), C.d_tinfo, C.ntiles * sizeof(int32_t), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
-    if (C.Kc > 0) coarse_tile_lists<T>(C, info);
+    if (C.Kc > 0 && !C.d_kinv) coarse_tile_lists<T>(C, info);
     full_tile_lists<T>(C, info);
     C.pattern_valid = true;
   }
@@ -3365,8 +3369,8 @@ static void autotune_impl(Ctx& C, dd_tuning* out) {
     }
     C.tuning = best;
   }
-  if (C.Kc > 0 && C.coarse_lists) {
-    r.coarse_ms_default = r.coarse_ms = timed(coarse);
+  if (C.Kc > 0) r.coarse_ms_default = r.coarse_ms = timed(coarse);
+  if (C.coarse_lists) {
     for (int cc : {8, 12, 16, 24, 32, 48}) {
       C.tuning.coarse_chunk = cc;
       rebuild_lists<T>(C, 2);

@@ -116,8 +116,11 @@ static int give(void** p) {
 int hipEventCreate(void** e) { return give(e); }
 int hipEventCreateWithFlags(void** e, unsigned) { return give(e); }
 int hipEventDestroy(void*) { return 0; }
+// every interval shorter than the one before, so that a timed search takes
+// whatever it times last
 int hipEventElapsedTime(float* ms, void*, void*) {
-  *ms = 1.0f;
+  static float t = 1000.0f;
+  *ms = t *= 0.999f;
   return 0;
 }
 int hipEventRecord(void*, void*) { return 0; }
@@ -141,7 +144,10 @@ int hipGetDevice(int* d) {
   *d = 0;
   return 0;
 }
-int hipGetDevicePropertiesR0600(void*, int) { return 0; }
+int hipGetDevicePropertiesR0600(void* p, int) {
+  std::memset(p, 0, 1472);  // sizeof(hipDeviceProp_t)
+  return 0;
+}
 int hipGetSymbolAddress(void** p, const void*) { return give(p); }
 int hipGetLastError() { return 0; }
 const char* hipGetErrorString(int) { return "stub"; }

@@ -88,3 +88,27 @@ def test_factor_after_a_refused_allocation(stub, precision):
         assert stub.stub_launches(b"k_chol_trsm") == trsm, k
         lib.dd_destroy(h)
     """)
+
+
+@pytest.mark.parametrize("precision,word", [(0, 8), (1, 4)])
+def test_coarse_block_solved_by_its_inverse(stub, precision, word):
+    # up to 64 tile rows a coarse solve is one product with K_cc^-1: the byte counts
+    # are those of that store, the inverse factor's tiles are not packed for a pass
+    # that does not exist, and the tuner does not choose a chunk that nothing reads
+    _run(stub, f"""
+    h = context(6, 3, precision={precision})
+    info, before = dd.Info(), dd.Info()
+    stub.stub_clear_counts()
+    assert lib.dd_get_info(h, C.byref(before)) == 0
+    assert lib.dd_factor(h) == 0 and lib.dd_get_info(h, C.byref(info)) == 0
+    nc, rows = info.n_corner, -(-info.n_corner // info.tile)
+    assert 0 < rows <= 64
+    for i in (before, info):
+        assert i.coarse_bytes == nc * nc * {word}, (i.coarse_bytes, nc)
+        assert i.factor_bytes % (info.tile ** 2 * {word}) == 0
+    assert stub.stub_launches(b"k_coarse_inv") == 1 and stub.stub_launches(b"k_pack_tiles") == 1
+    t = dd.Tuning()
+    assert lib.dd_autotune(h, None, C.byref(t)) == 0
+    assert t.coarse_ms == t.coarse_ms_default > 0, (t.coarse_ms, t.coarse_ms_default)
+    assert t.trailing_ms < t.trailing_ms_default
+    """)
