@@ -593,14 +593,9 @@ static void make_sym_list(Ctx& C, int pw, size_t wsz) {
   C.sym.d = upload(placed, C.owned, C.st);
   C.sym.n_out = (int64_t)outs.size();
   C.sym.outs = upload(outs, C.owned, C.st);
-  void* p = nullptr;
-  HIPCHK(hipMalloc(&p, std::max<int64_t>(1, slot) * kTile * C.nrhs * wsz / NB));
-  C.owned.push_back(p);
-  C.sym.partial = p;
-  HIPCHK(hipMalloc(&p, kTile * wsz));
-  C.owned.push_back(p);
-  HIPCHK(hipMemsetAsync(p, 0, kTile * wsz, C.st));
-  C.sym.zero = p;
+  C.sym.partial = dalloc<uint8_t>(std::max<int64_t>(1, slot) * kNB * C.nrhs * wsz, C.owned);
+  C.sym.zero = dalloc<uint8_t>(kTile * wsz, C.owned);
+  HIPCHK(hipMemsetAsync(C.sym.zero, 0, kTile * wsz, C.st));
 }
 
 // Right-hand sides per lane in the vector forms of the multiplier-space
@@ -1143,19 +1138,13 @@ static void build_device(Ctx& C, const double* coords) {
       std::vector<MvItem> sq;
       for (int o = 0; o < C.Kc; ++o) sq.push_back({nsub, o, 0, C.Kc, -1, 0});
       C.co_inv = make_items(C, sq, kSquareCoarse);
-      void* p = nullptr;
-      HIPCHK(hipMalloc(&p, (size_t)C.Kc * C.Kc * kTile * wsz));
-      C.owned.push_back(p);
-      C.co_inv.square = C.d_kinv = p;
+      C.co_inv.square = C.d_kinv = dalloc<uint8_t>((size_t)C.Kc * C.Kc * kTile * wsz, C.owned);
       C.factor_bytes += (int64_t)C.Kc * C.Kc * kTile * (int64_t)wsz;
       C.coarse_bytes = nc * nc * (int64_t)wsz;
     }
     C.blk_corner_N.swap(cN);
     C.blk_corner_T.swap(cT);
-    void* p = nullptr;
-    HIPCHK(hipMalloc(&p, std::max<int64_t>(1, C.max_slots) * kTile * C.nrhs * wsz / NB));
-    C.owned.push_back(p);
-    C.d_partial_mv = p;
+    C.d_partial_mv = dalloc<uint8_t>(std::max<int64_t>(1, C.max_slots) * kNB * C.nrhs * wsz, C.owned);
     C.partial_slots = std::max<int64_t>(1, C.max_slots);
   }
   // ---- work vectors --------------------------------------------------------------------
@@ -1364,10 +1353,7 @@ static void release_items(Ctx& C, Items& it) {
 template <class T>
 static void ensure_partial(Ctx& C) {
   if (C.max_slots <= C.partial_slots) return;
-  void* p = nullptr;
-  HIPCHK(hipMalloc(&p, C.max_slots * kNB * C.nrhs * sizeof(T)));
-  C.owned.push_back(p);
-  C.d_partial_mv = p;
+  C.d_partial_mv = dalloc<uint8_t>(C.max_slots * kNB * C.nrhs * sizeof(T), C.owned);
   C.partial_slots = C.max_slots;
 }
 

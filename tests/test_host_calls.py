@@ -27,7 +27,7 @@ lib = dd.load()
 from workloads.mesh import cube_mesh
 from workloads.partition import box_partition
 
-def context(n, parts, **opt):
+def context(n, parts, want=0, **opt):
     c, t, _ = cube_mesh(n)
     c, t = np.ascontiguousarray(c, np.float64), np.ascontiguousarray(t, np.int32)
     p = np.ascontiguousarray(box_partition(n, parts), np.int32)
@@ -40,7 +40,7 @@ def context(n, parts, **opt):
     m = dd.Mesh(len(c), ptr(c), len(t), ptr(t))
     h = C.c_void_p()
     rc = lib.dd_setup(C.byref(h), C.byref(m), ptr(p), ptr(eps), None, 0.05, 0.25, C.byref(o))
-    assert rc == 0, rc
+    assert rc == want and (rc != 0) == (not h.value), rc
     return h
 """
 
@@ -111,4 +111,20 @@ def test_coarse_block_solved_by_its_inverse(stub, precision, word):
     assert lib.dd_autotune(h, None, C.byref(t)) == 0
     assert t.coarse_ms == t.coarse_ms_default > 0, (t.coarse_ms, t.coarse_ms_default)
     assert t.trailing_ms < t.trailing_ms_default
+    """)
+
+
+@pytest.mark.parametrize("parts", [1, 3])
+def test_setup_without_memory_says_so(stub, parts):
+    # each allocation of dd_setup refused in turn: DD_ERR_OOM and no context (a
+    # DD_ERR_HIP would tell the caller that the device is lost)
+    _run(stub, f"""
+    stub.stub_fail_at(0)
+    lib.dd_destroy(context(4, {parts}))
+    allocs = stub.stub_mallocs()
+    assert allocs > 20
+    for k in range(1, allocs + 1):
+        stub.stub_fail_at(k)
+        context(4, {parts}, want=-8)
+        assert b"alloc" in lib.dd_last_error(), lib.dd_last_error()
     """)
