@@ -308,6 +308,7 @@ int dd_energy(void* ctx, const double* E_next, const double* E_n, double* out);
  * positions and velocities are [n][3] float64 row-major; cell[p] is a
  * tetrahedron index in the dd_setup order, or -1 for an inactive particle.
  * Mesh tables for these calls (face neighbours, per-tetrahedron geometry)
+ * and scratch for dd_pic_sort (32 bytes per tetrahedron, at least 16 MiB)
  * are built on the first call (allocates and synchronises once).  After
  * that the particle calls only enqueue work on the context stream: what
  * they find (absorbed particles, bad indices) goes to device counters that

@@ -3665,35 +3665,7 @@ static void build_dp2(Ctx& C, const double* coords, const double* eps, const dou
   HIPCHK(hipHostMalloc((void**)&C.h_gm_st, sizeof(GmState), hipHostMallocDefault));
 }
 
-// Room for the places of n particles, or null: inside a capture, and where the
-// device has no memory left, the ordering does without.  A smaller buffer is
-// kept until the context ends (a captured call may hold it); each is at least
-// twice the one before, the first holds eight particles a tetrahedron.
-static int32_t* pic_rank(Ctx& C, int64_t n) {
-  if (n <= C.pic_rank_cap) return C.d_pic_rank;
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(C.st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    return nullptr;
-  }
-  // (relaxed: the caller may be capturing another stream)
-  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-  HIPCHK(hipThreadExchangeStreamCaptureMode(&mode));
-  const int64_t cap = std::max(n, 2 * C.pic_rank_cap);
-  int32_t* d = nullptr;
-  const hipError_t e = hipMalloc((void**)&d, (size_t)cap * sizeof(int32_t));
-  HIPCHK(hipThreadExchangeStreamCaptureMode(&mode));
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    return nullptr;
-  }
-  C.owned.push_back(d);
-  C.d_pic_rank = d;
-  C.pic_rank_cap = cap;
-  return d;
-}
-
-// ---- particle tables (built on the first particle call) --------------------------
+// ---- particle tables (built on the first particle or mixed call) ------------------
 static void pic_prepare(Ctx& C) {
   if (C.d_pic_geo) return;
   const Plan& P = C.P;
@@ -3709,7 +3681,19 @@ static void pic_prepare(Ctx& C) {
   double* geo = dalloc<double>((size_t)P.nt * 12, C.owned);
   hipLaunchKernelGGL(k_tet_geo, dim3(nblk(P.nt)), dim3(256), 0, C.st, (int64_t)P.nt, C.d_coords, C.d_tsort, geo);
   HIPCHK(hipGetLastError());
-  pic_rank(C, 8 * (int64_t)P.nt);
+  // room for the places of an ordering (k_cell_hist), laid out here because only
+  // the first call may allocate (a later one may be captured): eight particles a
+  // tetrahedron, at least 16 MiB; an ordering of more, or on a device without that
+  // memory, does without
+  const int64_t room = std::max<int64_t>(8 * (int64_t)P.nt, 1 << 22);
+  void* places = nullptr;
+  if (hipMalloc(&places, (size_t)room * sizeof(int32_t)) == hipSuccess) {
+    C.owned.push_back(places);
+    C.d_pic_rank = (int32_t*)places;
+    C.pic_rank_cap = room;
+  } else {
+    (void)hipGetLastError();
+  }
   C.d_pic_geo = geo;
 }
 
@@ -4328,7 +4312,7 @@ int dd_pic_sort(void* ctx, int64_t n, const int32_t* cell, int32_t* perm) {
   pic_prepare(C);
   if (n == 0) return DD_OK;
   const int64_t nt = C.P.nt, m = nt + 1, nb = (m + kScanBlock - 1) / kScanBlock;
-  int32_t* rank = pic_rank(C, n);
+  int32_t* rank = n <= C.pic_rank_cap ? C.d_pic_rank : nullptr;
   // a fill kernel, not a memset: this call may be captured into a graph
   hipLaunchKernelGGL(k_zero_i32, dim3(nblk(m)), dim3(256), 0, C.st, m, C.d_pic_count);
   if (rank)

@@ -128,3 +128,24 @@ def test_setup_without_memory_says_so(stub, parts):
         context(4, {parts}, want=-8)
         assert b"alloc" in lib.dd_last_error(), lib.dd_last_error()
     """)
+
+
+def test_particle_calls_do_not_allocate_after_the_first(stub):
+    # the first particle call builds the tables; an ordering of any number of
+    # particles only enqueues work then, with or without room for their places
+    _run(stub, """
+    h = context(4, 2)
+    stub.stub_fail_at(0)
+    assert lib.dd_pic_status(h, None, 0) == 0
+    assert stub.stub_mallocs() > 0
+    stub.stub_fail_at(0)
+    buf = np.zeros(16, np.int32)          # (kernels do not run: never read)
+    ptr = buf.ctypes.data_as(C.c_void_p)
+    stub.stub_clear_counts()
+    sizes = (1000, 8 * 384, 8 * 384 + 1, 1 << 22, (1 << 22) + 1, 2 ** 31 - 1)
+    for n in sizes:
+        assert lib.dd_pic_sort(h, n, ptr, ptr) == 0
+        assert stub.stub_mallocs() == 0, n
+    places, cursors = stub.stub_launches(b"k_cell_place"), stub.stub_launches(b"k_cell_scatter")
+    assert places == 4 and cursors == 2, (places, cursors)
+    """)
