@@ -1836,8 +1836,6 @@ static void mv(Ctx& C, const Items& it, bool trans, const void* in, void* out, c
   if (timed) HIPCHK(hipEventRecord(e1, C.st));
 }
 
-// fork: work queued on st so far is visible to the side stream; join: the
-// side stream's work is visible to everything queued on st afterwards
 // per-RHS block partials of x . y over n rows [n][nrhs] (dot_blocks blocks)
 static void dot_partial(Ctx& C, hipStream_t st, int64_t n, const double* x, const double* y, double* partial,
                         const int* skip) {
@@ -1916,6 +1914,8 @@ static void scatter_dot(Ctx& C, const T* u, const T* u2, double* Fp, const doubl
                        Fp, p, nr, C.d_partial, skip);
 }
 
+// fork: work queued on st so far is visible to the side stream; join: the
+// side stream's work is visible to everything queued on st afterwards
 static void fork_side(Ctx& C) {
   HIPCHK(hipEventRecord(C.ev_fork, C.st));
   HIPCHK(hipStreamWaitEvent(C.st2, C.ev_fork, 0));

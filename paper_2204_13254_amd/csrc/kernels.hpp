@@ -54,20 +54,6 @@ struct Mfma<double> {
   static __device__ __forceinline__ int row(int l, int v) { return (l >> 4) + 4 * v; }
 };
 
-// One wave's 16x16 block (mb, nb) of a 32x32 tile product from LDS tiles:
-// BT ? A B^T : A B, accumulated into acc.
-template <class T, bool BT>
-__device__ __forceinline__ void tile_mma(const T (*A)[kNB + 1], const T (*B)[kNB + 1], int mb, int nb, int l,
-                                         typename Mfma<T>::acc_t& acc) {
-  const int i = l & 15, g = l >> 4;
-#pragma unroll
-  for (int ks = 0; ks < kNB / 4; ++ks) {
-    const T a = A[mb * 16 + i][ks * 4 + g];
-    const T b = BT ? B[nb * 16 + i][ks * 4 + g] : B[ks * 4 + g][nb * 16 + i];
-    acc = Mfma<T>::op(a, b, acc);
-  }
-}
-
 // List, in increasing order, of the m in [m0, m1) with ok(m), built by the
 // whole 256-thread workgroup with ballots (list holds m1 - m0 entries, m1 <=
 // 65536); returns the count.  Every thread must call it.
@@ -1139,7 +1125,8 @@ __global__ void __launch_bounds__(64 * kRowWaves) k_tile_mvw(const MvItem* __res
   }
 }
 
-// Row-pair form of k_tile_mv for the full passes (MFMA path, 9..32 RHS):
+// Row-pair form of k_tile_mv for the full passes (9..32 RHS, a limit of this form;
+// the MFMA path of k_tile_mv starts at 3):
 // one wave computes the output blocks o and o2 of one subdomain over the
 // union of their tile lists, so each input block is loaded once for both
 // rows (the input loads cost about as much as a tile's own once they are
@@ -1268,7 +1255,7 @@ __global__ void __launch_bounds__(256) k_tile_mv2(int64_t n_items, const MvItem*
   }  // groups
 }
 
-// Row-octet form for the full passes (MFMA path, 9..32 RHS): a workgroup
+// Row-octet form for the full passes (9..32 RHS, as the row pairs): a workgroup
 // item covers up to 8 consecutive output rows o .. o + w.o2 - 1 of one
 // subdomain over the union of their tile lists; each entry's input block is
 // staged once in LDS (transposed: a lane's 8 reduction values are
