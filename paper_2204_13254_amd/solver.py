@@ -114,7 +114,8 @@ class DDSolver:
     @property
     def info(self):
         """Sizes and byte counts (the coarse byte count reflects the stored
-        nonzero tiles once the context is factorised)."""
+        nonzero tiles once the context is factorised, or K_cc^-1 where a small
+        coarse block is solved by it)."""
         inf = Info()
         check(self.lib.dd_get_info(self.h, C.byref(inf)))
         return inf
