@@ -97,3 +97,35 @@ def test_results_do_not_depend_on_the_calls_before(kind, n, parts, nrhs, opt):
         assert torch.equal(got, want[k]), f"call {call}, load {k}: largest difference {d:.3e}"
         if kind != "adjoint":
             assert counts(c.s) == stats[k], f"call {call}, load {k}"
+
+
+def test_a_refinement_sweep_left_unfinished():
+    # single entries need as many iterations in both solves as the first solve of a
+    # random load, whose sweep needs more: the graph ends behind the first check
+    def solve_iters(s):
+        return tuple(s.stats.solve_iters)
+
+    opt = dict(cg_tol=1e-6)
+    c = _Calls(8, 2, 2, **opt)
+    _, (one, _), _ = _loads(c)
+    c("solve", one, None)
+    few = max(solve_iters(c.s))
+    e, pec = c.s.edges()
+    free = np.flatnonzero(~pec)
+    for seed in range(8):
+        load = torch.zeros_like(one)
+        load[:, torch.as_tensor(free, device="cuda")] = torch.tensor(
+            np.random.default_rng(seed).standard_normal((2, len(free))), device="cuda")
+        torch.cuda.synchronize()
+        fresh = _Calls(8, 2, 2, **opt)
+        want = fresh("solve", load, None)
+        iters = solve_iters(fresh.s)
+        if iters[0] <= few < iters[1]:
+            break
+    else:
+        pytest.fail(f"no load of that kind (single entries {few}, the last one {iters})")
+    for _ in range(2):
+        c("solve", one, None)
+    got = c("solve", load, None)
+    assert torch.equal(got, want) and solve_iters(c.s) == iters
+    assert c.s.stats.refine_sweeps == fresh.s.stats.refine_sweeps
